@@ -191,16 +191,25 @@ unsigned *order_table_for(hipStream_t stream)
 }
 
 // Out-of-place launch: one workgroup per (gossiping row, chunk of waves * 64 * U slices).
+//
+// Short rows: a workgroup of the operator's full size would leave too few chunks to deal out evenly to eight
+// XCDs, so the workgroup is halved until there are kMinChunks of them (or it is one wavefront): 13 or more
+// chunks per XCD keep the uneven last one below 8 %.  512 rows x 100,003 fp32 columns: 98 chunks of 4 waves.
+constexpr int64_t kMinChunks = 104;
 template <class Op, int U>
-bool try_gather(const Op &op, int want_u, int waves, int nt, int cl_req, int xcd_aware, const MixArgs &a,
-                int *status)
+bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, int cl_req, int xcd_aware,
+                const MixArgs &a, int *status)
 {
     if (want_u != U) return false;
     if constexpr (U > MaxSlices<Op>::value) {
         return false;
     } else {
+    const int64_t wave_cols = static_cast<int64_t>(kWave) * Op::kElems * U;
+    const int full_waves = waves;
+    while (!waves_fixed && xcd_aware && waves > 1 && a.P <= (kMinChunks - 1) * wave_cols * waves) waves /= 2;
     const int64_t chunk_cols = static_cast<int64_t>(kWave) * Op::kElems * U * waves;
     const int64_t nchunks = (a.P + chunk_cols - 1) / chunk_cols;
+    if (nchunks < 8) xcd_aware = 0;               // fewer chunks than XCDs: rows go round the XCDs instead
     const int nxcd = xcd_aware ? 8 : 1;
     // Rows in cycle order pay when the partner's fetch has to be kept out of HBM; a matrix that
     // the last-level cache holds whole gains nothing from the extra launch.
@@ -216,7 +225,7 @@ bool try_gather(const Op &op, int want_u, int waves, int nt, int cl_req, int xcd
         order = order_table_for(a.stream);
         if (!order) ordered = false;
     }
-    int64_t cl = cl_req;
+    int64_t cl = cl_req, least_cl = 1;
     if (cl < 1) {
         // ordered rows: the operator's visit length per XCD (shorter visits lose DRAM row
         // locality, longer ones push the previous visit out of L2);
@@ -234,7 +243,16 @@ bool try_gather(const Op &op, int want_u, int waves, int nt, int cl_req, int xcd
                 if (own_table) { *status = CX_ERR_SHAPE; return true; }       // beyond the stated maximum
                 cl = min_cl;
             }
+            least_cl = min_cl;
         }
+    }
+    if (cl_req < 1) {
+        // An XCD works through every nxcd-th cluster.  Clusters are shortened until the last round of clusters
+        // is as full as the others: 512 rows x 100,003 fp32 columns are 98 chunks, and clusters of the full 64
+        // would put them all on two of the eight XCDs (439 us a call; dealt out evenly 89 us).
+        const int64_t rounds = (nchunks + cl * nxcd - 1) / (cl * nxcd);
+        cl = (nchunks + rounds * nxcd - 1) / (rounds * nxcd);
+        if (cl < least_cl) cl = least_cl;
     }
     if (cl > 4096) cl = 4096;
     int64_t clusters = (nchunks + cl * nxcd - 1) / (cl * nxcd);
@@ -266,7 +284,7 @@ bool try_gather(const Op &op, int want_u, int waves, int nt, int cl_req, int xcd
         if (hipGetLastError() != hipSuccess) { *status = CX_ERR_HIP; return true; }
     }
     int cap = cx_get_tuning(9);
-    if (cap < 0 || cap > 16) cap = Op::kGather.wgs_per_cu;
+    if (cap < 0 || cap > 16) cap = Op::kGather.wgs_per_cu * full_waves / waves;   // the same waves per CU
     size_t glds = lds_reservation(cap);
     if (LdsStaged<Op>::value && glds < LdsStaged<Op>::bytes) glds = LdsStaged<Op>::bytes;
     if (glds < static_cast<size_t>(StageBytes<Op>::value) * waves) glds = static_cast<size_t>(StageBytes<Op>::value) * waves;
@@ -296,14 +314,15 @@ int launch_mix(const Op &op, const MixArgs &a)
         while (u > 1 && Op::kRawPerSlice * u > 8) u >>= 1;   // the rows in flight must fit the registers
         if (Op::kRawPerSlice >= 8 || u > MaxSlices<Op>::value) u = 1;
         int waves = cx_get_tuning(1);
-        if (waves < 1 || waves > kMaxWavesPerBlock) waves = Op::kGather.waves;
+        const bool waves_fixed = waves >= 1 && waves <= kMaxWavesPerBlock;
+        if (!waves_fixed) waves = Op::kGather.waves;
         const int nt = cx_get_tuning(2) == 0 ? 0 : 1;
         const int cl = cx_get_tuning(6);
         const int xcd_aware = cx_get_tuning(7) == 0 ? 0 : 1;
         int status = CX_OK;
-        if (try_gather<Op, 1>(op, u, waves, nt, cl, xcd_aware, a, &status) ||
-            try_gather<Op, 2>(op, u, waves, nt, cl, xcd_aware, a, &status) ||
-            try_gather<Op, 4>(op, u, waves, nt, cl, xcd_aware, a, &status))
+        if (try_gather<Op, 1>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status) ||
+            try_gather<Op, 2>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status) ||
+            try_gather<Op, 4>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status))
             return status;
     }
     Launch l = pick_launch(Op::kWalk);

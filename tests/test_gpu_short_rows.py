@@ -1,0 +1,67 @@
+"""Short rows out of place: where the launch halves its workgroups and shortens its clusters so that every XCD
+gets its share of the column chunks, and where there are too few chunks for that.  Row lengths on both sides of
+each edge of the rule (fewer than eight chunks, kMinChunks chunks of 1, 2, 4 and 8 waves), natural and cycle order."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2012_15198_amd import cxmix as cx
+from paper_2012_15198_amd import workloads as WL
+from gpu_util import Tuning, dev, host, once, same_bits
+
+pytestmark = pytest.mark.gpu
+
+TILE = 256                                                     # columns of one wavefront on fp32 rows
+EDGES = [TILE * 7, TILE * 8, TILE * 103, TILE * 206, TILE * 412, TILE * 824]
+
+
+@pytest.mark.parametrize("ordered", [-1, 1])
+@pytest.mark.parametrize("P", sorted(e + d for e in EDGES for d in (0, 1)))
+@pytest.mark.parametrize("kind", ["gossip", "hier", "fused", "bf16"])
+def test_short_rows(kind, P, ordered):
+    W, G, S = 6, 3, 3
+    ld = (P + 7) // 8 * 8
+    so = np.array([0, P // 3 + 1, P - 2, P], dtype=np.int64)
+    x = WL.gen_matrix(W, P, 0.05, seed=P, ld=ld)
+    print(kind, P, ordered, flush=True)
+    with Tuning(ordered=ordered):
+        if kind == "bf16":
+            pe = O.topology(P, W, S, 0, 1)[0]
+            xb = O.f32_to_bf16(x)
+            a = dev(xb.view(np.int16))
+            b = torch.zeros_like(a)
+            cx.cx_gossip_mix_bf16(a, b, P, dev(so), dev(pe))
+            assert (host(b).view(np.uint16)[:, :P] == O.gossip_mix_bf16(xb, P, so, pe)[:, :P]).all()
+            return
+        a, b = dev(x), torch.full((W, ld), float("nan"), device="cuda:0")
+        if kind == "gossip":
+            pe = O.topology(P, W, S, 0, 1)[0]
+            cx.cx_gossip_mix(a, b, P, dev(so), dev(pe))
+            want = O.gossip_mix(x, P, so, pe)
+        elif kind == "hier":
+            pe = O.topology(P, W // G, S, 0, 1)[0]
+            cx.cx_hier_mix(a, b, P, G, dev(so), dev(pe))
+            want = once(O.hier_mix_f64(x, P, G, so, pe))
+        else:
+            pe = O.topology(P, W, S, 0, 1)[0]
+            v, g = (WL.gen_matrix(W, P, s, seed=P, ld=ld, stream=k) for s, k in ((0.02, 1), (0.01, 2)))
+            vo = torch.zeros_like(a)
+            cx.cx_sgd_fused_mix(a, b, dev(v), vo, dev(g), 0.1, 0.9, 1e-4, P, dev(so), dev(pe))
+            want, wv = (once(t) for t in O.sgd_fused_mix_f64(x, v, g, 0.1, 0.9, 1e-4, P, so, pe))
+            assert same_bits(host(vo)[:, :P], wv[:, :P])
+        assert same_bits(host(b)[:, :P], want[:, :P])
+
+
+@pytest.mark.parametrize("W", [2, 257, 1024])
+def test_rows_of_one_column_to_one_chunk(W):
+    for P in (1, 3, 255, 257, 1000):
+        ld = (P + 3) // 4 * 4
+        x = WL.gen_matrix(W, P, 0.05, seed=P, ld=ld)
+        pe = O.topology(P, W, 1, 0, 1)[0]
+        so = np.array([0, P], dtype=np.int64)
+        a = dev(x)
+        for call in (cx.cx_gossip_mix, cx.cx_gossip_mix_noalloc):
+            b = torch.full((W, ld), float("nan"), device="cuda:0")
+            call(a, b, P, dev(so), dev(pe))
+            assert same_bits(host(b)[:, :P], O.gossip_mix(x, P, so, pe)[:, :P])
