@@ -29,11 +29,8 @@ __device__ __forceinline__ void tile_load16(const uint16_t *p, const unsigned (&
             const f4 *q = reinterpret_cast<const f4 *>(p + u * (kWave * 8));
             raw.v[u] = NT ? __builtin_nontemporal_load(q) : *q;
         } else {
-            u4 w = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if ((mask[u] >> e) & 1u) w[e >> 1] |= static_cast<unsigned>(p[u * (kWave * 8) + e]) << (16 * (e & 1));
-            raw.v[u] = __builtin_bit_cast(f4, w);
+            raw.v[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};             // boundary tiles: as in tile_load
+            if (mask[u] != 0) raw.v[u] = *reinterpret_cast<const f4 *>(p + u * (kWave * 8));
         }
     }
 }
@@ -48,11 +45,15 @@ __device__ __forceinline__ void tile_store16(uint16_t *p, const unsigned (&mask)
             f4 *q = reinterpret_cast<f4 *>(p + u * (kWave * 8));
             if (NT) __builtin_nontemporal_store(raw.v[u], q); else *q = raw.v[u];
         } else {
-            const u4 w = __builtin_bit_cast(u4, raw.v[u]);
+            if (mask[u] == 0xffu) {
+                *reinterpret_cast<f4 *>(p + u * (kWave * 8)) = raw.v[u];
+            } else {
+                const u4 w = __builtin_bit_cast(u4, raw.v[u]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if ((mask[u] >> e) & 1u)
-                    p[u * (kWave * 8) + e] = static_cast<uint16_t>(w[e >> 1] >> (16 * (e & 1)));
+                for (int e = 0; e < 8; ++e)
+                    if ((mask[u] >> e) & 1u)
+                        p[u * (kWave * 8) + e] = static_cast<uint16_t>(w[e >> 1] >> (16 * (e & 1)));
+            }
         }
     }
 }
@@ -244,8 +245,8 @@ struct Push16Op : Row16Op<IEEE_HALF, 1> {
 // cache line to the other access, and the fused step runs 7 % slower.  So whole slices of the
 // fp32 rows move between memory and registers in MEMORY order (register hh of lane l = columns
 // 256*hh + 4*l .. +3: each access of the wavefront one contiguous KB) and change to the lane's own
-// columns through 2 KB of LDS per wavefront (stage_to_own / stage_from_own).  Boundary tiles,
-// handled element by element, address the lane's own columns directly.
+// columns through 2 KB of LDS per wavefront (stage_to_own / stage_from_own).  Boundary tiles
+// address the lane's own columns directly.
 template <int U, bool FULL, bool NT>
 __device__ __forceinline__ void tile_load8(const float *p, const unsigned (&mask)[U], Tile<2 * U> &t)
 {
@@ -260,8 +261,8 @@ __device__ __forceinline__ void tile_load8(const float *p, const unsigned (&mask
                 t.v[2 * u + hh] = NT ? __builtin_nontemporal_load(q4) : *q4;
             } else {
                 const float *q = p + u * (kWave * 8) + 4 * hh;                                           // own columns
-#pragma unroll
-                for (int e = 0; e < 4; ++e) t.v[2 * u + hh][e] = ((mask[u] >> (4 * hh + e)) & 1u) ? q[e] : 0.0f;
+                t.v[2 * u + hh] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (((mask[u] >> (4 * hh)) & 0xfu) != 0) t.v[2 * u + hh] = *reinterpret_cast<const f4 *>(q);
             }
         }
 }
@@ -279,9 +280,13 @@ __device__ __forceinline__ void tile_store8(float *p, const unsigned (&mask)[U],
                 if (NT) __builtin_nontemporal_store(t.v[2 * u + hh], q4); else *q4 = t.v[2 * u + hh];
             } else {
                 float *q = p + u * (kWave * 8) + 4 * hh;
+                if (((mask[u] >> (4 * hh)) & 0xfu) == 0xfu) {
+                    *reinterpret_cast<f4 *>(q) = t.v[2 * u + hh];
+                } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if ((mask[u] >> (4 * hh + e)) & 1u) q[e] = t.v[2 * u + hh][e];
+                    for (int e = 0; e < 4; ++e)
+                        if ((mask[u] >> (4 * hh + e)) & 1u) q[e] = t.v[2 * u + hh][e];
+                }
             }
         }
 }

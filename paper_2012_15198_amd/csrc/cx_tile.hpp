@@ -1,7 +1,7 @@
 // Building blocks of the device half (internal header): the 16-byte column slice a lane handles, the tiles
 // of slices a lane keeps in registers (fp32, and fp64 for the operators that compute there), the pairwise
-// average, and the fp32 row accesses -- full tiles as one 16-byte access per slice, boundary tiles element by
-// element under a mask.  The overview of the kernels is at the top of cx_kernels.hpp.
+// average, and the fp32 row accesses -- full tiles as one 16-byte access per slice, boundary tiles
+// under a mask of elements.  The overview of the kernels is at the top of cx_kernels.hpp.
 #ifndef CX_TILE_HPP
 #define CX_TILE_HPP
 #include "cx_mix.h"
@@ -84,6 +84,14 @@ __device__ __forceinline__ void wave_sync()
 // Tile I/O.  `p` points at this lane's first slice of the row (row base + tile start
 // + 4*lane); slice u sits 256 floats further.  FULL: whole 16-byte slices.  Otherwise
 // bit e of mask[u] says whether element e of slice u belongs to this lane right now.
+//
+// A boundary tile loads a slice whole as soon as one of its elements counts, and stores it whole where
+// all do; only the slice that a boundary cuts is stored element by element.  What it loads beside the
+// wanted columns is the row's own memory -- rows are 16-byte aligned and hold ld >= P elements, ld a
+// multiple of the slice -- and goes nowhere, since only the mask's elements are stored.  (Element-wise loads
+// under a mask are a branch and a wait each: 8 columns of a group of 8 were 64 memory latencies in a row,
+// which made the boundary tile the longest part of every small launch: the binary16 gradient step on 42 x 242,981
+// in place, groups of 6: 91 -> 34 us; the binary16 group mean on 64 x 11,689,511 in place: 773 -> 678 us.)
 // ---------------------------------------------------------------------------------
 template <int U, bool FULL, bool NT>
 __device__ __forceinline__ void tile_load(const float *p, const unsigned (&mask)[U], Tile<U> &t)
@@ -94,8 +102,8 @@ __device__ __forceinline__ void tile_load(const float *p, const unsigned (&mask)
             const f4 *q = reinterpret_cast<const f4 *>(p + u * 256);
             t.v[u] = NT ? __builtin_nontemporal_load(q) : *q;
         } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) t.v[u][e] = ((mask[u] >> e) & 1u) ? p[u * 256 + e] : 0.0f;
+            t.v[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (mask[u] != 0) t.v[u] = *reinterpret_cast<const f4 *>(p + u * 256);
         }
     }
 }
@@ -109,9 +117,13 @@ __device__ __forceinline__ void tile_store(float *p, const unsigned (&mask)[U], 
             f4 *q = reinterpret_cast<f4 *>(p + u * 256);
             if (NT) __builtin_nontemporal_store(t.v[u], q); else *q = t.v[u];
         } else {
+            if (mask[u] == 0xfu) {
+                *reinterpret_cast<f4 *>(p + u * 256) = t.v[u];
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if ((mask[u] >> e) & 1u) p[u * 256 + e] = t.v[u][e];
+                for (int e = 0; e < 4; ++e)
+                    if ((mask[u] >> e) & 1u) p[u * 256 + e] = t.v[u][e];
+            }
         }
     }
 }

@@ -65,3 +65,36 @@ def test_rows_of_one_column_to_one_chunk(W):
             b = torch.full((W, ld), float("nan"), device="cuda:0")
             call(a, b, P, dev(so), dev(pe))
             assert same_bits(host(b)[:, :P], O.gossip_mix(x, P, so, pe)[:, :P])
+
+
+@pytest.mark.parametrize("P", [1, 5, 255, 259, 515, 1030])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_boundary_tiles_keep_to_their_columns(P, in_place):
+    """Boundary tiles load whole 16-byte slices: what lies in the padding (NaN here) or in the other segment of a
+    slice reaches no result, and neither does the padding change.  Segments of 1 to 7 columns cut every slice."""
+    W, rng = 5, np.random.default_rng(P)
+    ld = (P + 7) // 8 * 8 + 8
+    so = np.unique(np.concatenate([[0], np.cumsum(rng.integers(1, 8, size=P)), [P]]).clip(0, P)).astype(np.int64)
+    pe = O.topology(P, W, len(so) - 1, 0, 1)[0]
+    x, v, g = (WL.gen_matrix(W, P, s, seed=P, ld=ld, stream=k) for k, s in enumerate((0.05, 0.02, 0.01)))
+    for a in (x, v, g):
+        a[:, P:] = np.nan
+    sod, ped = dev(so), dev(pe)
+    a = dev(x)
+    b = a if in_place else dev(x)
+    cx.cx_gossip_mix(a, b, P, sod, ped)
+    assert same_bits(host(b)[:, :P], O.gossip_mix(x, P, so, pe)[:, :P]) and np.isnan(host(b)[:, P:]).all()
+    a, av = dev(x), dev(v)
+    b, bv = (a, av) if in_place else (dev(x), dev(v))
+    cx.cx_sgd_fused_mix(a, b, av, bv, dev(g), 0.1, 0.9, 1e-4, P, sod, ped)
+    wx, wv = (once(t) for t in O.sgd_fused_mix_f64(x, v, g, 0.1, 0.9, 1e-4, P, so, pe))
+    for got, want in ((b, wx), (bv, wv)):
+        assert same_bits(host(got)[:, :P], want[:, :P]) and np.isnan(host(got)[:, P:]).all()
+    for fmt, narrow in (("bf16", O.f32_to_bf16), ("f16", O.f32_to_f16)):
+        xb, gb = narrow(x), narrow(g)
+        a, av = dev(xb.view(np.int16)), dev(v)
+        b, bv = (a, av) if in_place else (dev(xb.view(np.int16)), dev(v))
+        getattr(cx, f"cx_sgd_fused_mix_{fmt}")(a, b, av, bv, dev(gb.view(np.int16)), 0.1, 0.9, 1e-4, P, sod, ped)
+        wx, wv = O.sgd_fused_mix16(fmt, xb, v, gb, 0.1, 0.9, 1e-4, P, so, pe)
+        assert (host(b).view(np.uint16)[:, :P] == wx[:, :P]).all() and same_bits(host(bv)[:, :P], wv[:, :P])
+        assert (host(b).view(np.uint16)[:, P:] == xb[:, P:]).all() and np.isnan(host(bv)[:, P:]).all()
