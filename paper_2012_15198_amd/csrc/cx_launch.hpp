@@ -107,17 +107,20 @@ bool try_launch(const Op &op, const Launch &l, const MixArgs &a)
         int waves = l.waves;
         while (waves > 1 && (sizeof(int) * kScheduleWords(a.n) + StageBytes<Op>::value) * waves > 48 * 1024) --waves;
         const int64_t nblocks = (ntiles + waves - 1) / waves;
-        const dim3 grid(static_cast<unsigned>(nblocks)), block(kWave * waves);
+        // one wavefront for each inner segment boundary, ahead of the tiles (boundaries that fall on a tile's edge
+        // leave theirs at once)
+        const unsigned pieces = a.S > 1 ? (static_cast<unsigned>(a.S) - 1 + waves - 1) / waves : 0;
+        const dim3 grid(static_cast<unsigned>(nblocks) + pieces), block(kWave * waves);
         const size_t schedules = (sizeof(int) * kScheduleWords(a.n) * waves + 15) / 16 * 16;
         size_t lds = schedules + static_cast<size_t>(StageBytes<Op>::value) * waves;
         if (lds < lds_reservation(l.wgs_per_cu)) lds = lds_reservation(l.wgs_per_cu);
         const Op staged = with_stage_base(op, schedules);
         if (l.nt)
             hipLaunchKernelGGL((mix_kernel<Op, U, D, true>), grid, block, lds, a.stream, staged, a.n, a.P,
-                               a.S, a.seg_off, a.peers, a.shift, a.skip_mix, ntiles, l.lockstep);
+                               a.S, a.seg_off, a.peers, a.shift, a.skip_mix, ntiles, l.lockstep, pieces);
         else
             hipLaunchKernelGGL((mix_kernel<Op, U, D, false>), grid, block, lds, a.stream, staged, a.n, a.P,
-                               a.S, a.seg_off, a.peers, a.shift, a.skip_mix, ntiles, l.lockstep);
+                               a.S, a.seg_off, a.peers, a.shift, a.skip_mix, ntiles, l.lockstep, pieces);
         return true;
     }
 }
