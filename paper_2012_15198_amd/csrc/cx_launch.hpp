@@ -95,6 +95,32 @@ constexpr bool fits()
            Op::kRawPerSlice * U * D * 4 <= 144 && !(U == 4 && Op::kRawPerSlice * D >= 8);
 }
 
+// In-place walk on short rows: a wavefront walks all rows of its tile one after the other, so a launch lasts as
+// long as one walk and the bytes in flight come from narrow tiles (more walks) and a deep ring (more rows of each).
+// Below kShortTiles tiles (8 wavefronts per CU) a lane takes one slice and the deepest ring that stays within
+// kShortRing 16-byte registers; workgroups are halved until there are kShortBlocks of them, one for every second CU
+// (fewer, larger ones lose to idle CUs, more lose the lock-step of the waves: bf16 gradient step on 256 x 300,007 in groups
+// of 8: 117 us with 4 waves, 132 with one).  fp32 optimizer step on 256 x 75,003: 444 -> 123 us with one slice, eight rows;
+// bf16 gossip on 256 x 300,007: 153 -> 108.
+constexpr int64_t kShortTiles = 2048, kShortBlocks = 128;
+constexpr int kShortRing = 32;
+template <class Op>
+WalkShape short_walk(int64_t P, WalkShape shape)
+{
+    const auto tiles = [&] {
+        const int64_t cols = static_cast<int64_t>(kWave) * Op::kElems * shape.U;
+        return (P + cols - 1) / cols;
+    };
+    if (tiles() < kShortTiles) {
+        shape.U = 1;
+        shape.D = fits<Op, 1, 8>() && Op::kRawPerSlice * 8 <= kShortRing   ? 8
+                  : fits<Op, 1, 4>() && Op::kRawPerSlice * 4 <= kShortRing ? 4
+                                                                          : 2;
+    }
+    while (shape.waves > 1 && tiles() <= (kShortBlocks - 1) * shape.waves) shape.waves /= 2;
+    return shape;
+}
+
 template <class Op, int U, int D>
 bool try_launch(const Op &op, const Launch &l, const MixArgs &a)
 {
@@ -328,7 +354,7 @@ int launch_mix(const Op &op, const MixArgs &a)
             try_gather<Op, 4>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status))
             return status;
     }
-    Launch l = pick_launch(Op::kWalk);
+    Launch l = pick_launch(short_walk<Op>(a.P, Op::kWalk));
     const bool done =
         try_launch<Op, 1, 2>(op, l, a) || try_launch<Op, 1, 4>(op, l, a) || try_launch<Op, 1, 8>(op, l, a) ||
         try_launch<Op, 2, 2>(op, l, a) || try_launch<Op, 2, 4>(op, l, a) || try_launch<Op, 2, 8>(op, l, a) ||

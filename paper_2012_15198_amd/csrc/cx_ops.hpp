@@ -24,6 +24,11 @@ struct GatherShape {
 struct WalkShape {
     int U, D, waves, wgs_per_cu;       // slices per lane, rows in flight, waves per workgroup,
 };                                     // resident workgroups per CU (0 = as many as fit)
+// Long rows take kWalk as it stands: eight waves in lock-step and two workgroups per CU keep the rows' streams
+// dense in DRAM.  In place on 64 x 11,689,511, against two waves per workgroup: fp32 mean of groups of 8
+// 1,280 -> 1,199 us, binary16 of groups of 4 641 -> 592, bf16 gradient step of groups of 8 865 -> 810, bf16
+// optimizer step (four waves) 2,239 -> 2,109; fp32 gossip with eight rows of two slices in flight 1,255 -> 1,151.
+// Short rows: see short_walk in cx_launch.hpp.
 
 // Plain gossip (G == 1) and hierarchical mode (a gossiping row = a group of G rows).
 // G == 1 is Algorithm 1's averaging line in fp32, as written.  For G > 1 the group sum (rows in
@@ -43,7 +48,7 @@ struct MeanOp {
         G == 1 ? GatherShape{1, 4, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0} : GatherShape{1, 8, 768, 0};
     static constexpr int kVisitKbFewRows = G >= 8 ? 256 : kGather.visit_kb;      // see VisitKb
     static constexpr WalkShape kWalk =
-        G == 1 ? WalkShape{1, 2, 2, 8} : G == 2 ? WalkShape{2, 4, 2, 2} : G <= 8 ? WalkShape{1, 4, 2, 2} : WalkShape{1, 2, 2, 2};
+        G == 1 ? WalkShape{2, 8, 8, 2} : G == 2 ? WalkShape{2, 4, 8, 2} : G <= 8 ? WalkShape{2, 2, 8, 2} : WalkShape{1, 2, 8, 2};
     template <int U> struct Raw { Tile<U> r[G]; };
     const float *xin;
     float *xout;
@@ -208,7 +213,7 @@ struct FusedOp {
     template <int U> using Work = WideTile<U>;             // the updated row, in fp64
     static constexpr int kRawPerSlice = 3;
     static constexpr GatherShape kGather{1, 8, 128, 3};
-    static constexpr WalkShape kWalk{2, 2, 8, 2};
+    static constexpr WalkShape kWalk{2, 4, 8, 2};
     static constexpr int kMaxU = 2;                        // fp64 rows: two slices per lane fill the registers
     template <int U> struct Raw { Tile<U> x, v, g; };
     const float *xin;
@@ -263,7 +268,7 @@ struct HierFusedOp {
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 8, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0} : GatherShape{1, 8, 768, 0};
     static constexpr int kVisitKbFewRows = G >= 8 ? 256 : kGather.visit_kb;      // see VisitKb
-    static constexpr WalkShape kWalk = G <= 4 ? WalkShape{1, 4, 2, 2} : WalkShape{1, 2, 2, 2};
+    static constexpr WalkShape kWalk = G <= 4 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G <= 2 ? 2 : 1;
     template <int U> struct Raw { Tile<U> g[G], x, v; };
     const float *xin;
@@ -317,7 +322,7 @@ struct PushOp {
     template <int U> using Work = Tile<U>;                 // fp32 values a lane works on
     static constexpr int kRawPerSlice = 1;
     static constexpr GatherShape kGather{2, 4, 512, 0};
-    static constexpr WalkShape kWalk{2, 2, 8, 2};
+    static constexpr WalkShape kWalk{2, 8, 8, 2};
     template <int U> struct Raw { Tile<U> x; };
     const float *xin;
     float *xout;

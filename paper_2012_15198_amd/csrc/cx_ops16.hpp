@@ -118,7 +118,7 @@ struct Row16Op {
     static constexpr int kRawPerSlice = G;
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 8, 96, 0} : G <= 4 ? GatherShape{1, 8, 256, 0} : GatherShape{1, 8, 384, 0};
-    static constexpr WalkShape kWalk = G == 1 ? WalkShape{1, 2, 8, 0} : WalkShape{1, 2, 2, 2};
+    static constexpr WalkShape kWalk = G == 1 ? WalkShape{2, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G == 1 ? 4 : 1;           // grouped: one slice per lane fills the registers
     template <int U> struct Raw { Tile<U> r[G]; };         // packed 16-bit pairs, as loaded
     const uint16_t *xin;
@@ -209,7 +209,7 @@ template <bool IEEE_HALF>
 struct Push16Op : Row16Op<IEEE_HALF, 1> {
     using Base = Row16Op<IEEE_HALF, 1>;
     static constexpr GatherShape kGather{2, 4, 192, 0};    // measured on C4: one slice per lane 52 %, two 76 %
-    static constexpr WalkShape kWalk{1, 2, 8, 0};
+    static constexpr WalkShape kWalk{2, 4, 8, 2};
     uint16_t *zout;       // may be null
     const float *win;
     int n, hop;
@@ -339,7 +339,7 @@ struct Fused16Op {
     template <int U> using Work = WideTile<2 * U>;         // the updated row, 8 doubles per slice
     static constexpr int kRawPerSlice = 4;                 // x, g: one register each; v: two
     static constexpr GatherShape kGather{1, 4, 96, 0};
-    static constexpr WalkShape kWalk{1, 2, 4, 2};
+    static constexpr WalkShape kWalk{1, 2, 8, 2};
     static constexpr int kMaxU = 1;
     static constexpr int kStageBytes = kStageBytesPerWave; // LDS per wavefront (see tile_load8)
     template <int U> struct Raw { Tile<U> x, g; Tile<2 * U> v; };
@@ -396,7 +396,7 @@ struct HierFused16Op {
     static constexpr int kRawPerSlice = G + 3;             // G gradient rows, x, and two registers of v
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 8, 192, 0} : G <= 4 ? GatherShape{1, 8, 256, 0} : GatherShape{1, 8, 384, 0};
-    static constexpr WalkShape kWalk{1, 2, 2, 2};
+    static constexpr WalkShape kWalk{1, 2, 8, 2};
     static constexpr int kMaxU = 1;
     static constexpr int kStageBytes = kStageBytesPerWave;
     template <int U> struct Raw { Tile<U> g[G], x; Tile<2 * U> v; };

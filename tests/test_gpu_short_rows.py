@@ -98,3 +98,33 @@ def test_boundary_tiles_keep_to_their_columns(P, in_place):
         wx, wv = O.sgd_fused_mix16(fmt, xb, v, gb, 0.1, 0.9, 1e-4, P, so, pe)
         assert (host(b).view(np.uint16)[:, :P] == wx[:, :P]).all() and same_bits(host(bv)[:, :P], wv[:, :P])
         assert (host(b).view(np.uint16)[:, P:] == xb[:, P:]).all() and np.isnan(host(bv)[:, P:]).all()
+
+
+# in place: the edges where workgroups are halved (127 * 1, 2, 4, 8 tiles) and where one slice per lane begins (2,047
+# tiles of two), for rings that the steady loop turns never, once and many times (n <= 2 D, n just above, n = 37)
+@pytest.mark.parametrize("W", [3, 5, 17, 37])
+@pytest.mark.parametrize("P", [TILE * 127 + 1, TILE * 254, TILE * 1016 + 3, 2 * TILE * 2047, 2 * TILE * 2047 + 1])
+@pytest.mark.parametrize("kind", ["gossip", "fused", "bf16"])
+def test_in_place_walk_shapes(kind, W, P):
+    ld = (P + 7) // 8 * 8
+    so = np.array([0, P // 3 + 1, P // 3 + 1, P - 2, P], dtype=np.int64)
+    pe = O.topology(P, W, len(so) - 1, 0, 1)[0]
+    x = WL.gen_matrix(W, P, 0.05, seed=P, ld=ld)
+    print(kind, W, P, flush=True)
+    if kind == "bf16":
+        xb = O.f32_to_bf16(x)
+        a = dev(xb.view(np.int16))
+        cx.cx_gossip_mix_bf16(a, a, P, dev(so), dev(pe))
+        assert (host(a).view(np.uint16)[:, :P] == O.gossip_mix_bf16(xb, P, so, pe)[:, :P]).all()
+        return
+    a = dev(x)
+    if kind == "gossip":
+        cx.cx_gossip_mix(a, a, P, dev(so), dev(pe))
+        want = O.gossip_mix(x, P, so, pe)
+    else:
+        v, g = (WL.gen_matrix(W, P, s, seed=P, ld=ld, stream=k) for s, k in ((0.02, 1), (0.01, 2)))
+        vd = dev(v)
+        cx.cx_sgd_fused_mix(a, a, vd, vd, dev(g), 0.1, 0.9, 1e-4, P, dev(so), dev(pe))
+        want, wv = (once(t) for t in O.sgd_fused_mix_f64(x, v, g, 0.1, 0.9, 1e-4, P, so, pe))
+        assert same_bits(host(vd)[:, :P], wv[:, :P])
+    assert same_bits(host(a)[:, :P], want[:, :P])
