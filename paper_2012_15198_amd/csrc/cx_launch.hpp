@@ -97,7 +97,7 @@ constexpr bool fits()
 
 // In-place walk on short rows: a wavefront walks all rows of its tile one after the other, so a launch lasts as
 // long as one walk and the bytes in flight come from narrow tiles (more walks) and a deep ring (more rows of each).
-// Below kShortTiles tiles (8 wavefronts per CU) a lane takes one slice and the deepest ring that stays within
+// Below kShortTiles tiles (8 wavefronts per CU; three times as many where a lane would take two slices) a lane takes one slice and the deepest ring that stays within
 // kShortRing 16-byte registers; workgroups are halved until there are kShortBlocks of them, one for every second CU
 // (fewer, larger ones lose to idle CUs, more lose the lock-step of the waves: bf16 gradient step on 256 x 300,007 in groups
 // of 8: 117 us with 4 waves, 132 with one).  fp32 optimizer step on 256 x 75,003: 444 -> 123 us with one slice, eight rows;
@@ -111,7 +111,7 @@ WalkShape short_walk(int64_t P, WalkShape shape)
         const int64_t cols = static_cast<int64_t>(kWave) * Op::kElems * shape.U;
         return (P + cols - 1) / cols;
     };
-    if (tiles() < kShortTiles) {
+    if (tiles() < (shape.U > 1 ? 3 : 1) * kShortTiles) {
         shape.U = 1;
         shape.D = fits<Op, 1, 8>() && Op::kRawPerSlice * 8 <= kShortRing   ? 8
                   : fits<Op, 1, 4>() && Op::kRawPerSlice * 4 <= kShortRing ? 4
