@@ -38,11 +38,12 @@
 //     lock-step variant) in LDS from the peer table; a table that is not a permutation is
 //     replaced by the identity, so no row index can leave [0, n).
 //
-//  Both: tiles wholly inside one segment take the 16-byte vector path; the at most S+1
-//  tiles that straddle a segment boundary or the ragged row end run once per overlapped
-//  segment with per-element predication.  Row operators (MeanOp / FusedOp / HierFusedOp /
-//  PushOp / Row16Op ...) say what loading and storing a "gossiping row" means: the mean of a
-//  group of G rows summed in fp64, the momentum-SGD update applied on the way in (to the row or
+//  Both: tiles wholly inside one segment take the 16-byte vector path.  In the at most S+1 tiles that a
+//  segment boundary or the ragged row end crosses, every piece between two boundaries loads the slices it
+//  meets and stores under a mask of elements: piece after piece by the tile's wavefront in gather_kernel, one
+//  wavefront for each piece in mix_kernel.  Columns [P, ld) are neither read nor written.  Row operators
+//  (MeanOp / FusedOp / HierFusedOp / PushOp / Row16Op ...) say what loading and storing a "gossiping row" means:
+//  the mean of a group of G rows summed in fp64, the momentum-SGD update applied on the way in (to the row or
 //  to a group leader fed with the group's mean gradient), the push-sum de-biasing, or the
 //  unpacking and rounding of 16-bit rows (bfloat16, binary16).  Each operator also names its
 //  measured launch shapes (kGather, kWalk).
@@ -77,7 +78,7 @@ struct BlockSync {
 // but one was in flight: gossip on 256 x 8,303 fp32, in place, 8 segments: 230 -> 86 us together with the boundary
 // pieces below; fused step 256 x 300,007: 806 -> 573 us.)  The schedule's words are read from LDS one step ahead and kept until their row arrives.
 // The last turns, up to 2 * D steps, decide step by step.
-template <class Op, int U, int D, bool FULL, bool NT, bool SYNC = false>
+template <class Op, int U, int D, TileMode MODE, bool NT, bool SYNC = false>
 __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool skip_mix,
                                      int64_t off, const unsigned (&mask)[U])
 {
@@ -90,7 +91,7 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
         WorkT out;
 #pragma unroll
         for (int u = 0; u < WorkT::kN; ++u) out.v[u] = average(cur.v[u], last ? first.v[u] : nx.v[u]);
-        op.template store<U, FULL, NT>(e & kRowMask, off, mask, out);
+        op.template store<U, MODE, NT>(e & kRowMask, off, mask, out);
         if (last) first = nx;
         cur = nx;
         e = e1;
@@ -100,13 +101,13 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
 #pragma unroll
         for (int j = 0; j < D; ++j) {
             word[j] = uniform(sched[j]);
-            op.template issue<U, FULL, NT>(word[j] & kRowMask, off, mask, slot[j]);
+            op.template issue<U, MODE, NT>(word[j] & kRowMask, off, mask, slot[j]);
         }
         int ahead = sched[D];
         e = word[0];
-        op.template finish<U, FULL, NT>(e & kRowMask, off, mask, slot[0], cur);
+        op.template finish<U, MODE, NT>(e & kRowMask, off, mask, slot[0], cur);
         word[0] = uniform(ahead);
-        op.template issue<U, FULL, NT>(word[0] & kRowMask, off, mask, slot[0]);
+        op.template issue<U, MODE, NT>(word[0] & kRowMask, off, mask, slot[0]);
         ahead = sched[D + 1];
         first = cur;
         for (; base + 2 * D < n; base += D) {
@@ -117,9 +118,9 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
                 if constexpr (SYNC) __builtin_amdgcn_s_barrier();   // the workgroup visits each row together
                 WorkT nx;
                 const int e1 = word[kNextSlot];           // row of step k+1 arrives; its slot is refilled at once
-                op.template finish<U, FULL, NT>(e1 & kRowMask, off, mask, slot[kNextSlot], nx);
+                op.template finish<U, MODE, NT>(e1 & kRowMask, off, mask, slot[kNextSlot], nx);
                 word[kNextSlot] = uniform(ahead);
-                op.template issue<U, FULL, NT>(word[kNextSlot] & kRowMask, off, mask, slot[kNextSlot]);
+                op.template issue<U, MODE, NT>(word[kNextSlot] & kRowMask, off, mask, slot[kNextSlot]);
                 ahead = sched[k + 2 + D < n ? k + 2 + D : n - 1];
                 step(nx, e1);
             });
@@ -127,12 +128,12 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
     } else {
 #pragma unroll
         for (int j = 0; j < D; ++j)
-            if (j < n) op.template issue<U, FULL, NT>(uniform(sched[j]) & kRowMask, off, mask, slot[j]);
+            if (j < n) op.template issue<U, MODE, NT>(uniform(sched[j]) & kRowMask, off, mask, slot[j]);
         e = uniform(sched[0]);
-        op.template finish<U, FULL, NT>(e & kRowMask, off, mask, slot[0], cur);
-        if (D < n) op.template issue<U, FULL, NT>(uniform(sched[D]) & kRowMask, off, mask, slot[0]);
+        op.template finish<U, MODE, NT>(e & kRowMask, off, mask, slot[0], cur);
+        if (D < n) op.template issue<U, MODE, NT>(uniform(sched[D]) & kRowMask, off, mask, slot[0]);
         if (skip_mix) {                   // a single gossiping row: nothing to average with
-            op.template store<U, FULL, NT>(e & kRowMask, off, mask, cur);
+            op.template store<U, MODE, NT>(e & kRowMask, off, mask, cur);
             return;
         }
         first = cur;
@@ -148,9 +149,9 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
                 int e1 = 0;
                 if (k + 1 < n) {
                     e1 = uniform(sched[k + 1]);
-                    op.template finish<U, FULL, NT>(e1 & kRowMask, off, mask, slot[kNextSlot], nx);
+                    op.template finish<U, MODE, NT>(e1 & kRowMask, off, mask, slot[kNextSlot], nx);
                     if (k + 1 + D < n)
-                        op.template issue<U, FULL, NT>(uniform(sched[k + 1 + D]) & kRowMask, off, mask,
+                        op.template issue<U, MODE, NT>(uniform(sched[k + 1 + D]) & kRowMask, off, mask,
                                                        slot[kNextSlot]);
                 }
                 step(nx, e1);
@@ -159,7 +160,8 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
     }
 }
 
-template <class Op, int U, int D, bool NT>
+// SHORT: rows shorter than one slice.
+template <class Op, int U, int D, bool NT, bool SHORT = false>
 __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
     Op op, int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
     const int32_t *__restrict__ peers, int shift, int skip_mix, int64_t ntiles, int lockstep, unsigned piece_blocks)
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
     constexpr int kSliceCols = Op::kElems;            // columns in one 16-byte slice
     constexpr int kTileCols = kWave * kSliceCols * U;
 
-    if (lockstep && !is_piece) {
+    if (!SHORT && lockstep && !is_piece) {
         // Workgroup-uniform fast path: the whole super-tile of the workgroup lies inside one
         // segment, so its waves share one schedule and walk the rows in lock-step.
         const int64_t g0 = block * nwaves * kTileCols;
@@ -197,7 +199,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
             unsigned mask[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) mask[u] = (1u << kSliceCols) - 1u;
-            walk<Op, U, D, true, NT, true>(op, sched, n, skip_mix != 0, column_of<Op>(g0 + static_cast<int64_t>(wave) * kTileCols, lane, 0, 0), mask);
+            walk<Op, U, D, kFull, NT, true>(op, sched, n, skip_mix != 0, column_of<Op>(g0 + static_cast<int64_t>(wave) * kTileCols, lane, 0, 0), mask);
             return;
         }
     }
@@ -233,24 +235,19 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
     int64_t e = bound(s + 1);
     if (e > c0 + kTileCols) e = c0 + kTileCols;
     if (b >= e) return;
-    const int64_t off = column_of<Op>(c0, lane, 0, 0);     // this lane's first column
+    const int64_t place = column_of<Op>(c0, lane, 0, 0);
+    const int64_t off = place - (SHORT ? 0 : row_end_slide(P, c0, place, U, kTileCols, kSliceCols));   // this lane's first column
     build_schedule(work, n, lane, kWave, peers, s, shift, WaveSync{});
     unsigned mask[U];
     if (e - b == kTileCols) {
 #pragma unroll
         for (int u = 0; u < U; ++u) mask[u] = (1u << kSliceCols) - 1u;
-        walk<Op, U, D, true, NT>(op, sched, n, skip_mix != 0, off, mask);
+        walk<Op, U, D, kFull, NT>(op, sched, n, skip_mix != 0, off, mask);
     } else {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            mask[u] = 0;
-#pragma unroll
-            for (int q = 0; q < kSliceCols; ++q) {
-                const int64_t c = column_of<Op>(c0, lane, u, q);
-                if (c >= b && c < e) mask[u] |= 1u << q;
-            }
-        }
-        walk<Op, U, D, false, NT>(op, sched, n, skip_mix != 0, off, mask);
+        for (int u = 0; u < U; ++u)
+            mask[u] = slice_mask(off + u * (kWave * kSliceCols), kSliceCols, wanted_from(b, place, U), e);
+        walk<Op, U, D, SHORT ? kShortRow : kBoundary, NT>(op, sched, n, skip_mix != 0, off, mask);
     }
 }
 
@@ -339,7 +336,8 @@ __global__ __launch_bounds__(256) void order_kernel(int n, int64_t P, int S,
 // Needs x_out != x_in (and v_out != v_in): a partner's input may be read after its owner
 // has stored.  Any table with entries in [0, n) is served, permutation or not.
 // ---------------------------------------------------------------------------------
-template <class Op, int U, bool NT>
+// SHORT: rows shorter than one slice.
+template <class Op, int U, bool NT, bool SHORT = false>
 __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     Op op, int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
     const int32_t *__restrict__ peers, int shift, int skip_mix, unsigned nchunks, unsigned CL,
@@ -372,31 +370,31 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     // own rows before the partner's are requested, which halves the registers in flight.
     int row = blockIdx.y;
     typename Op::template Raw<U> mine;
-    auto mix_and_store = [&](auto full_c, const unsigned (&m)[U], int peer) {
-        constexpr bool FULL = decltype(full_c)::value;
+    auto mix_and_store = [&](auto mode_c, int64_t at, const unsigned (&m)[U], int peer) {
+        constexpr TileMode MODE = decltype(mode_c)::value;
         using WorkT = typename Op::template Work<U>;
         constexpr bool kOneAtATime = Op::kRawPerSlice * WorkT::kN >= 16 ||            // 16-byte registers per phase
                                      (WorkT::kRegs == 8 && Op::kRawPerSlice * U >= 6);  // fp64 chains take more
         typename Op::template Work<U> a, out;
         if (skip_mix) {
-            op.template finish<U, FULL, NT, true>(row, off, m, mine, a);
+            op.template finish<U, MODE, NT, true>(row, at, m, mine, a);
             out = a;
         } else {
             typename Op::template Work<U> c;
             if constexpr (kOneAtATime) {
-                op.template finish<U, FULL, NT, true>(row, off, m, mine, a);
-                op.template issue<U, FULL, false>(peer, off, m, mine);
-                op.template finish<U, FULL, NT, false>(peer, off, m, mine, c);
+                op.template finish<U, MODE, NT, true>(row, at, m, mine, a);
+                op.template issue<U, MODE, false>(peer, at, m, mine);
+                op.template finish<U, MODE, NT, false>(peer, at, m, mine, c);
             } else {
                 typename Op::template Raw<U> theirs;
-                op.template issue<U, FULL, false>(peer, off, m, theirs);
-                op.template finish<U, FULL, NT, true>(row, off, m, mine, a);
-                op.template finish<U, FULL, NT, false>(peer, off, m, theirs, c);
+                op.template issue<U, MODE, false>(peer, at, m, theirs);
+                op.template finish<U, MODE, NT, true>(row, at, m, mine, a);
+                op.template finish<U, MODE, NT, false>(peer, at, m, theirs, c);
             }
 #pragma unroll
             for (int u = 0; u < Op::template Work<U>::kN; ++u) out.v[u] = average(a.v[u], c.v[u]);
         }
-        op.template store<U, FULL, NT>(row, off, m, out);
+        op.template store<U, MODE, NT>(row, at, m, out);
     };
 
     // y is the position in the cluster's row order: with the order kernel's table, rows follow
@@ -405,7 +403,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     // segment covers the cluster, so a tile that does not hang over the row end starts all its
     // loads after a single scalar load.  Whatever the table holds, no access leaves the
     // matrix: rows are checked against n and the tile against P.
-    if (order) {
+    if (!SHORT && order) {
         const unsigned e = order[cluster * static_cast<unsigned>(n) + blockIdx.y];
         const int r = static_cast<int>(e & kOrderRowField);
         const int q = static_cast<int>((e >> kOrderRowBits) & kOrderRowField);
@@ -423,8 +421,8 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
             }
         }
         if ((e & kOrderOneSegment) != 0 && r < n && q < n && c0 + kTileCols <= P) {
-            op.template issue<U, true, false>(row, off, full_mask, mine);
-            mix_and_store(std::true_type{}, full_mask, q);
+            op.template issue<U, kFull, false>(row, off, full_mask, mine);
+            mix_and_store(std::integral_constant<TileMode, kFull>{}, off, full_mask, q);
             return;
         }
     }
@@ -437,7 +435,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     // The row's own data does not depend on the segment: a tile that does not hang over the
     // row end puts its loads in flight before the lookup.
     const bool whole = c0 + kTileCols <= P;
-    if (whole) op.template issue<U, true, false>(row, off, full_mask, mine);
+    if (whole) op.template issue<U, kFull, false>(row, off, full_mask, mine);
     const bool in_lanes = S <= 63;
     int64_t lane_off = 0;
     int lane_peer = row;
@@ -461,6 +459,8 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
         const unsigned hi32 = __builtin_amdgcn_readlane(static_cast<int>(lane_off >> 32), k);
         return static_cast<int64_t>((static_cast<uint64_t>(hi32) << 32) | lo32);
     };
+    constexpr TileMode kCut = SHORT ? kShortRow : kBoundary;
+    const int64_t at = off - (SHORT ? 0 : row_end_slide(P, c0, off, U, kTileCols, kSliceCols));
     for (int s = first_seg; s < S; ++s) {
         int64_t sb = (s == 0) ? 0 : offset_at(s);
         int64_t se = (s == S - 1) ? P : offset_at(s + 1);
@@ -472,22 +472,16 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
         if (sb >= se) continue;
         const int peer = in_lanes ? __builtin_amdgcn_readlane(lane_peer, s) : partner_of(peers, shift, n, s, row);
         if (whole && sb == c0 && se == c0 + kTileCols) {  // one segment covers the whole tile
-            mix_and_store(std::true_type{}, full_mask, peer);
+            mix_and_store(std::integral_constant<TileMode, kFull>{}, off, full_mask, peer);
             return;
         }
         // boundary tile: per-element predication, once per overlapped segment
         unsigned mask[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            mask[u] = 0;
-#pragma unroll
-            for (int q = 0; q < kSliceCols; ++q) {
-                const int64_t c = column_of<Op>(c0, lane, u, q);
-                if (c >= sb && c < se) mask[u] |= 1u << q;
-            }
-        }
-        op.template issue<U, false, false>(row, off, mask, mine);
-        mix_and_store(std::false_type{}, mask, peer);
+        for (int u = 0; u < U; ++u)
+            mask[u] = slice_mask(at + u * (kWave * kSliceCols), kSliceCols, wanted_from(sb, off, U), se);
+        op.template issue<U, kCut, false>(row, at, mask, mine);
+        mix_and_store(std::integral_constant<TileMode, kCut>{}, at, mask, peer);
     }
 }
 

@@ -141,12 +141,14 @@ bool try_launch(const Op &op, const Launch &l, const MixArgs &a)
         size_t lds = schedules + static_cast<size_t>(StageBytes<Op>::value) * waves;
         if (lds < lds_reservation(l.wgs_per_cu)) lds = lds_reservation(l.wgs_per_cu);
         const Op staged = with_stage_base(op, schedules);
-        if (l.nt)
-            hipLaunchKernelGGL((mix_kernel<Op, U, D, true>), grid, block, lds, a.stream, staged, a.n, a.P,
-                               a.S, a.seg_off, a.peers, a.shift, a.skip_mix, ntiles, l.lockstep, pieces);
-        else
-            hipLaunchKernelGGL((mix_kernel<Op, U, D, false>), grid, block, lds, a.stream, staged, a.n, a.P,
-                               a.S, a.seg_off, a.peers, a.shift, a.skip_mix, ntiles, l.lockstep, pieces);
+        const auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, lds, a.stream, staged, a.n, a.P, a.S, a.seg_off, a.peers, a.shift,
+                               a.skip_mix, ntiles, l.lockstep, pieces);
+        };
+        if constexpr (U == 1 && D == 2)
+            if (a.P < Op::kElems) { launch(mix_kernel<Op, U, D, false, true>); return true; }
+        if (l.nt) launch(mix_kernel<Op, U, D, true>);
+        else launch(mix_kernel<Op, U, D, false>);
         return true;
     }
 }
@@ -318,14 +320,15 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     if (LdsStaged<Op>::value && glds < LdsStaged<Op>::bytes) glds = LdsStaged<Op>::bytes;
     if (glds < static_cast<size_t>(StageBytes<Op>::value) * waves) glds = static_cast<size_t>(StageBytes<Op>::value) * waves;
     const Op staged = with_stage_base(op, 0);
-    if (nt)
-        hipLaunchKernelGGL((gather_kernel<Op, U, true>), grid, block, glds, a.stream, staged, a.n, a.P, a.S,
-                           a.seg_off, a.peers, a.shift, a.skip_mix, static_cast<unsigned>(nchunks),
-                           static_cast<unsigned>(cl), static_cast<unsigned>(waves), xcd_shift, order);
-    else
-        hipLaunchKernelGGL((gather_kernel<Op, U, false>), grid, block, glds, a.stream, staged, a.n, a.P, a.S,
-                           a.seg_off, a.peers, a.shift, a.skip_mix, static_cast<unsigned>(nchunks),
-                           static_cast<unsigned>(cl), static_cast<unsigned>(waves), xcd_shift, order);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, glds, a.stream, staged, a.n, a.P, a.S, a.seg_off, a.peers, a.shift,
+                           a.skip_mix, static_cast<unsigned>(nchunks), static_cast<unsigned>(cl),
+                           static_cast<unsigned>(waves), xcd_shift, order);
+    };
+    if (a.P < Op::kElems) {
+        if constexpr (U == 1) launch(gather_kernel<Op, U, false, true>);
+    } else if (nt) launch(gather_kernel<Op, U, true>);
+    else launch(gather_kernel<Op, U, false>);
     *status = hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
     return true;
     }
@@ -336,12 +339,16 @@ int launch_mix(const Op &op, const MixArgs &a)
 {
     constexpr int U0 = Op::kWalk.U, D0 = Op::kWalk.D;
     static_assert(fits<Op, U0, D0>(), "default launch shape must fit");
+    static_assert(fits<Op, 1, 2>(), "the shape of rows shorter than a tile must fit");
     if ((a.P + 255) / 256 > 0x7fffffffLL) return CX_ERR_SHAPE;
+    constexpr int64_t kSliceLanes = static_cast<int64_t>(kWave) * Op::kElems;   // a tile of one slice per lane
+    // Rows shorter than a tile take one slice per lane, rows shorter than a slice the short-row kernels (in
+    // place: shape 1/2): the tile at the row end has nothing to slide over otherwise (cx_columns.hpp).
     if (a.out_of_place && cx_get_tuning(5) != 1) {
         int u = cx_get_tuning(0);
         if (u != 1 && u != 2 && u != 4) u = Op::kGather.U;
         while (u > 1 && Op::kRawPerSlice * u > 8) u >>= 1;   // the rows in flight must fit the registers
-        if (Op::kRawPerSlice >= 8 || u > MaxSlices<Op>::value) u = 1;
+        if (Op::kRawPerSlice >= 8 || u > MaxSlices<Op>::value || a.P < kSliceLanes * u) u = 1;
         int waves = cx_get_tuning(1);
         const bool waves_fixed = waves >= 1 && waves <= kMaxWavesPerBlock;
         if (!waves_fixed) waves = Op::kGather.waves;
@@ -355,14 +362,17 @@ int launch_mix(const Op &op, const MixArgs &a)
             return status;
     }
     Launch l = pick_launch(short_walk<Op>(a.P, Op::kWalk));
+    if (a.P < kSliceLanes * l.U) l.U = 1;
+    if (a.P < Op::kElems) l.D = 2;
     const bool done =
         try_launch<Op, 1, 2>(op, l, a) || try_launch<Op, 1, 4>(op, l, a) || try_launch<Op, 1, 8>(op, l, a) ||
         try_launch<Op, 2, 2>(op, l, a) || try_launch<Op, 2, 4>(op, l, a) || try_launch<Op, 2, 8>(op, l, a) ||
         try_launch<Op, 4, 2>(op, l, a) || try_launch<Op, 4, 4>(op, l, a) || try_launch<Op, 4, 8>(op, l, a);
     if (!done) {                     // requested shape not built for this operator
-        l.U = U0;
-        l.D = D0;
-        try_launch<Op, U0, D0>(op, l, a);
+        const bool narrow = a.P < kSliceLanes * U0;
+        l.U = narrow ? 1 : U0;
+        l.D = narrow ? 2 : D0;
+        if (!try_launch<Op, U0, D0>(op, l, a)) try_launch<Op, 1, 2>(op, l, a);
     }
     return hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
 }

@@ -54,14 +54,14 @@ struct MeanOp {
     float *xout;
     int64_t ld;
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
     {
         const float *p = xin + static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_load<U, FULL, NT>(p + j * ld, mask, raw.r[j]);
+        for (int j = 0; j < G; ++j) tile_load<U, MODE, NT>(p + j * ld, mask, raw.r[j]);
     }
-    template <int U, bool FULL, bool NT, bool COMMIT = true>
+    template <int U, TileMode MODE, bool NT, bool COMMIT = true>
     __device__ __forceinline__ void finish(int row, int64_t off, const unsigned (&mask)[U], const Raw<U> &raw, Work<U> &t) const
     {
         if constexpr (G == 1) {
@@ -76,7 +76,7 @@ struct MeanOp {
             }
         }
     }
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Work<U> &t) const
     {
         Tile<U> out;
@@ -88,7 +88,7 @@ struct MeanOp {
         }
         float *p = xout + static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_store<U, FULL, NT>(p + j * ld, mask, out);
+        for (int j = 0; j < G; ++j) tile_store<U, MODE, NT>(p + j * ld, mask, out);
     }
 };
 
@@ -224,16 +224,16 @@ struct FusedOp {
     int64_t ld;
     SgdStep sgd;
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
     {
         const int64_t o = static_cast<int64_t>(row) * ld + off;
-        tile_load<U, FULL, NT>(xin + o, mask, raw.x);
-        tile_load<U, FULL, NT>(vin + o, mask, raw.v);
-        tile_load<U, FULL, NT>(g + o, mask, raw.g);
+        tile_load<U, MODE, NT>(xin + o, mask, raw.x);
+        tile_load<U, MODE, NT>(vin + o, mask, raw.v);
+        tile_load<U, MODE, NT>(g + o, mask, raw.g);
     }
     // COMMIT: also write v' of this row (false when the row is only recomputed as a partner)
-    template <int U, bool FULL, bool NT, bool COMMIT = true>
+    template <int U, TileMode MODE, bool NT, bool COMMIT = true>
     __device__ __forceinline__ void finish(int row, int64_t off, const unsigned (&mask)[U], const Raw<U> &raw, Work<U> &t) const
     {
         Tile<U> v32;
@@ -243,15 +243,15 @@ struct FusedOp {
             t.v[u] = sgd.apply(widen(raw.x.v[u]), v, widen(raw.g.v[u]));
             v32.v[u] = narrow(v);
         }
-        if constexpr (COMMIT) tile_store<U, FULL, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
+        if constexpr (COMMIT) tile_store<U, MODE, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
     }
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Work<U> &t) const
     {
         Tile<U> out;
 #pragma unroll
         for (int u = 0; u < U; ++u) out.v[u] = narrow(t.v[u]);
-        tile_store<U, FULL, NT>(xout + static_cast<int64_t>(row) * ld + off, mask, out);
+        tile_store<U, MODE, NT>(xout + static_cast<int64_t>(row) * ld + off, mask, out);
     }
 };
 
@@ -279,16 +279,16 @@ struct HierFusedOp {
     int64_t ld;
     SgdStep sgd;
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
     {
         const int64_t lead = static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_load<U, FULL, NT>(g + lead + j * ld, mask, raw.g[j]);
-        tile_load<U, FULL, NT>(xin + lead, mask, raw.x);
-        tile_load<U, FULL, NT>(vin + static_cast<int64_t>(row) * ld + off, mask, raw.v);
+        for (int j = 0; j < G; ++j) tile_load<U, MODE, NT>(g + lead + j * ld, mask, raw.g[j]);
+        tile_load<U, MODE, NT>(xin + lead, mask, raw.x);
+        tile_load<U, MODE, NT>(vin + static_cast<int64_t>(row) * ld + off, mask, raw.v);
     }
-    template <int U, bool FULL, bool NT, bool COMMIT = true>
+    template <int U, TileMode MODE, bool NT, bool COMMIT = true>
     __device__ __forceinline__ void finish(int row, int64_t off, const unsigned (&mask)[U], const Raw<U> &raw, Work<U> &t) const
     {
         Tile<U> v32;
@@ -302,9 +302,9 @@ struct HierFusedOp {
             t.v[u] = sgd.apply(widen(raw.x.v[u]), v, gbar);
             v32.v[u] = narrow(v);
         }
-        if constexpr (COMMIT) tile_store<U, FULL, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
+        if constexpr (COMMIT) tile_store<U, MODE, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
     }
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Work<U> &t) const
     {
         Tile<U> out;
@@ -312,7 +312,7 @@ struct HierFusedOp {
         for (int u = 0; u < U; ++u) out.v[u] = narrow(t.v[u]);
         float *p = xout + static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_store<U, FULL, NT>(p + j * ld, mask, out);
+        for (int j = 0; j < G; ++j) tile_store<U, MODE, NT>(p + j * ld, mask, out);
     }
 };
 
@@ -331,28 +331,28 @@ struct PushOp {
     int64_t ld;
     int n, hop;
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
     {
-        tile_load<U, FULL, NT>(xin + static_cast<int64_t>(row) * ld + off, mask, raw.x);
+        tile_load<U, MODE, NT>(xin + static_cast<int64_t>(row) * ld + off, mask, raw.x);
     }
-    template <int U, bool FULL, bool NT, bool COMMIT = true>
+    template <int U, TileMode MODE, bool NT, bool COMMIT = true>
     __device__ __forceinline__ void finish(int row, int64_t off, const unsigned (&mask)[U], const Raw<U> &raw, Tile<U> &t) const
     {
         t = raw.x;
     }
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Tile<U> &t) const
     {
         const int64_t o = static_cast<int64_t>(row) * ld + off;
-        tile_store<U, FULL, NT>(xout + o, mask, t);
+        tile_store<U, MODE, NT>(xout + o, mask, t);
         if (zout) {
             const int from = row >= hop ? row - hop : row - hop + n;
             const float wn = (win[row] + win[from]) * 0.5f;
             Tile<U> z;
 #pragma unroll
             for (int u = 0; u < U; ++u) z.v[u] = t.v[u] / wn;
-            tile_store<U, FULL, NT>(zout + o, mask, z);
+            tile_store<U, MODE, NT>(zout + o, mask, z);
         }
     }
 };

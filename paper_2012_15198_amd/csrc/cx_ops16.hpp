@@ -19,34 +19,42 @@ __device__ __forceinline__ float f16_bits_to_float(unsigned h)
     return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h)));   // exact, subnormals kept
 }
 
-template <int U, bool FULL, bool NT>
+template <int U, TileMode MODE, bool NT>
 __device__ __forceinline__ void tile_load16(const uint16_t *p, const unsigned (&mask)[U], Tile<U> &raw)
 {
     typedef unsigned u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if constexpr (FULL) {
+        if constexpr (MODE == kFull) {
             const f4 *q = reinterpret_cast<const f4 *>(p + u * (kWave * 8));
             raw.v[u] = NT ? __builtin_nontemporal_load(q) : *q;
         } else {
-            raw.v[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};             // boundary tiles: as in tile_load
-            if (mask[u] != 0) raw.v[u] = *reinterpret_cast<const f4 *>(p + u * (kWave * 8));
+            raw.v[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (MODE == kBoundary) {                 // as in tile_load
+                if (mask[u] != 0) raw.v[u] = *reinterpret_cast<const f4_at2 *>(p + u * (kWave * 8));
+            } else {
+                u4 w = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if ((mask[u] >> e) & 1u) w[e >> 1] |= static_cast<unsigned>(p[u * (kWave * 8) + e]) << (16 * (e & 1));
+                raw.v[u] = __builtin_bit_cast(f4, w);
+            }
         }
     }
 }
 
-template <int U, bool FULL, bool NT>
+template <int U, TileMode MODE, bool NT>
 __device__ __forceinline__ void tile_store16(uint16_t *p, const unsigned (&mask)[U], const Tile<U> &raw)
 {
     typedef unsigned u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if constexpr (FULL) {
+        if constexpr (MODE == kFull) {
             f4 *q = reinterpret_cast<f4 *>(p + u * (kWave * 8));
             if (NT) __builtin_nontemporal_store(raw.v[u], q); else *q = raw.v[u];
         } else {
             if (mask[u] == 0xffu) {
-                *reinterpret_cast<f4 *>(p + u * (kWave * 8)) = raw.v[u];
+                *reinterpret_cast<f4_at2 *>(p + u * (kWave * 8)) = raw.v[u];
             } else {
                 const u4 w = __builtin_bit_cast(u4, raw.v[u]);
 #pragma unroll
@@ -125,12 +133,12 @@ struct Row16Op {
     uint16_t *xout;
     int64_t ld;
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
     {
         const uint16_t *p = xin + static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_load16<U, FULL, NT>(p + j * ld, mask, raw.r[j]);
+        for (int j = 0; j < G; ++j) tile_load16<U, MODE, NT>(p + j * ld, mask, raw.r[j]);
     }
     template <int U>
     static __device__ __forceinline__ void widen(const Tile<U> &packed, Tile<2 * U> &t)
@@ -146,7 +154,7 @@ struct Row16Op {
             }
         }
     }
-    template <int U, bool FULL, bool NT, bool COMMIT = true>
+    template <int U, TileMode MODE, bool NT, bool COMMIT = true>
     __device__ __forceinline__ void finish(int row, int64_t off, const unsigned (&mask)[U], const Raw<U> &raw, Work<U> &t) const
     {
         if constexpr (G == 1) {
@@ -183,7 +191,7 @@ struct Row16Op {
             packed.v[u] = __builtin_bit_cast(f4, w);
         }
     }
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Work<U> &t) const
     {
         Tile<U> packed;
@@ -195,7 +203,7 @@ struct Row16Op {
         }
         uint16_t *p = xout + static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_store16<U, FULL, NT>(p + j * ld, mask, packed);
+        for (int j = 0; j < G; ++j) tile_store16<U, MODE, NT>(p + j * ld, mask, packed);
     }
 };
 
@@ -214,10 +222,10 @@ struct Push16Op : Row16Op<IEEE_HALF, 1> {
     const float *win;
     int n, hop;
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Tile<2 * U> &t) const
     {
-        Base::template store<U, FULL, NT>(row, off, mask, t);
+        Base::template store<U, MODE, NT>(row, off, mask, t);
         if (zout) {
             const int from = row >= hop ? row - hop : row - hop + n;
             const float wn = (win[row] + win[from]) * 0.5f;
@@ -226,7 +234,7 @@ struct Push16Op : Row16Op<IEEE_HALF, 1> {
             for (int u = 0; u < 2 * U; ++u) z.v[u] = t.v[u] / wn;
             Tile<U> packed;
             Base::template pack<U>(z, packed);
-            tile_store16<U, FULL, NT>(zout + static_cast<int64_t>(row) * this->ld + off, mask, packed);
+            tile_store16<U, MODE, NT>(zout + static_cast<int64_t>(row) * this->ld + off, mask, packed);
         }
     }
 };
@@ -247,7 +255,7 @@ struct Push16Op : Row16Op<IEEE_HALF, 1> {
 // 256*hh + 4*l .. +3: each access of the wavefront one contiguous KB) and change to the lane's own
 // columns through 2 KB of LDS per wavefront (stage_to_own / stage_from_own).  Boundary tiles
 // address the lane's own columns directly.
-template <int U, bool FULL, bool NT>
+template <int U, TileMode MODE, bool NT>
 __device__ __forceinline__ void tile_load8(const float *p, const unsigned (&mask)[U], Tile<2 * U> &t)
 {
     // p = row base + this lane's first column (tile start + 8 * lane)
@@ -256,18 +264,24 @@ __device__ __forceinline__ void tile_load8(const float *p, const unsigned (&mask
     for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-            if constexpr (FULL) {
+            if constexpr (MODE == kFull) {
                 const f4 *q4 = reinterpret_cast<const f4 *>(p - 4 * lane + u * (kWave * 8) + 256 * hh);   // memory order
                 t.v[2 * u + hh] = NT ? __builtin_nontemporal_load(q4) : *q4;
             } else {
                 const float *q = p + u * (kWave * 8) + 4 * hh;                                           // own columns
                 t.v[2 * u + hh] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-                if (((mask[u] >> (4 * hh)) & 0xfu) != 0) t.v[2 * u + hh] = *reinterpret_cast<const f4 *>(q);
+                if constexpr (MODE == kBoundary) {
+                    if (((mask[u] >> (4 * hh)) & 0xfu) != 0) t.v[2 * u + hh] = *reinterpret_cast<const f4_at4 *>(q);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if ((mask[u] >> (4 * hh + e)) & 1u) t.v[2 * u + hh][e] = q[e];
+                }
             }
         }
 }
 
-template <int U, bool FULL, bool NT>
+template <int U, TileMode MODE, bool NT>
 __device__ __forceinline__ void tile_store8(float *p, const unsigned (&mask)[U], const Tile<2 * U> &t)
 {
     const int lane = static_cast<int>(threadIdx.x & (kWave - 1));
@@ -275,13 +289,13 @@ __device__ __forceinline__ void tile_store8(float *p, const unsigned (&mask)[U],
     for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-            if constexpr (FULL) {
+            if constexpr (MODE == kFull) {
                 f4 *q4 = reinterpret_cast<f4 *>(p - 4 * lane + u * (kWave * 8) + 256 * hh);
                 if (NT) __builtin_nontemporal_store(t.v[2 * u + hh], q4); else *q4 = t.v[2 * u + hh];
             } else {
                 float *q = p + u * (kWave * 8) + 4 * hh;
                 if (((mask[u] >> (4 * hh)) & 0xfu) == 0xfu) {
-                    *reinterpret_cast<f4 *>(q) = t.v[2 * u + hh];
+                    *reinterpret_cast<f4_at4 *>(q) = t.v[2 * u + hh];
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -352,19 +366,19 @@ struct Fused16Op {
     SgdStep sgd;
     int stage_base = 0;   // bytes into the dynamic LDS where the wavefronts' staging areas start (set at launch)
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
     {
         const int64_t o = static_cast<int64_t>(row) * ld + off;
-        tile_load16<U, FULL, NT>(xin + o, mask, raw.x);
-        tile_load8<U, FULL, NT>(vin + o, mask, raw.v);
-        tile_load16<U, FULL, NT>(g + o, mask, raw.g);
+        tile_load16<U, MODE, NT>(xin + o, mask, raw.x);
+        tile_load8<U, MODE, NT>(vin + o, mask, raw.v);
+        tile_load16<U, MODE, NT>(g + o, mask, raw.g);
     }
-    template <int U, bool FULL, bool NT, bool COMMIT = true>
+    template <int U, TileMode MODE, bool NT, bool COMMIT = true>
     __device__ __forceinline__ void finish(int row, int64_t off, const unsigned (&mask)[U], const Raw<U> &raw, Work<U> &t) const
     {
         Tile<2 * U> v32 = raw.v;
-        if constexpr (FULL) stage_to_own<U>(stage_of_this_wave(stage_base), v32);     // memory order -> own columns
+        if constexpr (MODE == kFull) stage_to_own<U>(stage_of_this_wave(stage_base), v32);     // memory order -> own columns
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -374,17 +388,17 @@ struct Fused16Op {
                 v32.v[2 * u + hh] = narrow(v);
             }
         if constexpr (COMMIT) {
-            if constexpr (FULL) stage_from_own<U>(stage_of_this_wave(stage_base), v32);
-            tile_store8<U, FULL, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
+            if constexpr (MODE == kFull) stage_from_own<U>(stage_of_this_wave(stage_base), v32);
+            tile_store8<U, MODE, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
         }
     }
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Work<U> &t) const
     {
         Tile<U> packed;
 #pragma unroll
         for (int u = 0; u < U; ++u) packed.v[u] = narrow16_once<IEEE_HALF>(t.v[2 * u], t.v[2 * u + 1]);
-        tile_store16<U, FULL, NT>(xout + static_cast<int64_t>(row) * ld + off, mask, packed);
+        tile_store16<U, MODE, NT>(xout + static_cast<int64_t>(row) * ld + off, mask, packed);
     }
 };
 
@@ -409,20 +423,20 @@ struct HierFused16Op {
     SgdStep sgd;
     int stage_base = 0;   // as in Fused16Op
 
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
     {
         const int64_t lead = static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_load16<U, FULL, NT>(g + lead + j * ld, mask, raw.g[j]);
-        tile_load16<U, FULL, NT>(xin + lead, mask, raw.x);
-        tile_load8<U, FULL, NT>(vin + static_cast<int64_t>(row) * ld + off, mask, raw.v);
+        for (int j = 0; j < G; ++j) tile_load16<U, MODE, NT>(g + lead + j * ld, mask, raw.g[j]);
+        tile_load16<U, MODE, NT>(xin + lead, mask, raw.x);
+        tile_load8<U, MODE, NT>(vin + static_cast<int64_t>(row) * ld + off, mask, raw.v);
     }
-    template <int U, bool FULL, bool NT, bool COMMIT = true>
+    template <int U, TileMode MODE, bool NT, bool COMMIT = true>
     __device__ __forceinline__ void finish(int row, int64_t off, const unsigned (&mask)[U], const Raw<U> &raw, Work<U> &t) const
     {
         Tile<2 * U> v32 = raw.v;
-        if constexpr (FULL) stage_to_own<U>(stage_of_this_wave(stage_base), v32);
+        if constexpr (MODE == kFull) stage_to_own<U>(stage_of_this_wave(stage_base), v32);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -436,11 +450,11 @@ struct HierFused16Op {
                 v32.v[2 * u + hh] = narrow(v);
             }
         if constexpr (COMMIT) {
-            if constexpr (FULL) stage_from_own<U>(stage_of_this_wave(stage_base), v32);
-            tile_store8<U, FULL, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
+            if constexpr (MODE == kFull) stage_from_own<U>(stage_of_this_wave(stage_base), v32);
+            tile_store8<U, MODE, NT>(vout + static_cast<int64_t>(row) * ld + off, mask, v32);
         }
     }
-    template <int U, bool FULL, bool NT>
+    template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Work<U> &t) const
     {
         Tile<U> packed;
@@ -448,7 +462,7 @@ struct HierFused16Op {
         for (int u = 0; u < U; ++u) packed.v[u] = narrow16_once<IEEE_HALF>(t.v[2 * u], t.v[2 * u + 1]);
         uint16_t *p = xout + static_cast<int64_t>(row) * G * ld + off;
 #pragma unroll
-        for (int j = 0; j < G; ++j) tile_store16<U, FULL, NT>(p + j * ld, mask, packed);
+        for (int j = 0; j < G; ++j) tile_store16<U, MODE, NT>(p + j * ld, mask, packed);
     }
 };
 

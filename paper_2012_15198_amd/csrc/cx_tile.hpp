@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #define CX_SCHED_FN __device__ __forceinline__
+#include "cx_columns.hpp"           // the columns of boundary tiles
 #include "cx_schedule.hpp"          // build_schedule: the cycle order of a peer table
 static_assert(CX_MAX_ROWS <= (1 << kRowBits), "row ids must fit the schedule's packed fields");
 
@@ -82,43 +83,55 @@ __device__ __forceinline__ void wave_sync()
 
 // ---------------------------------------------------------------------------------
 // Tile I/O.  `p` points at this lane's first slice of the row (row base + tile start
-// + 4*lane); slice u sits 256 floats further.  FULL: whole 16-byte slices.  Otherwise
+// + 4*lane); slice u sits 256 floats further.  MODE kFull: whole 16-byte slices.  Otherwise
 // bit e of mask[u] says whether element e of slice u belongs to this lane right now.
 //
-// A boundary tile loads a slice whole as soon as one of its elements counts, and stores it whole where
-// all do; only the slice that a boundary cuts is stored element by element.  What it loads beside the
-// wanted columns is the row's own memory -- rows are 16-byte aligned and hold ld >= P elements, ld a
-// multiple of the slice -- and goes nowhere, since only the mask's elements are stored.  (Element-wise loads
+// kBoundary: a slice is loaded whole as soon as one of its elements counts, and stored whole where
+// all do; only the slice that a boundary cuts is stored element by element.  What is loaded beside the
+// wanted columns are other columns below P of the same row (slices at the row end slide, cx_columns.hpp, and are
+// aligned to their elements only), and goes nowhere, since only the mask's elements are stored.  (Element-wise loads
 // under a mask are a branch and a wait each: 8 columns of a group of 8 were 64 memory latencies in a row,
 // which made the boundary tile the longest part of every small launch: the binary16 gradient step on 42 x 242,981
 // in place, groups of 6: 91 -> 34 us; the binary16 group mean on 64 x 11,689,511 in place: 773 -> 678 us.)
+//
+// kShortRow: rows shorter than one slice, loaded and stored element by element.
 // ---------------------------------------------------------------------------------
-template <int U, bool FULL, bool NT>
+enum TileMode { kBoundary, kFull, kShortRow };
+typedef f4 f4_at4 __attribute__((aligned(4)));         // a slice aligned to its 32-bit
+typedef f4 f4_at2 __attribute__((aligned(2)));         // or 16-bit columns
+
+template <int U, TileMode MODE, bool NT>
 __device__ __forceinline__ void tile_load(const float *p, const unsigned (&mask)[U], Tile<U> &t)
 {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if constexpr (FULL) {
+        if constexpr (MODE == kFull) {
             const f4 *q = reinterpret_cast<const f4 *>(p + u * 256);
             t.v[u] = NT ? __builtin_nontemporal_load(q) : *q;
         } else {
             t.v[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (mask[u] != 0) t.v[u] = *reinterpret_cast<const f4 *>(p + u * 256);
+            if constexpr (MODE == kBoundary) {
+                if (mask[u] != 0) t.v[u] = *reinterpret_cast<const f4_at4 *>(p + u * 256);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if ((mask[u] >> e) & 1u) t.v[u][e] = p[u * 256 + e];
+            }
         }
     }
 }
 
-template <int U, bool FULL, bool NT>
+template <int U, TileMode MODE, bool NT>
 __device__ __forceinline__ void tile_store(float *p, const unsigned (&mask)[U], const Tile<U> &t)
 {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if constexpr (FULL) {
+        if constexpr (MODE == kFull) {
             f4 *q = reinterpret_cast<f4 *>(p + u * 256);
             if (NT) __builtin_nontemporal_store(t.v[u], q); else *q = t.v[u];
         } else {
             if (mask[u] == 0xfu) {
-                *reinterpret_cast<f4 *>(p + u * 256) = t.v[u];
+                *reinterpret_cast<f4_at4 *>(p + u * 256) = t.v[u];
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)

@@ -128,3 +128,51 @@ def test_in_place_walk_shapes(kind, W, P):
         want, wv = (once(t) for t in O.sgd_fused_mix_f64(x, v, g, 0.1, 0.9, 1e-4, P, so, pe))
         assert same_bits(host(vd)[:, :P], wv[:, :P])
     assert same_bits(host(a)[:, :P], want[:, :P])
+
+
+@pytest.mark.parametrize("slices", [-1, 2, 4])
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 7, 9, 259, 515, 1030, 2061])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_the_last_rows_storage_may_end_at_its_last_column(P, in_place, slices):
+    """Columns [P, ld) are the caller's own: a matrix may stop at the last row's column P (what follows here belongs
+    to somebody else and stays as it is).  Row lengths below a slice, below a tile and just above, slices per lane
+    1, 2 and 4: no slice at the row end ends with the row."""
+    W, G, S = 6, 3, 3
+    ld = (P + 7) // 8 * 8 + 8
+    so = np.array([0, P // 3, max(P - 2, P // 3), P], dtype=np.int64)
+    pe, pl = O.topology(P, W, S, 0, 1)[0], O.topology(P, W // G, S, 0, 1)[0]
+    x, v, g = (WL.gen_matrix(W, P, s, seed=P, ld=ld, stream=k) for k, s in enumerate((0.05, 0.02, 0.01)))
+    sod, ped, pld = dev(so), dev(pe), dev(pl)
+    print(P, in_place, slices, flush=True)
+
+    def tight(a):                                          # rows of a in storage that ends at the last row's column P
+        a = np.ascontiguousarray(a)
+        n = (a.shape[0] - 1) * ld + P
+        buf = dev(np.concatenate([a.reshape(-1)[:n], np.full(16, 77, a.dtype)]))
+        return buf, buf[:n].as_strided((a.shape[0], P), (ld, 1))
+
+    def check(call, a, want, wide=(), keep=()):
+        """call(x_in, x_out, *other buffers) with a's rows; want: the oracle's matrices, one for each written buffer."""
+        bufs = [tight(m) for m in (a, *wide)]
+        outs = bufs if in_place else [tight(m) for m in (a, *wide)]
+        kept = [tight(m)[1] for m in keep]
+        call(*[t for pair in zip(bufs, outs) for t in (pair[0][1], pair[1][1])], *kept)
+        for (buf, out), w in zip(outs, want):
+            got = host(out)
+            if got.dtype == np.int16:
+                assert (got.view(np.uint16) == w[:, :P]).all()
+            else:
+                assert same_bits(got, w[:, :P])
+            assert (host(buf)[-16:] == 77).all()
+
+    with Tuning(slices=slices):
+        check(lambda a, b: cx.cx_gossip_mix(a, b, P, sod, ped), x, [O.gossip_mix(x, P, so, pe)])
+        check(lambda a, b: cx.cx_hier_mix(a, b, P, G, sod, pld), x, [once(O.hier_mix_f64(x, P, G, so, pl))])
+        want = [once(t) for t in O.sgd_fused_mix_f64(x, v, g, 0.1, 0.9, 1e-4, P, so, pe)]
+        check(lambda a, b, c, d, e: cx.cx_sgd_fused_mix(a, b, c, d, e, 0.1, 0.9, 1e-4, P, sod, ped), x, want, [v], [g])
+        for fmt, narrow in (("bf16", O.f32_to_bf16), ("f16", O.f32_to_f16)):
+            xb, gb = narrow(x), narrow(g)
+            mix, step = getattr(cx, f"cx_gossip_mix_{fmt}"), getattr(cx, f"cx_sgd_fused_mix_{fmt}")
+            check(lambda a, b: mix(a, b, P, sod, ped), xb.view(np.int16), [getattr(O, f"gossip_mix_{fmt}")(xb, P, so, pe)])
+            check(lambda a, b, c, d, e: step(a, b, c, d, e, 0.1, 0.9, 1e-4, P, sod, ped), xb.view(np.int16),
+                  O.sgd_fused_mix16(fmt, xb, v, gb, 0.1, 0.9, 1e-4, P, so, pe), [v], [gb.view(np.int16)])

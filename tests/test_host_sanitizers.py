@@ -7,6 +7,8 @@ code the kernels share with the host, and the oracle.  CPU only; every build goe
   * tests/host/host_half_check.cpp: csrc/cx_host.cpp and oracle/cx_oracle.c in one ASan + UBSan program:
     topologies of both compared for every mode, the table checkers, every oracle function on exact-size
     heap buffers;
+  * tests/host/boundary_tile_check.cpp: the columns that a boundary tile's lanes load and store
+    (csrc/cx_columns.hpp), on every short row length;
   * the oracle's own pin tests re-run against an ASan + UBSan build of the oracle;
   * tests/host/hbm_policy_check.cpp: csrc/cx_hbm.cpp (placement of the matrices in physical memory) against a model
     of device memory behind a stand-in runtime header: where the pieces land, what is given back, and every
@@ -44,6 +46,13 @@ def test_cycle_schedule_under_address_sanitizer_at_the_maximum_row_count(tmp_pat
     run(["g++", "-std=c++17", *SAN, "-I", CSRC, os.path.join(HOST, "schedule_check.cpp"), "-o", str(exe), "-lpthread"])
     assert run([str(exe), "7", "1024"], env=ENV).startswith("ok")
     assert run([str(exe), "1", "1024"], env=ENV).startswith("ok")
+
+
+def test_boundary_tiles_read_no_column_beyond_the_row(tmp_path):
+    exe = tmp_path / "boundary_tile"
+    run(["g++", "-std=c++17", *SAN, "-Wall", "-Wextra", "-Wno-unknown-pragmas", "-I", CSRC,
+         os.path.join(HOST, "boundary_tile_check.cpp"), "-o", str(exe)])
+    assert run([str(exe)], env=ENV).startswith("ok")
 
 
 def test_host_half_and_oracle_under_address_and_ub_sanitizers(tmp_path):
