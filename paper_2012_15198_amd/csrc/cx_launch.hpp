@@ -226,7 +226,22 @@ unsigned *order_table_for(hipStream_t stream)
 // Short rows: a workgroup of the operator's full size would leave too few chunks to deal out evenly to eight
 // XCDs, so the workgroup is halved until there are kMinChunks of them (or it is one wavefront): 13 or more
 // chunks per XCD keep the uneven last one below 8 %.  512 rows x 100,003 fp32 columns: 98 chunks of 4 waves.
+// An operator staged through LDS keeps its waves: the staging is laid out for one shape, and other workgroups of it
+// take the path in registers.
 constexpr int64_t kMinChunks = 104;
+template <class Op, int U>
+constexpr int gather_waves(int64_t P, int waves)
+{
+    const int64_t wave_cols = static_cast<int64_t>(kWave) * Op::kElems * U;
+    while (!LdsStaged<Op>::value && waves > 1 && P <= (kMinChunks - 1) * wave_cols * waves) waves /= 2;
+    return waves;
+}
+template <class Op>
+constexpr bool staged_shape(int waves)
+{
+    return LdsStaged<Op>::value && static_cast<size_t>(waves) * waves * kWave * sizeof(f4) == LdsStaged<Op>::bytes;
+}
+
 template <class Op, int U>
 bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, int cl_req, int xcd_aware,
                 const MixArgs &a, int *status)
@@ -235,9 +250,8 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     if constexpr (U > MaxSlices<Op>::value) {
         return false;
     } else {
-    const int64_t wave_cols = static_cast<int64_t>(kWave) * Op::kElems * U;
     const int full_waves = waves;
-    while (!waves_fixed && xcd_aware && waves > 1 && a.P <= (kMinChunks - 1) * wave_cols * waves) waves /= 2;
+    if (!waves_fixed && xcd_aware) waves = gather_waves<Op, U>(a.P, waves);
     const int64_t chunk_cols = static_cast<int64_t>(kWave) * Op::kElems * U * waves;
     const int64_t nchunks = (a.P + chunk_cols - 1) / chunk_cols;
     if (nchunks < 8) xcd_aware = 0;               // fewer chunks than XCDs: rows go round the XCDs instead
@@ -317,7 +331,7 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     int cap = cx_get_tuning(9);
     if (cap < 0 || cap > 16) cap = Op::kGather.wgs_per_cu * full_waves / waves;   // the same waves per CU
     size_t glds = lds_reservation(cap);
-    if (LdsStaged<Op>::value && glds < LdsStaged<Op>::bytes) glds = LdsStaged<Op>::bytes;
+    if (U == 1 && staged_shape<Op>(waves) && glds < LdsStaged<Op>::bytes) glds = LdsStaged<Op>::bytes;
     if (glds < static_cast<size_t>(StageBytes<Op>::value) * waves) glds = static_cast<size_t>(StageBytes<Op>::value) * waves;
     const Op staged = with_stage_base(op, 0);
     const auto launch = [&](auto kernel) {
