@@ -86,6 +86,7 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
     typename Op::template Raw<U> slot[D];
     WorkT cur, first;
     int e = 0, base = 0;
+    constexpr bool kSteady = !std::is_same_v<Op, MeanOp<16>>;   // whose registers spill with the steady loop as well
     auto step = [&](const WorkT &nx, int e1) {            // average row k, open the next cycle where one closes
         const bool last = (e & kLastBit) != 0;
         WorkT out;
@@ -96,7 +97,7 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
         cur = nx;
         e = e1;
     };
-    if (n > 2 * D) {
+    if (kSteady && n > 2 * D) {
         int word[D];                                      // schedule words of the rows in flight
 #pragma unroll
         for (int j = 0; j < D; ++j) {

@@ -85,12 +85,22 @@ struct MaxSlices<Op, std::void_t<decltype(Op::kMaxU)>> {
     static constexpr int value = Op::kMaxU;                // an operator may build fewer shapes
 };
 
+// Shapes within the estimate below for which the compiler still put registers into scratch (an operator names its own).
+template <class Op, int U, int D, class = void>
+struct Spills {
+    static constexpr bool value = false;
+};
+template <class Op, int U, int D>
+struct Spills<Op, U, D, std::void_t<decltype(Op::template kSpills<U, D>)>> {
+    static constexpr bool value = Op::template kSpills<U, D>;
+};
+
 template <class Op, int U, int D>
 constexpr bool fits()
 {
     // registers of the ring of rows in flight plus the four working tiles of the walk: a
     // workgroup of eight waves leaves each wave 256 registers
-    return U <= MaxSlices<Op>::value &&
+    return U <= MaxSlices<Op>::value && !Spills<Op, U, D>::value &&
            Op::kRawPerSlice * U * D * 4 + 4 * Op::template Work<U>::kN * Op::template Work<U>::kRegs <= 224 &&
            Op::kRawPerSlice * U * D * 4 <= 144 && !(U == 4 && Op::kRawPerSlice * D >= 8);
 }
@@ -247,7 +257,7 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
                 const MixArgs &a, int *status)
 {
     if (want_u != U) return false;
-    if constexpr (U > MaxSlices<Op>::value) {
+    if constexpr (U > MaxSlices<Op>::value || (U > 1 && Op::kRawPerSlice * U > 8)) {   // launch_mix asks for no such U
         return false;
     } else {
     const int full_waves = waves;

@@ -48,7 +48,8 @@ struct MeanOp {
         G == 1 ? GatherShape{1, 4, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0} : GatherShape{1, 8, 768, 0};
     static constexpr int kVisitKbFewRows = G >= 8 ? 256 : kGather.visit_kb;      // see VisitKb
     static constexpr WalkShape kWalk =
-        G == 1 ? WalkShape{2, 8, 8, 2} : G == 2 ? WalkShape{2, 4, 8, 2} : G <= 8 ? WalkShape{2, 2, 8, 2} : WalkShape{1, 2, 8, 2};
+        G == 1 ? WalkShape{2, 8, 8, 2} : G == 2 ? WalkShape{2, 4, 8, 2} : G <= 5 ? WalkShape{2, 2, 8, 2} : G <= 8 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
+    template <int U, int D> static constexpr bool kSpills = U > 1 && (G >= 6 || (G == 3 && U * D >= 8));
     template <int U> struct Raw { Tile<U> r[G]; };
     const float *xin;
     float *xout;
@@ -270,6 +271,7 @@ struct HierFusedOp {
     static constexpr int kVisitKbFewRows = G >= 8 ? 256 : kGather.visit_kb;      // see VisitKb
     static constexpr WalkShape kWalk = G <= 4 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G <= 2 ? 2 : 1;
+    template <int U, int D> static constexpr bool kSpills = G == 5 && D == 4;
     template <int U> struct Raw { Tile<U> g[G], x, v; };
     const float *xin;
     float *xout;

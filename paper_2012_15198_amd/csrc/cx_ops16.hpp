@@ -128,6 +128,7 @@ struct Row16Op {
         G == 1 ? GatherShape{1, 8, 96, 0} : G <= 4 ? GatherShape{1, 8, 256, 0} : GatherShape{1, 8, 384, 0};
     static constexpr WalkShape kWalk = G == 1 ? WalkShape{2, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G == 1 ? 4 : 1;           // grouped: one slice per lane fills the registers
+    template <int U, int D> static constexpr bool kSpills = U == 4 && D == 4;
     template <int U> struct Raw { Tile<U> r[G]; };         // packed 16-bit pairs, as loaded
     const uint16_t *xin;
     uint16_t *xout;
@@ -218,6 +219,7 @@ struct Push16Op : Row16Op<IEEE_HALF, 1> {
     using Base = Row16Op<IEEE_HALF, 1>;
     static constexpr GatherShape kGather{2, 4, 192, 0};    // measured on C4: one slice per lane 52 %, two 76 %
     static constexpr WalkShape kWalk{2, 4, 8, 2};
+    template <int U, int D> static constexpr bool kSpills = U * D >= 16;
     uint16_t *zout;       // may be null
     const float *win;
     int n, hop;

@@ -48,3 +48,10 @@ def kernels(tmp_path_factory):
 def test_boundary_tiles_do_not_cost_the_out_of_place_kernels_wavefronts(kernels, op, waves):
     registers = kernels[f"gather_kernel<{op}, 1, true, false>"][0]
     assert 512 // (-(-registers // 8) * 8) >= waves, registers
+
+
+def test_no_mixing_kernel_keeps_registers_in_scratch(kernels):
+    """fits() in cx_launch.hpp admits shapes that stay in registers: scratch is slow, and the runtime would reserve it
+    on the first launch, where no call may allocate."""
+    mixing = {name: scratch for name, (_, scratch) in kernels.items() if name.startswith(("mix_kernel<", "gather_kernel<"))}
+    assert len(mixing) > 400 and not {name: scratch for name, scratch in mixing.items() if scratch}
