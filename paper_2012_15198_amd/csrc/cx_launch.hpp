@@ -105,18 +105,32 @@ constexpr bool fits()
            Op::kRawPerSlice * U * D * 4 <= 144 && !(U == 4 && Op::kRawPerSlice * D >= 8);
 }
 
+// The waves of an in-place workgroup whose schedules, one per wave, stay within 48 KB of LDS.
+template <class Op>
+constexpr int waves_with_schedules(int n, int waves)
+{
+    while (waves > 1 && (sizeof(int) * kScheduleWords(n) + StageBytes<Op>::value) * waves > 48 * 1024) --waves;
+    return waves;
+}
+
 // In-place walk on short rows: a wavefront walks all rows of its tile one after the other, so a launch lasts as
 // long as one walk and the bytes in flight come from narrow tiles (more walks) and a deep ring (more rows of each).
-// Below kShortTiles tiles (8 wavefronts per CU; three times as many where a lane would take two slices) a lane takes one slice and the deepest ring that stays within
-// kShortRing 16-byte registers; workgroups are halved until there are kShortBlocks of them, one for every second CU
-// (fewer, larger ones lose to idle CUs, more lose the lock-step of the waves: bf16 gradient step on 256 x 300,007 in groups
-// of 8: 117 us with 4 waves, 132 with one).  fp32 optimizer step on 256 x 75,003: 444 -> 123 us with one slice, eight rows;
-// bf16 gossip on 256 x 300,007: 153 -> 108.
+// Below kShortTiles tiles (8 wavefronts per CU; three times as many where a lane would take two slices) a lane takes
+// one slice and the deepest ring that stays within kShortRing 16-byte registers; workgroups are halved until there
+// are kShortBlocks of them, one for every second CU (fewer, larger ones lose to idle CUs, more lose the lock-step of
+// the waves: bf16 gradient step on 256 x 300,007 in groups of 8: 117 us with 4 waves, 132 with one).  fp32 optimizer
+// step on 256 x 75,003: 444 -> 123 us with one slice, eight rows; bf16 gossip on 256 x 300,007: 153 -> 108.
+//
+// The cap on resident workgroups is a cap on wavefronts: where a workgroup has fewer than the operator's, because rows
+// are short or because many rows' schedules fill the LDS, more of them may be resident.  1,024 x 300,007 fp32 in place,
+// workgroups of two waves, two of them against eight per CU: gossip 707 -> 592 us, optimizer step 1,494 -> 1,349,
+// push-sum with the de-biased copy 1,713 -> 1,179.
 constexpr int64_t kShortTiles = 2048, kShortBlocks = 128;
 constexpr int kShortRing = 32;
 template <class Op>
-WalkShape short_walk(int64_t P, WalkShape shape)
+constexpr WalkShape walk_shape(int n, int64_t P)
 {
+    WalkShape shape = Op::kWalk;
     const auto tiles = [&] {
         const int64_t cols = static_cast<int64_t>(kWave) * Op::kElems * shape.U;
         return (P + cols - 1) / cols;
@@ -127,7 +141,10 @@ WalkShape short_walk(int64_t P, WalkShape shape)
                   : fits<Op, 1, 4>() && Op::kRawPerSlice * 4 <= kShortRing ? 4
                                                                           : 2;
     }
+    const int full_waves = shape.waves;
     while (shape.waves > 1 && tiles() <= (kShortBlocks - 1) * shape.waves) shape.waves /= 2;
+    shape.waves = waves_with_schedules<Op>(n, shape.waves);
+    shape.wgs_per_cu = shape.wgs_per_cu * full_waves / shape.waves;
     return shape;
 }
 
@@ -140,8 +157,7 @@ bool try_launch(const Op &op, const Launch &l, const MixArgs &a)
     } else {
         const int64_t tile_cols = static_cast<int64_t>(kWave) * Op::kElems * U;
         const int64_t ntiles = (a.P + tile_cols - 1) / tile_cols;
-        int waves = l.waves;
-        while (waves > 1 && (sizeof(int) * kScheduleWords(a.n) + StageBytes<Op>::value) * waves > 48 * 1024) --waves;
+        const int waves = waves_with_schedules<Op>(a.n, l.waves);
         const int64_t nblocks = (ntiles + waves - 1) / waves;
         // one wavefront for each inner segment boundary, ahead of the tiles (boundaries that fall on a tile's edge
         // leave theirs at once)
@@ -385,7 +401,7 @@ int launch_mix(const Op &op, const MixArgs &a)
             try_gather<Op, 4>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status))
             return status;
     }
-    Launch l = pick_launch(short_walk<Op>(a.P, Op::kWalk));
+    Launch l = pick_launch(walk_shape<Op>(a.n, a.P));
     if (a.P < kSliceLanes * l.U) l.U = 1;
     if (a.P < Op::kElems) l.D = 2;
     const bool done =

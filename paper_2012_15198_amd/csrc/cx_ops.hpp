@@ -28,7 +28,7 @@ struct WalkShape {
 // dense in DRAM.  In place on 64 x 11,689,511, against two waves per workgroup: fp32 mean of groups of 8
 // 1,280 -> 1,199 us, binary16 of groups of 4 641 -> 592, bf16 gradient step of groups of 8 865 -> 810, bf16
 // optimizer step (four waves) 2,239 -> 2,141; fp32 gossip with eight rows of two slices in flight 1,255 -> 1,160.
-// Short rows: see short_walk in cx_launch.hpp.
+// Short rows: see walk_shape in cx_launch.hpp.
 
 // Plain gossip (G == 1) and hierarchical mode (a gossiping row = a group of G rows).
 // G == 1 is Algorithm 1's averaging line in fp32, as written.  For G > 1 the group sum (rows in

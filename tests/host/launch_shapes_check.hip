@@ -10,4 +10,12 @@ static_assert(gather_waves<MeanLdsOp<8>, 1>(150001, MeanLdsOp<8>::kGather.waves)
 static_assert(staged_shape<MeanLdsOp<8>>(MeanLdsOp<8>::kGather.waves) && !staged_shape<MeanLdsOp<8>>(4));
 static_assert(gather_waves<MeanOp<8>, 1>(150001, MeanOp<8>::kGather.waves) == 4 && !staged_shape<MeanOp<8>>(8));
 
+// In place, as many wavefronts per CU whatever the workgroup's size: two workgroups of eight, or eight of two where
+// 1,024 rows' schedules leave no room for more.
+constexpr bool same_waves_per_cu(const WalkShape &s) { return s.wgs_per_cu * s.waves == 16; }
+static_assert(walk_shape<MeanOp<1>>(256, 11689511).waves == 8 && same_waves_per_cu(walk_shape<MeanOp<1>>(256, 11689511)));
+static_assert(walk_shape<MeanOp<1>>(1024, 300007).waves == 2 && same_waves_per_cu(walk_shape<MeanOp<1>>(1024, 300007)));
+static_assert(walk_shape<PushOp>(1024, 11689511).waves == 2 && same_waves_per_cu(walk_shape<PushOp>(1024, 11689511)));
+static_assert(walk_shape<FusedOp>(256, 100003).waves == 2 && same_waves_per_cu(walk_shape<FusedOp>(256, 100003)));
+
 }  // namespace
