@@ -86,7 +86,9 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
     typename Op::template Raw<U> slot[D];
     WorkT cur, first;
     int e = 0, base = 0;
-    constexpr bool kSteady = !std::is_same_v<Op, MeanOp<16>>;   // whose registers spill with the steady loop as well
+    // Without the steady loop: the mean of groups of 16, whose registers would spill, and the shape that few long rows of
+    // plain gossip take (MeanOp::walk).
+    constexpr bool kSteady = !std::is_same_v<Op, MeanOp<16>> && !(std::is_same_v<Op, MeanOp<1>> && U == 1 && D == 2);
     auto step = [&](const WorkT &nx, int e1) {            // average row k, open the next cycle where one closes
         const bool last = (e & kLastBit) != 0;
         WorkT out;

@@ -125,21 +125,37 @@ constexpr int waves_with_schedules(int n, int waves)
 // are short or because many rows' schedules fill the LDS, more of them may be resident.  1,024 x 300,007 fp32 in place,
 // workgroups of two waves, two of them against eight per CU: gossip 707 -> 592 us, optimizer step 1,494 -> 1,349,
 // push-sum with the de-biased copy 1,713 -> 1,179.
+//
+// Operators on plain rows that take one slice instead of two there, with tiles enough, take eight rows in flight beside
+// many rows only: push-sum of 16-bit rows with the copy on 64 x 2,500,007 271 us with eight, 228 with four; bf16 gossip
+// on 32 x 3,200,013 98 us with eight, 85 with four; push-sum of 16-bit rows on 256 x 3,000,001 587 with either.
 constexpr int64_t kShortTiles = 2048, kShortBlocks = 128;
 constexpr int kShortRing = 32;
+template <class Op, class = void>
+struct LongWalk {
+    static constexpr WalkShape of(const Op &, int, int64_t, bool) { return Op::kWalk; }
+};
 template <class Op>
-constexpr WalkShape walk_shape(int n, int64_t P)
+struct LongWalk<Op, std::void_t<decltype(std::declval<const Op &>().walk(0, 0, false))>> {
+    static constexpr WalkShape of(const Op &op, int n, int64_t P, bool whole_lines) { return op.walk(n, P, whole_lines); }
+};
+template <class Op>
+constexpr WalkShape walk_shape(const Op &op, int n, int64_t P)
 {
-    WalkShape shape = Op::kWalk;
+    const bool whole_lines = op.ld * (16 / Op::kElems) % 128 == 0;
+    WalkShape shape = LongWalk<Op>::of(op, n, P, whole_lines);
     const auto tiles = [&] {
         const int64_t cols = static_cast<int64_t>(kWave) * Op::kElems * shape.U;
         return (P + cols - 1) / cols;
     };
     if (tiles() < (shape.U > 1 ? 3 : 1) * kShortTiles) {
         shape.U = 1;
+        shape.waves = Op::kWalk.waves;
+        shape.wgs_per_cu = Op::kWalk.wgs_per_cu;
         shape.D = fits<Op, 1, 8>() && Op::kRawPerSlice * 8 <= kShortRing   ? 8
                   : fits<Op, 1, 4>() && Op::kRawPerSlice * 4 <= kShortRing ? 4
                                                                           : 2;
+        if (Op::kRawPerSlice == 1 && tiles() >= kShortTiles && shape.D > ring_for(n)) shape.D = ring_for(n);
     }
     const int full_waves = shape.waves;
     while (shape.waves > 1 && tiles() <= (kShortBlocks - 1) * shape.waves) shape.waves /= 2;
@@ -401,7 +417,7 @@ int launch_mix(const Op &op, const MixArgs &a)
             try_gather<Op, 4>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status))
             return status;
     }
-    Launch l = pick_launch(walk_shape<Op>(a.n, a.P));
+    Launch l = pick_launch(walk_shape(op, a.n, a.P));
     if (a.P < kSliceLanes * l.U) l.U = 1;
     if (a.P < Op::kElems) l.D = 2;
     const bool done =

@@ -24,11 +24,29 @@ struct GatherShape {
 struct WalkShape {
     int U, D, waves, wgs_per_cu;       // slices per lane, rows in flight, waves per workgroup,
 };                                     // resident workgroups per CU (0 = as many as fit)
-// Long rows take kWalk as it stands: eight waves in lock-step and two workgroups per CU keep the rows' streams
-// dense in DRAM.  In place on 64 x 11,689,511, against two waves per workgroup: fp32 mean of groups of 8
-// 1,280 -> 1,199 us, binary16 of groups of 4 641 -> 592, bf16 gradient step of groups of 8 865 -> 810, bf16
-// optimizer step (four waves) 2,239 -> 2,141; fp32 gossip with eight rows of two slices in flight 1,255 -> 1,160.
+// Long rows in place: kWalk, eight waves in lock-step, unless the operator's walk(n, P, whole_lines) names another shape
+// (whole_lines: the row stride is a multiple of 128 bytes, so that rows begin on lines where the allocation does).
 // Short rows: see walk_shape in cx_launch.hpp.
+//
+// Rows that begin inside a line: neighbouring tiles share lines, and eight waves in lock-step touch them together.
+// Rows that begin on a line, and few rows in general, are better off with workgroups of two waves: no lines to share,
+// and the last of few rounds of large workgroups leaves CUs idle.  Two waves against eight, in place, us:
+//                                    64 x 11,689,511 on lines   inside lines   32 x 25,000,003 on lines   inside lines
+//     fp32 gossip                    1,089 / 1,126              1,185 / 1,151  1,155 / 1,194              1,208 / 1,217
+//     fp32 mean of groups of 4       1,103 / 1,130              1,221 / 1,195  1,095 / 1,247              1,234 / 1,281
+//     fp32 mean of groups of 8       1,117 / 1,155              1,266 / 1,258  1,140 / 1,201              1,310 / 1,275
+//     fp32 gradient step, groups of 6  1,298 / 1,371            1,453 / 1,476  1,371 / 1,454
+// 256 rows on lines take eight again: mean of groups of 4 on 256 x 3,000,001 1,238 / 1,195.  16-bit groups gain
+// nothing from two waves on long rows (binary16 mean of groups of 4 on 64 x 11,689,511: 581 / 558).
+// Neither do rows below two million columns (32 x 900,001, groups of 8: 50 / 45).
+constexpr bool two_waves(int G, int rows, int64_t P, bool whole_lines)
+{
+    return P >= (2 << 20) && ((rows <= 32 && G <= 5) || (rows <= 128 && whole_lines));
+}
+
+// Rows in flight of an operator whose finish() only copies or widens (see walk() in cx_kernels.hpp): eight beside
+// many rows only, since the last 2 * D steps of a walk are slower ones.
+constexpr int ring_for(int n) { return n >= 128 ? 8 : 4; }
 
 // Plain gossip (G == 1) and hierarchical mode (a gossiping row = a group of G rows).
 // G == 1 is Algorithm 1's averaging line in fp32, as written.  For G > 1 the group sum (rows in
@@ -50,6 +68,22 @@ struct MeanOp {
     static constexpr WalkShape kWalk =
         G == 1 ? WalkShape{2, 8, 8, 2} : G == 2 ? WalkShape{2, 4, 8, 2} : G <= 5 ? WalkShape{2, 2, 8, 2} : G <= 8 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     template <int U, int D> static constexpr bool kSpills = U > 1 && (G >= 6 || (G == 3 && U * D >= 8));
+    constexpr WalkShape walk(int n, int64_t P, bool whole_lines) const
+    {
+        const bool few = n * G <= 32;
+        if constexpr (G == 1) {
+            // few long rows on lines: one slice of two rows, many small workgroups, no steady loop (32 x 25,000,003:
+            // 1,109 us, with the steady loop 1,192, with two slices of two to eight rows 1,144 to 1,194; the length is
+            // that from which two slices count as long)
+            if (few) return whole_lines && P >= (3 << 20) ? WalkShape{1, 2, 2, 8} : WalkShape{2, 4, 2, 2};
+            return n <= 256 && whole_lines ? WalkShape{2, 2, 2, 2} : kWalk;
+        } else {
+            if (G > 8 || !two_waves(G, n * G, P, whole_lines)) return kWalk;
+            if (G == 2) return few ? WalkShape{2, 4, 2, 2} : kWalk;
+            if (G == 3) return few ? WalkShape{2, 2, 2, 2} : WalkShape{1, 4, 2, 2};
+            return WalkShape{1, G == 4 && !few ? 4 : 2, 2, 2};
+        }
+    }
     template <int U> struct Raw { Tile<U> r[G]; };
     const float *xin;
     float *xout;
@@ -216,6 +250,12 @@ struct FusedOp {
     static constexpr GatherShape kGather{1, 8, 128, 3};
     static constexpr WalkShape kWalk{2, 4, 8, 2};
     static constexpr int kMaxU = 2;                        // fp64 rows: two slices per lane fill the registers
+    constexpr WalkShape walk(int n, int64_t P, bool whole_lines) const
+    {
+        // in place, rows on lines, two waves against eight: 32 x 3,200,013 384 / 442 us, 64 x 11,689,511 2,917 / 2,862,
+        // 32 x 900,001 119 / 114
+        return n <= 32 && P >= (2 << 20) && whole_lines ? WalkShape{1, 4, 2, 2} : kWalk;
+    }
     template <int U> struct Raw { Tile<U> x, v, g; };
     const float *xin;
     float *xout;
@@ -272,6 +312,10 @@ struct HierFusedOp {
     static constexpr WalkShape kWalk = G <= 4 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G <= 2 ? 2 : 1;
     template <int U, int D> static constexpr bool kSpills = G == 5 && D == 4;
+    constexpr WalkShape walk(int n, int64_t P, bool whole_lines) const
+    {
+        return G <= 8 && two_waves(G, n * G, P, whole_lines) ? WalkShape{1, G == 1 ? 4 : 2, 2, 2} : kWalk;
+    }
     template <int U> struct Raw { Tile<U> g[G], x, v; };
     const float *xin;
     float *xout;
@@ -326,6 +370,14 @@ struct PushOp {
     static constexpr GatherShape kGather{2, 4, 512, 0};
     static constexpr WalkShape kWalk{2, 8, 8, 2};
     template <int U> struct Raw { Tile<U> x; };
+    // The weights that the de-biased copy loads make every row wait for all before it: one slice and a
+    // short ring.  Against eight rows of two slices and eight waves, rows on lines: 64 x 11,689,511 with the copy
+    // 1,791 -> 1,713 us, without 1,127 -> 1,070; 256 x 3,000,001 without 1,228 -> 1,185.
+    constexpr WalkShape walk(int n, int64_t, bool) const
+    {
+        if (zout) return WalkShape{1, ring_for(n), 8, 2};
+        return n <= 256 ? WalkShape{2, n <= 32 ? 4 : 2, 2, 2} : kWalk;
+    }
     const float *xin;
     float *xout;
     float *zout;          // may be null

@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 #define CX_SCHED_FN __device__ __forceinline__
 #include "cx_columns.hpp"           // the columns of boundary tiles

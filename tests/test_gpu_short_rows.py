@@ -100,8 +100,8 @@ def test_boundary_tiles_keep_to_their_columns(P, in_place):
         assert (host(b).view(np.uint16)[:, P:] == xb[:, P:]).all() and np.isnan(host(bv)[:, P:]).all()
 
 
-# in place: the edges where workgroups are halved (127 * 1, 2, 4, 8 tiles) and where one slice per lane begins (2,047
-# tiles of two), for rings that the steady loop turns never, once and many times (n <= 2 D, n just above, n = 37)
+# in place: the edges where workgroups are halved (127 * 1, 2, 4, 8 tiles) and full ones of one slice per lane, for rings
+# that the steady loop turns never, once and many times (n <= 2 D, n just above, n = 37)
 @pytest.mark.parametrize("W", [3, 5, 17, 37])
 @pytest.mark.parametrize("P", [TILE * 127 + 1, TILE * 254, TILE * 1016 + 3, 2 * TILE * 2047, 2 * TILE * 2047 + 1])
 @pytest.mark.parametrize("kind", ["gossip", "fused", "bf16"])
@@ -176,3 +176,70 @@ def test_the_last_rows_storage_may_end_at_its_last_column(P, in_place, slices):
             check(lambda a, b: mix(a, b, P, sod, ped), xb.view(np.int16), [getattr(O, f"gossip_mix_{fmt}")(xb, P, so, pe)])
             check(lambda a, b, c, d, e: step(a, b, c, d, e, 0.1, 0.9, 1e-4, P, sod, ped), xb.view(np.int16),
                   O.sgd_fused_mix16(fmt, xb, v, gb, 0.1, 0.9, 1e-4, P, so, pe), [v], [gb.view(np.int16)])
+
+
+# in place, both sides of the edges between shapes: 2,048 tiles of one slice per lane (256 fp32 or 512 16-bit columns), 3 *
+# 2,048 of two where the long shape has two, the two or three million columns from which workgroups of two waves are taken;
+# walks of just more than 2 D steps, so that the steady loop turns.
+# (kind, rows per group, gossiping rows, columns of the last row below the edge, ld a multiple of)
+LONG_EDGES = [("gossip", 1, 9, (3 << 20) - 1, 32), ("gossip", 1, 9, 512 * 6143, 8), ("gossip", 1, 33, 512 * 6143, 32),
+              ("gossip", 1, 33, 512 * 6143, 8), ("hier", 2, 9, 512 * 6143, 8), ("hier", 3, 5, 512 * 6143, 8),
+              ("hier", 3, 13, (2 << 20) - 1, 32), ("hier", 4, 5, (2 << 20) - 1, 8), ("hier", 4, 9, (2 << 20) - 1, 32),
+              ("hier", 4, 9, 512 * 6143, 8), ("hier", 8, 5, (2 << 20) - 1, 32), ("hier", 8, 9, 256 * 2047, 8),
+              ("hier", 16, 5, 256 * 2047, 32), ("fused", 1, 9, (2 << 20) - 1, 32), ("fused", 1, 9, 512 * 6143, 8),
+              ("hiersgd", 1, 9, (2 << 20) - 1, 32), ("hiersgd", 4, 5, (2 << 20) - 1, 8), ("hiersgd", 5, 9, 256 * 2047, 8),
+              ("hiersgd", 6, 5, (2 << 20) - 1, 32), ("pushsum", 1, 9, 512 * 6143, 8), ("debias", 1, 17, 256 * 2047, 32),
+              ("gossip16", 1, 9, 1024 * 6143, 8), ("pushsum16", 1, 9, 1024 * 6143, 8), ("debias16", 1, 9, 512 * 2047, 64),
+              ("hier16", 4, 5, 512 * 2047, 8), ("fused16", 1, 5, 512 * 2047, 8), ("hiersgd16", 3, 5, 512 * 2047, 64)]
+
+
+@pytest.mark.parametrize("kind,G,n,short,ld_of", LONG_EDGES)
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_in_place_edge_of_short_rows(kind, G, n, short, ld_of, beyond):
+    W, P = n * G, short + beyond
+    ld = (P + ld_of - 1) // ld_of * ld_of
+    print(kind, G, n, P, ld, flush=True)
+    rng = np.random.default_rng(P + n)
+    so = np.array([0, P // 3 + 1, P // 3 + 1, P - 2, P], dtype=np.int64)
+    pe, hop = O.topology(P, n, len(so) - 1, 0, 1)[0], 2
+    sod, ped = dev(so), dev(pe)
+    matrix = lambda rows, sigma: rng.standard_normal((rows, ld), dtype=np.float32) * np.float32(sigma)
+    x, sgd = matrix(W, 0.05), (0.1, 0.9, 1e-4)
+    wide = kind.endswith("16")
+    if wide:
+        x = O.f32_to_bf16(x)
+    a = dev(x.view(np.int16) if wide else x)
+    kind, b16 = kind.removesuffix("16"), "_bf16" if wide else ""
+    if kind == "gossip":
+        getattr(cx, "cx_gossip_mix" + b16)(a, a, P, sod, ped)
+        want = O.gossip_mix_bf16(x, P, so, pe) if wide else O.gossip_mix(x, P, so, pe)
+    elif kind == "hier":
+        getattr(cx, "cx_hier_mix" + b16)(a, a, P, G, sod, ped)
+        want = O.hier_mix16("bf16", x, P, G, so, pe) if wide else once(O.hier_mix_f64(x, P, G, so, pe))
+    elif kind in ("pushsum", "debias"):
+        w = (0.5 + rng.random(W)).astype(np.float32)
+        wd, wo, z = dev(w), dev(w), torch.zeros_like(a) if kind == "debias" else None
+        getattr(cx, "cx_pushsum_mix" + b16)(a, a, wd, wo, z, P, hop)
+        want, ww, wz = O.pushsum_mix16("bf16", x, w, P, hop, True) if wide else O.pushsum_mix_f32(x, w, P, hop, True)
+        assert same_bits(host(wo), ww)
+        if z is not None:
+            got = host(z)[:, :P]
+            assert (got.view(np.uint16) == wz[:, :P]).all() if wide else same_bits(got, wz[:, :P])
+    else:
+        v, g = matrix(n, 0.02), matrix(W, 0.01)
+        if wide:
+            g = O.f32_to_bf16(g)
+        vd, gd = dev(v), dev(g.view(np.int16) if wide else g)
+        if kind == "fused":
+            getattr(cx, "cx_sgd_fused_mix" + b16)(a, a, vd, vd, gd, *sgd, P, sod, ped)
+            want, wv = O.sgd_fused_mix16("bf16", x, v, g, *sgd, P, so, pe) if wide else \
+                (once(t) for t in O.sgd_fused_mix_f64(x, v, g, *sgd, P, so, pe))
+        else:
+            getattr(cx, "cx_hier_sgd_fused_mix" + b16)(a, a, vd, vd, gd, *sgd, P, G, sod, ped)
+            want, wv = O.hier_sgd_fused_mix16("bf16", x, v, g, *sgd, P, G, so, pe) if wide else \
+                (once(t) for t in O.hier_sgd_fused_mix_f64(x, v, g, *sgd, P, G, so, pe))
+        assert same_bits(host(vd)[:, :P], wv[:, :P])
+    if wide:
+        assert (host(a).view(np.uint16)[:, :P] == want[:, :P]).all()
+    else:
+        assert same_bits(host(a)[:, :P], want[:, :P])
