@@ -66,18 +66,21 @@ struct BlockSync {
     __device__ __forceinline__ void add(int *p, int v) const { atomicAdd(p, v); }
 };
 
-// One lane's walk over all cycles of the schedule, software-pipelined: the global loads of
-// the rows of steps k+2 .. k+1+D are in flight while step k is averaged and stored.  Rows
-// are fetched in schedule order, each exactly once, into a ring of D register slots
-// (statically indexed: the step loop is unrolled by D).  Loads are always issued ahead of
-// the store of the current row, so a load never waits behind a store's acknowledgement.
+// One lane's walk over all cycles of the schedule.  Rows are fetched in schedule order, each exactly
+// once, into a ring of D register slots (statically indexed: the step loop is unrolled by D), up to D
+// rows ahead of the step that averages and stores.
 //
-// The steps run in two loops.  As long as every step of a turn has a row to fetch, a turn holds no branch around
-// a load: the compiler then knows how many accesses follow the one it waits for and waits for that one alone.
-// (With a branch around each load it waited for all but the last access of the wavefront, so D rows were issued
-// but one was in flight: gossip on 256 x 8,303 fp32, in place, 8 segments: 230 -> 86 us together with the boundary
-// pieces below; fused step 256 x 300,007: 806 -> 573 us.)  The schedule's words are read from LDS one step ahead and kept until their row arrives.
-// The last turns, up to 2 * D steps, decide step by step.
+// The steps run in two loops.  As long as every step of a turn has a row to fetch, a turn holds no branch
+// around a load, so the compiler knows how many accesses follow the one it waits for.  What it makes of that
+// depends on finish() (waits read from the assembly): where finish() consumes the slot by arithmetic and a store
+// (FusedOp with one slice, HierFusedOp, Fused16Op), every step waits for its own row and the others stay in
+// flight; where finish() only copies, widens or sums the slot (gossip, group means, push-sum, 16-bit rows), the
+// compiler gathers that at the head of the turn and waits there for all rows in flight and the last stores: the
+// ring is a batch of D rows a turn, not a pipeline.  (A branch around each load made it wait for all but the last
+// access of the wavefront at every step: gossip on 256 x 8,303 fp32, in place, 8 segments: 230 -> 86 us together
+// with the boundary pieces below; fused step 256 x 300,007: 806 -> 573 us.)  The schedule's words are read from
+// LDS one step ahead and kept until their row arrives.  The last turns, up to 2 * D steps, decide step by step;
+// walks of at most 2 * D rows consist of them.
 template <class Op, int U, int D, TileMode MODE, bool NT, bool SYNC = false>
 __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool skip_mix,
                                      int64_t off, const unsigned (&mask)[U])
@@ -202,7 +205,8 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
             unsigned mask[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) mask[u] = (1u << kSliceCols) - 1u;
-            walk<Op, U, D, kFull, NT, true>(op, sched, n, skip_mix != 0, column_of<Op>(g0 + static_cast<int64_t>(wave) * kTileCols, lane, 0, 0), mask);
+            const int64_t first = g0 + static_cast<int64_t>(wave) * kTileCols;
+            walk<Op, U, D, kFull, NT, true>(op, sched, n, skip_mix != 0, column_of<Op>(first, lane, 0, 0), mask);
             return;
         }
     }
@@ -239,7 +243,8 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
     if (e > c0 + kTileCols) e = c0 + kTileCols;
     if (b >= e) return;
     const int64_t place = column_of<Op>(c0, lane, 0, 0);
-    const int64_t off = place - (SHORT ? 0 : row_end_slide(P, c0, place, U, kTileCols, kSliceCols));   // this lane's first column
+    // this lane's first column
+    const int64_t off = place - (SHORT ? 0 : row_end_slide(P, c0, place, U, kTileCols, kSliceCols));
     build_schedule(work, n, lane, kWave, peers, s, shift, WaveSync{});
     unsigned mask[U];
     if (e - b == kTileCols) {
