@@ -41,7 +41,7 @@ struct WalkShape {
 // Neither do rows below two million columns (32 x 900,001, groups of 8: 50 / 45).
 constexpr bool two_waves(int G, int rows, int64_t P, bool whole_lines)
 {
-    return P >= (2 << 20) && ((rows <= 32 && G <= 5) || (rows <= 128 && whole_lines));
+    return P >= (2 << 20) && ((rows <= 32 && G <= 5) || (rows <= 64 && whole_lines));
 }
 
 // Rows in flight of an operator whose finish() only copies or widens (see walk() in cx_kernels.hpp): eight beside
@@ -77,7 +77,7 @@ struct MeanOp {
             // 1,109 us, with the steady loop 1,192, with two slices of two to eight rows 1,144 to 1,194; the length is
             // that from which two slices count as long)
             if (few) return whole_lines && P >= (3 << 20) ? WalkShape{1, 2, 2, 8} : WalkShape{2, 4, 2, 2};
-            return n <= 256 && whole_lines ? WalkShape{2, 2, 2, 2} : kWalk;
+            return n <= 64 && whole_lines ? WalkShape{2, 2, 2, 2} : kWalk;
         } else {
             if (G > 8 || !two_waves(G, n * G, P, whole_lines)) return kWalk;
             if (G == 2) return few ? WalkShape{2, 4, 2, 2} : kWalk;
@@ -373,11 +373,11 @@ struct PushOp {
     template <int U> struct Raw { Tile<U> x; };
     // The weights that the de-biased copy loads make every row wait for all before it: one slice and a
     // short ring.  Against eight rows of two slices and eight waves, rows on lines: 64 x 11,689,511 with the copy
-    // 1,791 -> 1,713 us, without 1,127 -> 1,070; 256 x 3,000,001 without 1,228 -> 1,185.
+    // 1,791 -> 1,713 us, without 1,127 -> 1,070; 128 x 25,557,032 without 4,247 -> 4,346, so many rows keep them.
     constexpr WalkShape walk(int n, int64_t, bool) const
     {
         if (zout) return WalkShape{1, ring_for(n), 8, 2};
-        return n <= 256 ? WalkShape{2, n <= 32 ? 4 : 2, 2, 2} : kWalk;
+        return n <= 64 ? WalkShape{2, n <= 32 ? 4 : 2, 2, 2} : kWalk;
     }
     const float *xin;
     float *xout;

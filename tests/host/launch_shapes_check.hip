@@ -34,6 +34,7 @@ static_assert(is(shape<MeanOp<4>>(16, 11689511, 11689536), 1, 4, 2, 2) && is(sha
 static_assert(is(shape<MeanOp<4>>(8, 11689511, 11689512), 1, 2, 2, 2) && is(shape<MeanOp<4>>(64, 11689511, 11689536), 2, 2, 8, 2));
 static_assert(is(shape<HierFusedOp<8>>(8, 11689511, 11689536), 1, 2, 2, 2) && is(shape<HierFusedOp<8>>(8, 11689511, 11689512), 1, 2, 8, 2));
 static_assert(is(shape<MeanOp<8>>(4, 900001, 900032), 1, 4, 8, 2) && is(shape<FusedOp>(32, 900001, 900032), 1, 8, 8, 2));
+static_assert(is(shape<PushOp>(64, 25557032, 25557056), 2, 2, 2, 2) && is(shape<PushOp>(128, 25557032, 25557056), 2, 8, 8, 2));
 static_assert(is(shape<MeanOp<16>>(4, 11689511, 11689536), 1, 2, 8, 2) && is(shape<Row16Op<false, 4>>(16, 11689511, 11689536), 1, 2, 8, 2));
 
 // Plain rows: eight rows in flight beside many rows, or where tiles are few.
