@@ -99,3 +99,61 @@ def test_tables_and_vectors_are_checked():
     refuses(cx.cx_pushsum_mix, mat(), mat(), torch.ones(W - 1), torch.ones(W), None, P, 1, match="w_in")
     refuses(cx.cx_pushsum_mix, mat(), mat(), torch.ones(W), torch.ones(W, dtype=torch.float64), None, P, 1, match="w_out")
     refuses(cx.cx_copy_baseline, torch.zeros(64), torch.zeros(32), match="dst")
+
+
+class OnDevice:
+    """A host tensor that says it lives on a GPU: the argument checks ask a tensor for nothing but its properties."""
+    is_cuda = True
+
+    def __init__(self, tensor, device="cuda:0"):
+        self.tensor, self.device = tensor, torch.device(device)
+
+    def __getattr__(self, name):
+        return getattr(self.tensor, name)
+
+
+def vec(n=W, dtype=torch.float32):
+    return torch.ones(n, dtype=dtype)
+
+
+@pytest.mark.parametrize("kind", ["gossip", "hier", "fused", "hiersgd", "gossip16", "fused16", "pushsum"])
+def test_the_short_way_through_the_checks_accepts_only_what_the_full_checks_accept(kind):
+    """_ready() answers for the usual tensors: what it accepts the full checks accept with the same geometry, and of the
+    correct call it is not silent; every call with one odd argument gets the full checks' answer."""
+    cx.lib()
+    size = 2 if kind.endswith("16") else 4
+    x = lambda: mat(dtype=torch.bfloat16 if size == 2 else torch.float32)
+    G_of = G if kind.startswith("hier") else 1
+    mats = {"gossip": [x], "hier": [x], "gossip16": [x], "fused": [x, mat, mat, x], "fused16": [x, mat, mat, x],
+            "hiersgd": [x, lambda: mat(W // G), lambda: mat(W // G), x], "pushsum": [x, x]}[kind]
+    rows_of = [1, G_of, G_of, 1] if len(mats) == 4 else [1] * len(mats)
+    sizes = [size, 4, 4, size] if len(mats) == 4 else [size] * len(mats)
+    so, pe = tables(W // G_of)
+    good = [x()] + [m() for m in mats] + ([vec(), vec()] if kind == "pushsum" else [so, pe])
+    odd = [mat(), mat(ld=P), mat(rows=W - 1), mat(rows=1), mat(rows=W // G), mat(ld=LD + 1)[:, :LD], mat(ld=2 * LD)[:, ::2],
+           mat(ld=LD + 8)[:, 8:], torch.zeros((W + 1) * LD).as_strided((W, LD + 1), (LD, 1)), torch.zeros(W, 2, LD),
+           torch.zeros(W * LD), mat(dtype=torch.int32), mat(dtype=torch.float64), mat(dtype=torch.bfloat16),
+           mat(dtype=torch.int16), vec(), vec(W + 3), vec(W - 1), vec(2 * W)[::2], vec(dtype=torch.float64),
+           vec(dtype=torch.int32), so, so[:1], so.to(torch.int32), so.repeat(2)[::2], pe, pe[:, 1:], pe.to(torch.int64), pe.t(),
+           pe.reshape(-1), pe.to(torch.float32), None]
+
+    def ask(check, args, cols, groups, elsewhere=None):
+        t = [a if a is None else OnDevice(a, "cuda:1" if i == elsewhere else "cuda:0") for i, a in enumerate(args)]
+        m = tuple((f"m{i}", a, r, s) for i, (a, r, s) in enumerate(zip(t[1:], rows_of, sizes)))
+        tail = t[1 + len(m):]
+        try:
+            if kind == "pushsum":
+                return check(t[0], size, m, cols, groups, None, None, (("w_in", tail[0]), ("w_out", tail[1])))
+            return check(t[0], size, m, cols, groups, tail[0], tail[1], ())
+        except (ValueError, AttributeError):
+            return "refused"
+
+    assert ask(cx._ready, good, P, G_of) == ask(cx._full_checks, good, P, G_of) == (W, LD, 1 if kind == "pushsum" else S)
+    calls = [(good, cols, groups, None) for cols in (0, 1, LD, LD + 1) for groups in (G_of, 0, -1, 3, W, 2 * W)]
+    calls += [(good, P, G_of, i) for i in range(len(good))]
+    calls += [(good[:i] + [bad] + good[i + 1:], P, G_of, None) for i in range(len(good)) for bad in odd]
+    for args, cols, groups, elsewhere in calls:
+        if args[0] is None or (groups != G_of and kind == "hiersgd" and groups < 1):
+            continue
+        short = ask(cx._ready, args, cols, groups, elsewhere)
+        assert short in (None, "refused") or short == ask(cx._full_checks, args, cols, groups, elsewhere)
