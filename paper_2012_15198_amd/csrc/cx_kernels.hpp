@@ -8,7 +8,7 @@
 // Mixing is independent per column and every element has to be read once and written once
 // (8 B per worker-parameter; 20 B with the fused optimizer), so the whole path is bound by
 // HBM bandwidth.  A lane always handles 16-byte column slices (4 fp32 or 8 bfloat16), a
-// wavefront 1 KB of contiguous columns per memory instruction.  Two kernels serve the same
+// wavefront 1 KB of contiguous columns per memory instruction.  Three kernels serve the same
 // arithmetic:
 //
 //  gather_kernel (output buffer != input buffer) -- the fast one.
@@ -38,7 +38,9 @@
 //     lock-step variant) in LDS from the peer table; a table that is not a permutation is
 //     replaced by the identity, so no row index can leave [0, n).
 //
-//  Both: tiles wholly inside one segment take the 16-byte vector path.  In the at most S+1 tiles that a
+//  parts_kernel (in place, few tiles) -- the same walk, with the rows of a tile split over the wavefronts of a workgroup.
+//
+//  All: tiles wholly inside one segment take the 16-byte vector path.  In the at most S+1 tiles that a
 //  segment boundary or the ragged row end crosses, every piece between two boundaries loads the slices it
 //  meets and stores under a mask of elements: piece after piece by the tile's wavefront in gather_kernel, one
 //  wavefront for each piece in mix_kernel.  Columns [P, ld) are neither read nor written.  Row operators
@@ -81,14 +83,20 @@ struct BlockSync {
 // with the boundary pieces below; fused step 256 x 300,007: 806 -> 573 us.)  The schedule's words are read from
 // LDS one step ahead and kept until their row arrives.  The last turns, up to 2 * D steps, decide step by step;
 // walks of at most 2 * D rows consist of them.
-template <class Op, int U, int D, TileMode MODE, bool NT, bool SYNC = false>
+struct NoEnds {
+    static constexpr bool kPart = false, kAhead = false;
+    __device__ __forceinline__ bool has_head() const { return false; }
+};
+template <class Op, int U, int D, TileMode MODE, bool NT, class Ends = NoEnds, bool SYNC = false>
 __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool skip_mix,
-                                     int64_t off, const unsigned (&mask)[U])
+                                     int64_t off, const unsigned (&mask)[U], const Ends &ends = Ends{})
 {
+    constexpr bool PART = Ends::kPart;
     using WorkT = typename Op::template Work<U>;
     typename Op::template Raw<U> slot[D];
-    WorkT cur, first;
+    WorkT cur, first, tail;
     int e = 0, base = 0;
+    if constexpr (PART && Ends::kAhead) ends.template load<MODE, NT>(mask, first, tail);
     // Without the steady loop: the mean of groups of 16, whose registers would spill, and the shape that few long rows of
     // plain gossip take (MeanOp::walk).
     constexpr bool kSteady = !std::is_same_v<Op, MeanOp<16>> && !(std::is_same_v<Op, MeanOp<1>> && U == 1 && D == 2);
@@ -110,12 +118,13 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
             op.template issue<U, MODE, NT>(word[j] & kRowMask, off, mask, slot[j]);
         }
         int ahead = sched[D];
+        if constexpr (PART && !Ends::kAhead) ends.template load<MODE, NT>(mask, first, tail);
         e = word[0];
         op.template finish<U, MODE, NT>(e & kRowMask, off, mask, slot[0], cur);
         word[0] = uniform(ahead);
         op.template issue<U, MODE, NT>(word[0] & kRowMask, off, mask, slot[0]);
         ahead = sched[D + 1];
-        first = cur;
+        if (!ends.has_head()) first = cur;
         for (; base + 2 * D < n; base += D) {
             static_for<0, D>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
@@ -135,6 +144,7 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
 #pragma unroll
         for (int j = 0; j < D; ++j)
             if (j < n) op.template issue<U, MODE, NT>(uniform(sched[j]) & kRowMask, off, mask, slot[j]);
+        if constexpr (PART && !Ends::kAhead) ends.template load<MODE, NT>(mask, first, tail);
         e = uniform(sched[0]);
         op.template finish<U, MODE, NT>(e & kRowMask, off, mask, slot[0], cur);
         if (D < n) op.template issue<U, MODE, NT>(uniform(sched[D]) & kRowMask, off, mask, slot[0]);
@@ -142,7 +152,7 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
             op.template store<U, MODE, NT>(e & kRowMask, off, mask, cur);
             return;
         }
-        first = cur;
+        if (!ends.has_head()) first = cur;
     }
     for (; base < n; base += D) {
         static_for<0, D>([&](auto jc) {
@@ -159,6 +169,8 @@ __device__ __forceinline__ void walk(const Op &op, const int *sched, int n, bool
                     if (k + 1 + D < n)
                         op.template issue<U, MODE, NT>(uniform(sched[k + 1 + D]) & kRowMask, off, mask,
                                                        slot[kNextSlot]);
+                } else if constexpr (PART) {
+                    nx = first = tail;
                 }
                 step(nx, e1);
             }
@@ -206,7 +218,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
 #pragma unroll
             for (int u = 0; u < U; ++u) mask[u] = (1u << kSliceCols) - 1u;
             const int64_t first = g0 + static_cast<int64_t>(wave) * kTileCols;
-            walk<Op, U, D, kFull, NT, true>(op, sched, n, skip_mix != 0, column_of<Op>(first, lane, 0, 0), mask);
+            walk<Op, U, D, kFull, NT, NoEnds, true>(op, sched, n, skip_mix != 0, column_of<Op>(first, lane, 0, 0), mask);
             return;
         }
     }
@@ -256,6 +268,122 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
         for (int u = 0; u < U; ++u)
             mask[u] = slice_mask(off + u * (kWave * kSliceCols), kSliceCols, wanted_from(b, place, U), e);
         walk<Op, U, D, SHORT ? kShortRow : kBoundary, NT>(op, sched, n, skip_mix != 0, off, mask);
+    }
+}
+
+// ---------------------------------------------------------------------------------
+// In place, the rows of a tile split over wavefronts.  A wavefront that visits every row of its tile one after the
+// other makes a launch last as long as one walk, whatever the tile's width: 1,024 rows eight at a time are 128 memory
+// latencies.  Here `parts` wavefronts of a workgroup share a tile and its schedule, which they build together, and
+// take a part of the rows each (schedule_part); `tiles` adjacent tiles make up the workgroup.  The rows of a part that
+// other parts overwrite are read ahead (PartEnds), and no wavefront stores before all of the workgroup have theirs.
+// In place, us, mix_kernel / this: fp32 gossip on 512 x 3,001 118 / 21, on 256 x 30,011 61 / 20; bf16 gossip on
+// 355 x 50,356 123 / 31; binary16 optimizer step on 256 x 30,011 232 / 50; push-sum with the copy on 826 x 79,896 628 / 249;
+// fp32 optimizer step on 256 x 300,007 364 / 344.
+// The first `pieces` workgroups serve the pieces that begin at a segment boundary inside a workgroup's columns.
+// ---------------------------------------------------------------------------------
+template <class Op, int U>
+struct PartEnds {
+    static constexpr bool kPart = true;
+    // operators with many registers behind a row turn the two rows into tiles one after the other, before the ring
+    static constexpr bool kAhead = Op::kRawPerSlice * U >= 6;
+    using WorkT = typename Op::template Work<U>;
+    const Op &op;
+    int64_t off;
+    int head_row, tail_row;                    // head_row -1: none
+    __device__ __forceinline__ bool has_head() const { return head_row >= 0; }
+    // COMMIT is false throughout: what an operator writes on arrival (v') is the owner's to write
+    template <TileMode MODE, bool NT>
+    __device__ __forceinline__ void load(const unsigned (&mask)[U], WorkT &head, WorkT &tail) const
+    {
+        typename Op::template Raw<U> raw;
+        op.template issue<U, MODE, false>(tail_row, off, mask, raw);
+        if constexpr (kAhead) {
+            op.template finish<U, MODE, NT, false>(tail_row, off, mask, raw, tail);
+            if (head_row >= 0) {
+                op.template issue<U, MODE, false>(head_row, off, mask, raw);
+                op.template finish<U, MODE, NT, false>(head_row, off, mask, raw, head);
+            }
+        } else {
+            typename Op::template Raw<U> other;
+            if (head_row >= 0) op.template issue<U, MODE, false>(head_row, off, mask, other);
+            op.template finish<U, MODE, NT, false>(tail_row, off, mask, raw, tail);
+            if (head_row >= 0) op.template finish<U, MODE, NT, false>(head_row, off, mask, other, head);
+        }
+        // the loads themselves have to be back, not only ordered: other wavefronts store to these rows next
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+};
+
+// Most wavefronts of a workgroup: sixteen leave each 128 registers.
+template <class Op, int U, int D>
+constexpr int kPartWaves = (Op::kRawPerSlice * U * (PartEnds<Op, U>::kAhead ? D + 1 : D + 2) * 4 +
+                            5 * Op::template Work<U>::kN * Op::template Work<U>::kRegs) <= 100 ? 16 : kMaxWavesPerBlock;
+
+template <class Op, int U, int D>
+__global__ __launch_bounds__((kWave * kPartWaves<Op, U, D>)) void parts_kernel(
+    Op op, int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
+    const int32_t *__restrict__ peers, int shift, int parts, unsigned pieces)
+{
+    extern __shared__ int lds[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform(threadIdx.x >> 6);
+    const int tiles = static_cast<int>(blockDim.x >> 6) / parts;
+    constexpr int kSliceCols = Op::kElems;
+    constexpr int kTileCols = kWave * kSliceCols * U;
+    const int64_t block_cols = static_cast<int64_t>(kTileCols) * tiles;
+    auto bound = [&](int s) -> int64_t {                   // where segment s begins, inside [0, P]
+        if (s <= 0) return 0;
+        if (s >= S) return P;
+        const int64_t b = seg_off[s];
+        return b < 0 ? 0 : (b > P ? P : b);
+    };
+    // the columns [b, e) of one segment that this workgroup serves: the returns are its waves' all together
+    int s;
+    int64_t b, c0;
+    if (blockIdx.x < pieces) {
+        s = static_cast<int>(blockIdx.x) + 1;
+        b = bound(s);
+        c0 = b / block_cols * block_cols;
+        if (b == c0) return;                               // begins with a workgroup's columns: that one's
+    } else {
+        b = c0 = (static_cast<int64_t>(blockIdx.x) - pieces) * block_cols;
+        int lo = 1, hi = S;                                // segment of c0: number of interior boundaries <= c0
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (seg_off[mid] <= c0) lo = mid + 1; else hi = mid;
+        }
+        s = lo - 1;
+    }
+    int64_t e = bound(s + 1);
+    if (e > c0 + block_cols) e = c0 + block_cols;
+    if (b >= e) return;
+    build_schedule(lds, n, static_cast<int>(threadIdx.x), static_cast<int>(blockDim.x), peers, s, shift, BlockSync{});
+    const SchedulePart part = schedule_part(lds, n, wave / tiles, parts, lane, kWave,
+                                            [](bool c) { return __builtin_amdgcn_ballot_w64(c); });
+    c0 += static_cast<int64_t>(wave % tiles) * kTileCols;
+    if (b < c0) b = c0;
+    if (e > c0 + kTileCols) e = c0 + kTileCols;
+    const int first = uniform(part.begin), rows = uniform(part.end) - first;
+    if (rows == 0 || b >= e) {
+        __syncthreads();                                   // PartEnds::load of the others
+        return;
+    }
+    const int64_t place = column_of<Op>(c0, lane, 0, 0);
+    const int64_t off = place - row_end_slide(P, c0, place, U, kTileCols, kSliceCols);
+    const PartEnds<Op, U> ends{op, off, uniform(part.head), uniform(part.tail)};
+    const int *sched = lds + n + first;
+    unsigned mask[U];
+    if (e - b == kTileCols) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) mask[u] = (1u << kSliceCols) - 1u;
+        walk<Op, U, D, kFull, true>(op, sched, rows, false, off, mask, ends);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            mask[u] = slice_mask(off + u * (kWave * kSliceCols), kSliceCols, wanted_from(b, place, U), e);
+        walk<Op, U, D, kBoundary, true>(op, sched, rows, false, off, mask, ends);
     }
 }
 

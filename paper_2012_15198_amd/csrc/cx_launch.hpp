@@ -390,6 +390,117 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     }
 }
 
+// ---------------------------------------------------------------------------------
+// In place with the rows of a tile split over wavefronts (parts_kernel), or parts == 0: mix_kernel.
+//
+// Rows of few tiles want as many wavefronts as there can be: the smallest power of two of parts that gives kPartJobs of
+// them.  Longer ones gain from two parts, since the two rows that a part reads ahead come all at once, with two slices per
+// lane where the registers allow it; there the launch has few rounds of workgroups, and mix_kernel stays where the last
+// one would leave too many CUs idle.  Times in place, us, mix_kernel / parts, every pass on the next of several matrices:
+//   below kPartLong tiles (n >= 4): fp32 gossip on 512 x 3,001 118 / 21; fewer than four rows have nothing to split;
+//   below kPartMid: 8 rows (bf16 gossip on 100 x 250,007 56 / 32), 16 where fp32 rows carry groups or momentum (fp32
+//     mean of groups of 2 on 16 x 350,003 11.7 / 14.2), 32 for groups on the longer half (of 4 on 80 x 250,007 33 / 36);
+//   16-bit rows up to kPartWide16 tiles (bf16 gossip on 70 x 2,100,003 0.93, 3,000,017 0.99, 4,000,037 1.04 of
+//     mix_kernel's time), kPartVeryLong with four or five registers a row and slice (binary16 optimizer step on
+//     33 x 1,500,003 0.89, 8,000,021 1.05), half of that with two or three (groups of 2 of 70 x 1,100,003 0.91, 1,500,003 1.03);
+//   fp32 rows from 16 on: gossip and the optimizer step up to 2 * kPartVeryLong tiles (33 x 1,100,003 0.91 and 0.87,
+//     9,000,011 gossip 1.03), push-sum with the copy up to kPartWide16 (0.91, 2,100,003 without gain), groups in
+//     workgroups of one tile of two slices (of 4 of 33 x 1,100,003 0.90; two and four tiles 1.00 to 1.07, one slice up to 1.12);
+//   up to 8 very long fp32 rows, which mix_kernel's two waves serve badly: gossip where they begin inside lines
+//     (8 x 6,000,011 0.84), push-sum without the copy (5 x 6,000,011 0.78).
+// ---------------------------------------------------------------------------------
+struct PartShape {
+    int U, D, parts, tiles;
+};
+enum class Push { kNo, kPlain, kWithCopy };
+template <class Op> constexpr Push push_kind(const Op &) { return Push::kNo; }
+constexpr Push push_kind(const PushOp &op) { return op.zout ? Push::kWithCopy : Push::kPlain; }
+
+template <class Op>
+struct PartRing {                       // the two rings that are built: short rows, long rows
+    static constexpr bool kBuilt = !LdsStaged<Op>::value && Op::kRawPerSlice < 16;          // groups of 16 keep mix_kernel
+    static constexpr int kLongU = fits<Op, 2, 2>() ? 2 : 1, kLongD = std::is_same_v<Op, FusedOp> ? 4 : 2;
+    static constexpr int kShortD = Op::kRawPerSlice == 1 ? 4 : 2;
+};
+
+constexpr int64_t kPartJobs = 1024, kCUs = 256;           // wavefronts
+constexpr int64_t kPartLong = 400, kPartMid = 1000, kPartVeryLong = 4096, kPartWide16 = 5000;   // tiles of one slice per lane
+template <class Op>
+constexpr PartShape part_shape(const Op &op, int n, int64_t P, int S)
+{
+    using Ring = PartRing<Op>;
+    constexpr PartShape kNone{0, 0, 0, 0};
+    constexpr bool kWideRows = Op::kElems == 4, kPlainRows = Op::kRawPerSlice == 1;
+    constexpr bool kGroups = kWideRows && !kPlainRows && !std::is_same_v<Op, FusedOp>;
+    if (!Ring::kBuilt || n < 4 || P < Op::kElems) return kNone;
+    const int64_t tiles = (P + kWave * Op::kElems - 1) / (kWave * Op::kElems);
+    const bool long_rows = tiles >= kPartLong;
+    if (tiles >= kPartMid) {
+        if (kWideRows) {
+            const Push push = push_kind(op);
+            const bool whole_lines = op.ld * (16 / Op::kElems) % 128 == 0;
+            const bool few = kPlainRows && n <= 8 && tiles >= 4 * kPartVeryLong &&
+                             (push == Push::kNo ? !whole_lines : push == Push::kPlain);
+            const int64_t most = push == Push::kPlain ? 0 : push == Push::kWithCopy || kGroups ? kPartWide16 : 2 * kPartVeryLong;
+            if (!few && (n < 16 || tiles >= most)) return kNone;
+        } else if (n < 8 || tiles >= (kPlainRows || Op::kRawPerSlice > 5 ? kPartWide16 : Op::kRawPerSlice > 3 ? kPartVeryLong : kPartVeryLong / 2)) {
+            return kNone;
+        }
+    } else if (long_rows && n < (!kWideRows || kPlainRows ? 8 : kGroups && tiles >= kPartMid / 2 ? 32 : 16)) {
+        return kNone;
+    }
+    PartShape s{long_rows ? Ring::kLongU : 1, long_rows ? Ring::kLongD : Ring::kShortD, 2, 1};
+    const int limit = long_rows ? kPartWaves<Op, Ring::kLongU, Ring::kLongD> : kPartWaves<Op, 1, Ring::kShortD>;
+    const int64_t jobs = (tiles + s.U - 1) / s.U;
+    while (s.parts * jobs < kPartJobs && s.parts < limit && 2 * s.parts <= n) s.parts *= 2;
+    // As many adjacent tiles a workgroup as leave the last round of workgroups, one a CU, nearly as full as the others
+    // (2 parts x 4 tiles, 258 workgroups: fp32 mean of groups of 2 on 24 x 515,003 28.6 us, mix_kernel 20.0).  Beside
+    // many rows one round of the widest is best whatever it leaves idle: fp32 optimizer step on 256 x 300,007, 154
+    // workgroups of 4 tiles 340 us, 593 of one tile 362.
+    int most_full = 0;
+    const int widest = s.parts >= kMaxWavesPerBlock ? 1 : (n < 8 ? 4 : kMaxWavesPerBlock) / s.parts;
+    for (int t = widest; t >= 1 && most_full < 90; t /= 2) {
+        const int64_t blocks = (jobs + t - 1) / t + S - 1, rounds = (blocks + kCUs - 1) / kCUs;
+        const int full = n >= 64 && long_rows && rounds == 1 ? 100 : static_cast<int>(100 * blocks / (rounds * kCUs));
+        if (full > most_full) {
+            s.tiles = t;
+            most_full = full;
+        }
+    }
+    if (tiles >= kPartMid && (most_full < 88 || (kGroups && (s.tiles > 1 || s.U == 1)))) return kNone;
+    return s;
+}
+
+template <class Op>
+bool try_parts(const Op &op, const MixArgs &a)
+{
+    if constexpr (!PartRing<Op>::kBuilt) {
+        return false;
+    } else {
+        // launch parameters of the in-place kernel ask for mix_kernel's shapes
+        for (const int key : {0, 1, 2, 3, 4, 9})
+            if (cx_get_tuning(key) != -1) return false;
+        if (a.skip_mix) return false;
+        const PartShape s = part_shape(op, a.n, a.P, a.S);
+        if (s.parts == 0) return false;
+        const int64_t block_cols = static_cast<int64_t>(kWave) * Op::kElems * s.U * s.tiles;
+        const int64_t blocks = (a.P + block_cols - 1) / block_cols + a.S - 1;
+        if (blocks > 0x7fffffffLL) return false;
+        const int waves = s.parts * s.tiles;
+        const size_t schedule = (sizeof(int) * kScheduleWords(a.n) + 15) / 16 * 16;
+        const size_t lds = schedule + static_cast<size_t>(StageBytes<Op>::value) * waves;
+        const Op staged = with_stage_base(op, schedule);
+        const auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kWave * waves), lds, a.stream, staged, a.n, a.P,
+                               a.S, a.seg_off, a.peers, a.shift, s.parts, static_cast<unsigned>(a.S - 1));
+        };
+        using Ring = PartRing<Op>;
+        if (s.U == Ring::kLongU && s.D == Ring::kLongD) launch(parts_kernel<Op, Ring::kLongU, Ring::kLongD>);
+        else launch(parts_kernel<Op, 1, Ring::kShortD>);
+        return true;
+    }
+}
+
 template <class Op>
 int launch_mix(const Op &op, const MixArgs &a)
 {
@@ -417,6 +528,7 @@ int launch_mix(const Op &op, const MixArgs &a)
             try_gather<Op, 4>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status))
             return status;
     }
+    if (try_parts<Op>(op, a)) return hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
     Launch l = pick_launch(walk_shape(op, a.n, a.P));
     if (a.P < kSliceLanes * l.U) l.U = 1;
     if (a.P < Op::kElems) l.D = 2;

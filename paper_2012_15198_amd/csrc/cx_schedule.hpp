@@ -98,4 +98,36 @@ CX_SCHED_FN void build_schedule(int *work, int n, int tid, int nthreads, const i
     group.sync();
 }
 
+// ---------------------------------------------------------------------------------
+// A schedule walked in parts, each by a wavefront of its own and all of them at once: part q of Q takes the positions
+// [n*q/Q, n*(q+1)/Q).  In place, a part's walk needs two rows that another part overwrites, and reads them before any
+// part stores:
+//   tail  the row that the last position averages with (the next part's first row, or where a cycle closes there its
+//         first row, which may lie in an earlier part);
+//   head  the first row of the cycle that was open when the part began, where that cycle closes inside the part before
+//         the last position; -1 otherwise.  Every cycle that opens inside the part finds its first row in registers.
+// `ballot(c)` collects one bit a lane of the `lanes` that call together.
+// ---------------------------------------------------------------------------------
+struct SchedulePart {
+    int begin, end, head, tail;
+};
+
+template <class Ballot>
+CX_SCHED_FN SchedulePart schedule_part(const int *work, int n, int part, int parts, int lane, int lanes, Ballot ballot)
+{
+    const int *tab = work, *sched = work + n;
+    SchedulePart p{n * part / parts, n * (part + 1) / parts, -1, -1};
+    if (p.begin == p.end) return p;
+    p.tail = tab[sched[p.end - 1] & kRowMask];
+    if (p.begin == 0 || (sched[p.begin - 1] & kLastBit)) return p;
+    for (int k = p.begin; k < p.end - 1; k += lanes) {
+        const uint64_t closes = ballot(k + lane < p.end - 1 && (sched[k + lane] & kLastBit));
+        if (closes) {
+            p.head = tab[sched[k + __builtin_ctzll(closes)] & kRowMask];
+            break;
+        }
+    }
+    return p;
+}
+
 #endif  // CX_SCHEDULE_HPP

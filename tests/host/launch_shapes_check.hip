@@ -42,4 +42,29 @@ static_assert(is(shape<Row16Op<false>>(256, 3000003, 3000008), 1, 8, 8, 2) && is
               is(shape<Row16Op<false>>(16, 3000003, 3000008), 1, 4, 8, 2) && is(shape<Row16Op<false>>(16, 100003, 100008), 1, 8, 1, 16) &&
               is(shape<MeanOp<1>>(16, 100003, 100032), 1, 8, 2, 8));
 
+// In place with a tile's rows split over wavefronts: as many parts as make kPartJobs wavefronts and the rows and the
+// registers allow, as many tiles a workgroup as fill the last round of workgroups; mix_kernel elsewhere.
+template <class Op>
+constexpr bool parts_are(int n, int64_t P, int S, int U, int D, int parts, int tiles, int64_t ld = 0, Op op = Op{})
+{
+    op.ld = ld ? ld : P + 4;
+    const PartShape s = part_shape(op, n, P, S);
+    return s.parts == parts && (parts == 0 || (s.U == U && s.D == D && s.tiles == tiles));
+}
+template <class Op>
+constexpr bool no_parts(int n, int64_t P, int S, int64_t ld = 0)
+{
+    return parts_are<Op>(n, P, S, 0, 0, 0, 0, ld);
+}
+static_assert(parts_are<MeanOp<1>>(512, 3001, 4, 1, 4, 16, 1) && parts_are<MeanOp<1>>(9, 3001, 4, 1, 4, 8, 1) &&
+              parts_are<FusedOp>(4, 2000, 4, 1, 2, 4, 1) && no_parts<FusedOp>(3, 2000, 4));
+static_assert(parts_are<MeanOp<1>>(16, 256 * 399, 1, 1, 4, 4, 2) && parts_are<MeanOp<1>>(16, 256 * 399 + 1, 1, 2, 2, 8, 1) &&
+              no_parts<MeanOp<1>>(7, 256 * 399 + 1, 1) && no_parts<FusedOp>(15, 256 * 399 + 1, 1));
+static_assert(parts_are<FusedOp>(256, 300007, 8, 2, 4, 2, 4) && no_parts<MeanOp<4>>(33, 515003, 7) && no_parts<MeanOp<1>>(33, 800003, 7) &&
+              parts_are<MeanOp<4>>(33, 1100003, 7, 2, 2, 2, 1) && parts_are<MeanOp<1>>(33, 515003, 7, 2, 2, 2, 2));
+static_assert(parts_are<MeanOp<1>>(8, 6000011, 7, 2, 2, 2, 4) && no_parts<MeanOp<1>>(8, 6000011, 7, 6000032) && no_parts<MeanOp<1>>(9, 6000011, 7));
+static_assert(parts_are<Row16Op<true, 4>>(16, 400009, 7, 1, 2, 2, 4) && no_parts<Row16Op<true, 4>>(16, 4000009, 7) &&
+              parts_are<Row16Op<true, 8>>(16, 2100003, 7, 1, 2, 2, 1) && no_parts<Row16Op<false>>(32, 25557032, 8));
+static_assert(no_parts<MeanOp<16>>(32, 3001, 4) && kPartWaves<MeanOp<1>, 1, 4> == 16 && kPartWaves<FusedOp, 2, 4> == 8);
+
 }  // namespace

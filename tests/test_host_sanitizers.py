@@ -4,6 +4,7 @@ code the kernels share with the host, and the oracle.  CPU only; every build goe
   * tests/host/schedule_check.cpp: build_schedule (csrc/cx_schedule.hpp) run by a group of real threads
     against a serial cycle walk -- under ThreadSanitizer, where a missing group.sync() is a data race,
     and under AddressSanitizer + UBSan at the largest row count;
+  * tests/host/parts_check.cpp: schedule_part (csrc/cx_schedule.hpp), the rows of a segment mixed in place by parts;
   * tests/host/host_half_check.cpp: csrc/cx_host.cpp and oracle/cx_oracle.c in one ASan + UBSan program:
     topologies of both compared for every mode, the table checkers, every oracle function on exact-size
     heap buffers;
@@ -46,6 +47,12 @@ def test_cycle_schedule_under_address_sanitizer_at_the_maximum_row_count(tmp_pat
     run(["g++", "-std=c++17", *SAN, "-I", CSRC, os.path.join(HOST, "schedule_check.cpp"), "-o", str(exe), "-lpthread"])
     assert run([str(exe), "7", "1024"], env=ENV).startswith("ok")
     assert run([str(exe), "1", "1024"], env=ENV).startswith("ok")
+
+
+def test_rows_mixed_in_place_by_parts(tmp_path):
+    exe = tmp_path / "parts"
+    run(["g++", "-std=c++17", *SAN, "-Wall", "-Wextra", "-I", CSRC, os.path.join(HOST, "parts_check.cpp"), "-o", str(exe)])
+    assert run([str(exe)], env=ENV).startswith("ok")
 
 
 def test_boundary_tiles_read_no_column_beyond_the_row(tmp_path):
