@@ -20,10 +20,11 @@
 //     so a block's partner is the next block's own row).
 //   * Long contiguous row visits per XCD keep the DRAM row buffers busy, which a kernel
 //     whose waves each wander over all rows cannot do as well.
-//   * order_kernel, a few microseconds ahead of it, derives the row order from the
+//   * segment_order_kernel, a few microseconds ahead of it, derives the row order from the
 //     device-resident peer table into library-owned device memory (no allocation): one word
-//     per (cluster, position) with the row, its partner and a "one segment covers this
-//     cluster" bit, so almost every workgroup starts its loads after one scalar load.
+//     per (segment, position) with the row and its partner, and one per tile with its segment and
+//     a "one segment covers this tile" bit, so almost every workgroup starts its loads after two
+//     scalar loads.  (order_kernel: one word per (cluster, position), for rows too long for that.)
 //     Workgroups are many and small (one slice per lane for plain gossip): their count of
 //     instructions, not only their bytes, decides the rate.
 //
@@ -392,7 +393,8 @@ __global__ __launch_bounds__((kWave * kPartWaves<Op, U, D>)) void parts_kernel(
 // library owns (no allocation at run time), written by order_kernel and read by gather_kernel
 // through a pointer both receive as an argument.
 //
-// Entry (cluster, k): the k-th row the cluster's workgroups visit, that row's partner in the
+// Two layouts, by the tile (segment_order_kernel) and by the cluster (order_kernel).  By the cluster,
+// entry (cluster, k): the k-th row the cluster's workgroups visit, that row's partner in the
 // segment of the cluster's first column, and a flag saying that this segment covers every
 // column of the cluster (so a whole tile of the cluster needs no segment lookup at all).
 //
@@ -457,6 +459,38 @@ __global__ __launch_bounds__(256) void order_kernel(int n, int64_t P, int S,
     }
 }
 
+// The order by the tile: n words for each segment, its row order, and behind all S of them one word for each tile, the
+// segment of its first column and whether that one covers the tile (one segment: n words).  A cluster that several
+// segments meet walks every tile in its own segment's order; in the order of the cluster's first column the partners of
+// the others miss L2 and their tiles look the segment up.  Against order_kernel's, us: fp32 gossip on 512 x 100,003,
+// 16 ragged segments 111 / 98, on 512 x 312,501 302 / 253, on 128 x 2,500,001 499 / 449; fp32 optimizer step on
+// 512 x 312,501 813 / 650; bf16 gossip on 512 x 625,001 347 / 271; 32 x 25,557,032 in 8 segments 1,085 / 1,084.
+constexpr unsigned kTileOneSegment = 1u << 31;
+
+__global__ __launch_bounds__(256) void segment_order_kernel(int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
+                                                            const int32_t *__restrict__ peers, int shift, int tile_shift,
+                                                            unsigned *__restrict__ order)
+{
+    extern __shared__ int lds[];
+    const int *sched = lds + n;
+    const int s = blockIdx.x;
+    build_schedule(lds, n, static_cast<int>(threadIdx.x), static_cast<int>(blockDim.x), peers, s, shift, BlockSync{});
+    for (int k = threadIdx.x; k < n; k += blockDim.x) {
+        const int row = sched[k] & kRowMask;
+        order[static_cast<unsigned>(s) * n + k] = static_cast<unsigned>(row) |
+            (static_cast<unsigned>(partner_of(peers, shift, n, s, row)) << kOrderRowBits);
+    }
+    int64_t sb = (s == 0) ? 0 : seg_off[s];
+    int64_t se = (s == S - 1) ? P : seg_off[s + 1];
+    sb = sb < 0 ? 0 : (sb > P ? P : sb);
+    se = se < 0 ? 0 : (se > P ? P : se);
+    if (S == 1) return;
+    unsigned *tiles = order + static_cast<unsigned>(S) * n;
+    const int64_t tile_cols = static_cast<int64_t>(1) << tile_shift;
+    for (int64_t t = ((sb + tile_cols - 1) >> tile_shift) + threadIdx.x; (t << tile_shift) < se; t += blockDim.x)
+        tiles[t] = static_cast<unsigned>(s) | ((t + 1) << tile_shift <= se ? kTileOneSegment : 0u);
+}
+
 // The same column, but not known to the compiler as such: what is computed from it is computed again instead of
 // being kept in registers.
 __device__ __forceinline__ int64_t fresh_column(int64_t column)
@@ -485,7 +519,7 @@ template <class Op, int U, bool NT, bool SHORT = false>
 __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     Op op, int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
     const int32_t *__restrict__ peers, int shift, int skip_mix, unsigned nchunks, unsigned CL,
-    unsigned nwaves, int xcd_shift, const unsigned *__restrict__ order)
+    unsigned nwaves, int xcd_shift, const unsigned *__restrict__ order, int by_tile)
 {
     // grid: x = (chunk within cluster, xcd) with the xcd in the low bits, y = gossiping row,
     // z = cluster.  Blocks are dispatched x-fastest, so an XCD sees, for one cluster, row 0's
@@ -553,7 +587,14 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     // loads after a single scalar load.  Whatever the table holds, no access leaves the
     // matrix: rows are checked against n and the tile against P.
     if (!SHORT && order) {
-        const unsigned e = order[cluster * static_cast<unsigned>(n) + blockIdx.y];
+        unsigned at = cluster, one_segment = 0;
+        if (by_tile) {
+            const unsigned w = S > 1 ? order[static_cast<unsigned>(S * n) + chunk * nwaves + wave] : kTileOneSegment;
+            at = w & ~kTileOneSegment;
+            one_segment = w & kTileOneSegment ? kOrderOneSegment : 0u;
+            if (at >= static_cast<unsigned>(S)) at = 0;
+        }
+        const unsigned e = order[at * static_cast<unsigned>(n) + blockIdx.y] | one_segment;
         const int r = static_cast<int>(e & kOrderRowField);
         const int q = static_cast<int>((e >> kOrderRowBits) & kOrderRowField);
         if (r < n) row = r;

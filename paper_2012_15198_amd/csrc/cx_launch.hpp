@@ -354,6 +354,10 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
         if (own_table) { *status = CX_ERR_SHAPE; return true; }
         ordered = false;
     }
+    // The order by the tile wherever the table holds it (order_kernel's otherwise: rows of more than about 50 M columns).
+    // The mean staged through LDS needs one row for a whole workgroup, which the order by the cluster gives.
+    const bool by_tile = ordered && !(LdsStaged<Op>::value && a.S > 1) &&
+                         static_cast<int64_t>(a.S) * a.n + (a.S > 1 ? (nchunks + 1) * waves : 0) <= order_entries;
     const dim3 grid(static_cast<unsigned>(cl * nxcd), static_cast<unsigned>(a.n),
                     static_cast<unsigned>(clusters));
     const dim3 block(kWave * waves);
@@ -363,7 +367,11 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
         order = a.order_provider();
         if (!order) { *status = CX_ERR_HIP; return true; }
     }
-    if (ordered) {
+    if (by_tile) {
+        hipLaunchKernelGGL(segment_order_kernel, dim3(a.S), dim3(256), sizeof(int) * kScheduleWords(a.n), a.stream, a.n, a.P, a.S,
+                           a.seg_off, a.peers, a.shift, __builtin_ctz(kWave * Op::kElems * U), order);
+        if (hipGetLastError() != hipSuccess) { *status = CX_ERR_HIP; return true; }
+    } else if (ordered) {
         const int64_t nclusters = clusters * nxcd;
         hipLaunchKernelGGL(order_kernel, dim3(a.S), dim3(256), sizeof(int) * kScheduleWords(a.n), a.stream, a.n,
                            a.P, a.S, a.seg_off, a.peers, a.shift, cl * chunk_cols, static_cast<int>(nclusters),
@@ -379,7 +387,8 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     const auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, glds, a.stream, staged, a.n, a.P, a.S, a.seg_off, a.peers, a.shift,
                            a.skip_mix, static_cast<unsigned>(nchunks), static_cast<unsigned>(cl),
-                           static_cast<unsigned>(waves), xcd_shift, order);
+                           static_cast<unsigned>(waves), xcd_shift, order,
+                           by_tile ? 1 : 0);
     };
     if (a.P < Op::kElems) {
         if constexpr (U == 1) launch(gather_kernel<Op, U, false, true>);
