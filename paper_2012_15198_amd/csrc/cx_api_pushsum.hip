@@ -17,9 +17,7 @@ int cx_pushsum_mix(const float *x_in, float *x_out, const float *w_in, float *w_
         if (any_overlap(z_out, x_in, bytes) || any_overlap(z_out, x_out, bytes)) return CX_ERR_ALIAS;
     }
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(pushsum_weight_kernel, dim3(1), dim3(256), 0, st, w_in, w_out, W, hop);
-    if (hipGetLastError() != hipSuccess) return CX_ERR_HIP;
-    const PushOp op{x_in, x_out, z_out, w_in, ld, W, hop};
+    const PushOp op{x_in, x_out, z_out, ld, {w_in, w_out, W, hop}};
     const MixArgs a{W, P, 1, /*seg_off: unused for S == 1*/ nullptr, nullptr, hop, 0, st, x_in != x_out, 1};
     return launch_mix<PushOp>(op, a);
 }

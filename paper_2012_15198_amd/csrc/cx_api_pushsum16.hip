@@ -18,10 +18,8 @@ int pushsum16(const uint16_t *x_in, uint16_t *x_out, const float *w_in, float *w
         if (any_overlap(z_out, x_in, bytes) || any_overlap(z_out, x_out, bytes)) return CX_ERR_ALIAS;
     }
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(pushsum_weight_kernel, dim3(1), dim3(256), 0, st, w_in, w_out, W, hop);
-    if (hipGetLastError() != hipSuccess) return CX_ERR_HIP;
     using Op = Push16Op<IEEE_HALF>;
-    const Op op{{x_in, x_out, ld}, z_out, w_in, W, hop};
+    const Op op{{x_in, x_out, ld}, z_out, {w_in, w_out, W, hop}};
     const MixArgs a{W, P, 1, /*seg_off: unused for S == 1*/ nullptr, nullptr, hop, 0, st, x_in != x_out, 1};
     return launch_mix<Op>(op, a);
 }

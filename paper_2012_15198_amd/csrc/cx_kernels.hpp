@@ -190,6 +190,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
     // boundary in it.  (One wavefront per tile walked all rows again for every segment that meets the tile, one
     // walk after the other: the longest part of every launch with few tiles.)
     extern __shared__ int lds[];
+    OncePerLaunch<Op>::run(op);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int nwaves = blockDim.x >> 6;
@@ -328,6 +329,7 @@ __global__ __launch_bounds__((kWave * kPartWaves<Op, U, D>)) void parts_kernel(
     const int32_t *__restrict__ peers, int shift, int parts, unsigned pieces)
 {
     extern __shared__ int lds[];
+    OncePerLaunch<Op>::run(op);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x >> 6);
     const int tiles = static_cast<int>(blockDim.x >> 6) / parts;
@@ -527,6 +529,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     // Chunk and tile numbers fit 32 bits (checked by the host), so the block is decoded with
     // a handful of scalar instructions, and the two ways out of the grid's padding share one
     // branch: the kernel's arguments are fetched once, ahead of it.
+    OncePerLaunch<Op>::run(op);
     const int lane = threadIdx.x & (kWave - 1);
     const unsigned wave = uniform(threadIdx.x >> 6);
     const unsigned xcd = blockIdx.x & ((1u << xcd_shift) - 1u);

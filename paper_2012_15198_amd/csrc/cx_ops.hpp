@@ -363,6 +363,38 @@ struct HierFusedOp {
     }
 };
 
+// The weights of push-sum, w_out[i] = (w_in[i] + w_in[(i - hop) mod n]) * 0.5f.  The de-biasing of a row divides by its new
+// weight; the first workgroup of the launch also writes them (a launch of its own in front of the mix cost as much as
+// the mix on small matrices: 8 x 20,011 fp32 15.3 / 8.0 us.  Written beside the row's column 0 instead, in store(), the
+// branch cost the in-place walk its rows in flight: 64 x 300,007 fp32 without the copy 37 / 55).
+struct PushWeights {
+    const float *in;
+    float *out;
+    int n, hop;
+    __device__ __forceinline__ float of(int row) const
+    {
+        const int from = row >= hop ? row - hop : row - hop + n;
+        return (in[row] + in[from]) * 0.5f;
+    }
+    __device__ __forceinline__ void write_all() const
+    {
+        for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = of(i);
+    }
+};
+
+// What an operator has done once a launch, by its first workgroup.
+template <class Op, class = void>
+struct OncePerLaunch {
+    static __device__ __forceinline__ void run(const Op &) {}
+};
+template <class Op>
+struct OncePerLaunch<Op, std::void_t<decltype(std::declval<const Op &>().weights)>> {
+    static __device__ __forceinline__ void run(const Op &op)
+    {
+        if ((blockIdx.x | blockIdx.y | blockIdx.z) == 0) op.weights.write_all();
+    }
+};
+
 // Push-sum: plain rows, optional de-biased copy z = x' / w'.
 struct PushOp {
     static constexpr int kElems = 4;                       // fp32 columns per 16-byte slice
@@ -382,9 +414,8 @@ struct PushOp {
     const float *xin;
     float *xout;
     float *zout;          // may be null
-    const float *win;
     int64_t ld;
-    int n, hop;
+    PushWeights weights;
 
     template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void issue(int row, int64_t off, const unsigned (&mask)[U], Raw<U> &raw) const
@@ -402,8 +433,7 @@ struct PushOp {
         const int64_t o = static_cast<int64_t>(row) * ld + off;
         tile_store<U, MODE, NT>(xout + o, mask, t);
         if (zout) {
-            const int from = row >= hop ? row - hop : row - hop + n;
-            const float wn = (win[row] + win[from]) * 0.5f;
+            const float wn = weights.of(row);
             Tile<U> z;
 #pragma unroll
             for (int u = 0; u < U; ++u) z.v[u] = t.v[u] / wn;
@@ -411,17 +441,6 @@ struct PushOp {
         }
     }
 };
-
-// w_out[i] = (w_in[i] + w_in[(i - hop) mod n]) * 0.5f  (push-sum weights, n <= CX_MAX_ROWS): the de-biasing in
-// PushOp / Push16Op reads w_in, so the new weights are written by their own tiny launch
-[[maybe_unused]] __global__ void pushsum_weight_kernel(const float *__restrict__ w_in, float *__restrict__ w_out,
-                                                       int n, int hop)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const int from = i >= hop ? i - hop : i - hop + n;
-        w_out[i] = (w_in[i] + w_in[from]) * 0.5f;
-    }
-}
 
 }  // namespace
 

@@ -227,16 +227,14 @@ struct Push16Op : Row16Op<IEEE_HALF, 1> {
         return zout && P < (8 << 20) ? WalkShape{1, 2, 8, 2} : kWalk;
     }
     uint16_t *zout;       // may be null
-    const float *win;
-    int n, hop;
+    PushWeights weights;
 
     template <int U, TileMode MODE, bool NT>
     __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Tile<2 * U> &t) const
     {
         Base::template store<U, MODE, NT>(row, off, mask, t);
         if (zout) {
-            const int from = row >= hop ? row - hop : row - hop + n;
-            const float wn = (win[row] + win[from]) * 0.5f;
+            const float wn = weights.of(row);
             Tile<2 * U> z;
 #pragma unroll
             for (int u = 0; u < 2 * U; ++u) z.v[u] = t.v[u] / wn;
