@@ -379,7 +379,7 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
         if (hipGetLastError() != hipSuccess) { *status = CX_ERR_HIP; return true; }
     }
     int cap = cx_get_tuning(9);
-    if (cap < 0 || cap > 16) cap = Op::kGather.wgs_per_cu * full_waves / waves;   // the same waves per CU
+    if (cap < 0 || cap > 16) cap = GatherWgs<Op>::of(op) * full_waves / waves;   // the same waves per CU
     size_t glds = lds_reservation(cap);
     if (U == 1 && staged_shape<Op>(waves) && glds < LdsStaged<Op>::bytes) glds = LdsStaged<Op>::bytes;
     if (glds < static_cast<size_t>(StageBytes<Op>::value) * waves) glds = static_cast<size_t>(StageBytes<Op>::value) * waves;
