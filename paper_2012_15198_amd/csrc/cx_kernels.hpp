@@ -24,7 +24,8 @@
 //     device-resident peer table into library-owned device memory (no allocation): one word
 //     per (segment, position) with the row and its partner, and one per tile with its segment and
 //     a "one segment covers this tile" bit, so almost every workgroup starts its loads after two
-//     scalar loads.  (order_kernel: one word per (cluster, position), for rows too long for that.)
+//     scalar loads; or order_kernel, where clusters are many beside the segments' edges: one word
+//     per (cluster, position) with the row, its partner and that bit, and one scalar load.
 //     Workgroups are many and small (one slice per lane for plain gossip): their count of
 //     instructions, not only their bytes, decides the rate.
 //
@@ -392,7 +393,7 @@ __global__ __launch_bounds__((kWave * kPartWaves<Op, U, D>)) void parts_kernel(
 
 // ---------------------------------------------------------------------------------
 // Row order of the out-of-place path: a table of 32-bit words in device memory that the
-// library owns (no allocation at run time), written by order_kernel and read by gather_kernel
+// library owns (no allocation at run time), written by order_kernel or segment_order_kernel and read by gather_kernel
 // through a pointer both receive as an argument.
 //
 // Two layouts, by the tile (segment_order_kernel) and by the cluster (order_kernel).  By the cluster,
@@ -466,7 +467,7 @@ __global__ __launch_bounds__(256) void order_kernel(int n, int64_t P, int S,
 // segments meet walks every tile in its own segment's order; in the order of the cluster's first column the partners of
 // the others miss L2 and their tiles look the segment up.  Against order_kernel's, us: fp32 gossip on 512 x 100,003,
 // 16 ragged segments 111 / 98, on 512 x 312,501 302 / 253, on 128 x 2,500,001 499 / 449; fp32 optimizer step on
-// 512 x 312,501 813 / 650; bf16 gossip on 512 x 625,001 347 / 271; 32 x 25,557,032 in 8 segments 1,085 / 1,084.
+// 512 x 312,501 813 / 650; bf16 gossip on 512 x 625,001 347 / 271.
 constexpr unsigned kTileOneSegment = 1u << 31;
 
 __global__ __launch_bounds__(256) void segment_order_kernel(int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
@@ -585,9 +586,9 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
 
     // y is the position in the cluster's row order: with the order kernel's table, rows follow
     // the permutation cycles, so this block's partner is the next block's own row (fresh in L2).
-    // Fast path, almost every tile: the table entry also names the partner and says that one
-    // segment covers the cluster, so a tile that does not hang over the row end starts all its
-    // loads after a single scalar load.  Whatever the table holds, no access leaves the
+    // Fast path, almost every tile: the table entry also names the partner and it or the tile's word says
+    // that one segment covers the tile, so a tile that does not hang over the row end starts all its
+    // loads after one or two scalar loads.  Whatever the table holds, no access leaves the
     // matrix: rows are checked against n and the tile against P.
     if (!SHORT && order) {
         unsigned at = cluster, one_segment = 0;

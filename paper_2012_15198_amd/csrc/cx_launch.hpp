@@ -271,6 +271,7 @@ unsigned *order_table_for(hipStream_t stream)
 // An operator staged through LDS keeps its waves: the staging is laid out for one shape, and other workgroups of it
 // take the path in registers.
 constexpr int64_t kMinChunks = 104;
+constexpr int kTileOrder = 16;                            // see by_tile in try_gather
 template <class Op, int U>
 constexpr int gather_waves(int64_t P, int waves)
 {
@@ -354,9 +355,12 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
         if (own_table) { *status = CX_ERR_SHAPE; return true; }
         ordered = false;
     }
-    // The order by the tile wherever the table holds it (order_kernel's otherwise: rows of more than about 50 M columns).
-    // The mean staged through LDS needs one row for a whole workgroup, which the order by the cluster gives.
-    const bool by_tile = ordered && !(LdsStaged<Op>::value && a.S > 1) &&
+    // The order by the tile where the table holds it and about every kTileOrder-th cluster or more holds the edge of a
+    // segment; one segment needs no words of tiles.  On long rows a tile's word is read from memory for few rows, ahead
+    // of all loads (4 x 23,403,072 fp32 in 3 segments: by the cluster 137 us, by the tile 151), and clusters with an edge
+    // are few.  The mean staged through LDS needs one row for a whole workgroup, which the order by the cluster gives.
+    const bool edges = !LdsStaged<Op>::value && a.n >= 8 && static_cast<int64_t>(a.S - 1) * kTileOrder >= clusters * nxcd;
+    const bool by_tile = ordered && (a.S == 1 || edges) &&
                          static_cast<int64_t>(a.S) * a.n + (a.S > 1 ? (nchunks + 1) * waves : 0) <= order_entries;
     const dim3 grid(static_cast<unsigned>(cl * nxcd), static_cast<unsigned>(a.n),
                     static_cast<unsigned>(clusters));
@@ -428,7 +432,8 @@ constexpr Push push_kind(const PushOp &op) { return op.zout ? Push::kWithCopy : 
 template <class Op>
 struct PartRing {                       // the two rings that are built: short rows, long rows
     static constexpr bool kBuilt = !LdsStaged<Op>::value && Op::kRawPerSlice < 16;          // groups of 16 keep mix_kernel
-    static constexpr int kLongU = fits<Op, 2, 2>() ? 2 : 1, kLongD = std::is_same_v<Op, FusedOp> ? 4 : 2;
+    // (two slices of groups of 5 would keep registers in scratch)
+    static constexpr int kLongU = fits<Op, 2, 2>() && Op::kRawPerSlice <= 4 ? 2 : 1, kLongD = std::is_same_v<Op, FusedOp> ? 4 : 2;
     static constexpr int kShortD = Op::kRawPerSlice == 1 ? 4 : 2;
 };
 

@@ -13,7 +13,7 @@ from gpu_util import dev
 pytestmark = pytest.mark.gpu
 
 KINDS = {"gossip": ("f32", 1), "gossip16": ("bf16", 1), "fused": ("f32", 1), "fused16": ("f16", 1), "hier": ("f32", 3),
-         "hier16": ("bf16", 8), "hiersgd": ("f32", 2), "hiersgd16": ("f16", 4), "pushsum": ("f32", 1), "pushsum16": ("bf16", 1)}
+         "hier5": ("f32", 5), "hier16": ("bf16", 8), "hiersgd": ("f32", 2), "hiersgd16": ("f16", 4), "pushsum": ("f32", 1), "pushsum16": ("bf16", 1)}
 TYPES = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
 
 
@@ -27,7 +27,7 @@ def mixed(kind, n, P, so, in_place, seed):
     x = make(n * G, t, 0)
     y = second(x)
     call = getattr(cx, {"gossip": "cx_gossip_mix", "fused": "cx_sgd_fused_mix", "hier": "cx_hier_mix", "hiersgd":
-                        "cx_hier_sgd_fused_mix", "pushsum": "cx_pushsum_mix"}[kind.rstrip("16")] + ("" if rows == "f32" else "_" + rows))
+                        "cx_hier_sgd_fused_mix", "pushsum": "cx_pushsum_mix"}[kind.rstrip("156")] + ("" if rows == "f32" else "_" + rows))
     if kind.startswith("pushsum"):
         w, w2, z = torch.rand(n, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(seed)) + 0.5, torch.zeros(n, device="cuda:0"), torch.zeros_like(x)
         call(x, y, w, w2, z, P, max(1, n // 3))
@@ -36,7 +36,7 @@ def mixed(kind, n, P, so, in_place, seed):
     if kind.startswith("gossip"):
         call(x, y, P, *tables)
         return (y,)
-    if kind.rstrip("16") == "hier":
+    if kind.rstrip("156") == "hier":
         call(x, y, P, G, *tables)
         return (y,)
     v, g = make(n, torch.float32, 1), make(n * G, t, 2)
