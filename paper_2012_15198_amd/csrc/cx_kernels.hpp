@@ -429,7 +429,7 @@ __device__ __forceinline__ int partner_of(const int32_t *__restrict__ peers, int
 
 // One workgroup per segment: builds the segment's cycle schedule and writes it as the row
 // order of every cluster whose first column lies in that segment.
-__global__ __launch_bounds__(256) void order_kernel(int n, int64_t P, int S,
+__global__ __launch_bounds__(1024) void order_kernel(int n, int64_t P, int S,
                                                     const int64_t *__restrict__ seg_off,
                                                     const int32_t *__restrict__ peers, int shift,
                                                     int64_t cluster_cols, int nclusters,
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(256) void order_kernel(int n, int64_t P, int S,
 // 512 x 312,501 813 / 650; bf16 gossip on 512 x 625,001 347 / 271.
 constexpr unsigned kTileOneSegment = 1u << 31;
 
-__global__ __launch_bounds__(256) void segment_order_kernel(int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
+__global__ __launch_bounds__(1024) void segment_order_kernel(int n, int64_t P, int S, const int64_t *__restrict__ seg_off,
                                                             const int32_t *__restrict__ peers, int shift, int tile_shift,
                                                             unsigned *__restrict__ order)
 {

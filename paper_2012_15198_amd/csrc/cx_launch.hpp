@@ -271,6 +271,10 @@ unsigned *order_table_for(hipStream_t stream)
 // An operator staged through LDS keeps its waves: the staging is laid out for one shape, and other workgroups of it
 // take the path in registers.
 constexpr int64_t kMinChunks = 104;
+// A thread for every row, so that each of the schedule's rounds, of which there are about 2 log2 n, is one LDS access a
+// thread: 512 rows 9.5 us with 256 threads, 7.4 with 512; the call on 512 x 100,003
+// fp32 98.3 / 96.4, on 1,000 x 30,011 68.6 / 62.8.
+constexpr int order_threads(int n) { return n <= 256 ? 256 : n <= 512 ? 512 : 1024; }
 constexpr int kTileOrder = 16;                            // see by_tile in try_gather
 template <class Op, int U>
 constexpr int gather_waves(int64_t P, int waves)
@@ -372,12 +376,12 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
         if (!order) { *status = CX_ERR_HIP; return true; }
     }
     if (by_tile) {
-        hipLaunchKernelGGL(segment_order_kernel, dim3(a.S), dim3(256), sizeof(int) * kScheduleWords(a.n), a.stream, a.n, a.P, a.S,
+        hipLaunchKernelGGL(segment_order_kernel, dim3(a.S), dim3(order_threads(a.n)), sizeof(int) * kScheduleWords(a.n), a.stream, a.n, a.P, a.S,
                            a.seg_off, a.peers, a.shift, __builtin_ctz(kWave * Op::kElems * U), order);
         if (hipGetLastError() != hipSuccess) { *status = CX_ERR_HIP; return true; }
     } else if (ordered) {
         const int64_t nclusters = clusters * nxcd;
-        hipLaunchKernelGGL(order_kernel, dim3(a.S), dim3(256), sizeof(int) * kScheduleWords(a.n), a.stream, a.n,
+        hipLaunchKernelGGL(order_kernel, dim3(a.S), dim3(order_threads(a.n)), sizeof(int) * kScheduleWords(a.n), a.stream, a.n,
                            a.P, a.S, a.seg_off, a.peers, a.shift, cl * chunk_cols, static_cast<int>(nclusters),
                            order);
         if (hipGetLastError() != hipSuccess) { *status = CX_ERR_HIP; return true; }
