@@ -389,6 +389,8 @@ int cx_hbm_free(void *ptr);
  *   key 10: cx_hier_mix, G = 8, out of place: 1 = reduce the group through LDS, one row per wavefront
  *           (same results as the default sum in registers; kept for side-by-side measurement)
  * A (key 0, key 3) pair that an operator was not built with falls back to its default.
+ * In place, any of keys 0 to 4 and 9 asks for the walk with one wavefront per tile, also where a call would by default
+ * split a tile's rows over several.
  * cx_set_tuning returns CX_ERR_SHAPE for an unknown key or value; a value of -1 restores
  * the default.
  */
