@@ -209,7 +209,7 @@ def _ready(x_in, size, mats, P, G, seg_off_dev, peers_dev, vectors):
         return None
     for _, t, rows_of, t_size in mats:
         s = t.shape
-        if (len(s) != 2 or s[0] != W // rows_of or s[1] > ld or t.stride() != (ld, 1) or t.dtype not in _PLAIN[t_size]
+        if (len(s) != 2 or s[0] != W // rows_of or not P <= s[1] <= ld or t.stride() != (ld, 1) or t.dtype not in _PLAIN[t_size]
                 or t.device != device):
             return None
     for _, t in vectors:
@@ -249,6 +249,9 @@ def _full_checks(x_in, size, mats, P, G, seg_off_dev, peers_dev, vectors):
             raise ValueError("P must lie in [1, row length]")
     else:
         S = _tables(x_in, P, seg_off_dev, peers_dev, n)
+    for name, t, _, _ in mats:           # a row's P columns from the tensor's own first one: beyond its width lies the next
+        if t.shape[1] < P:               # row's beginning, and behind the last row somebody else's memory
+            raise ValueError(f"{name}: rows of {t.shape[1]} columns, P is {P}")
     _same_device(x_in, *(t for _, t, _, _ in mats), *(t for _, t in vectors), seg_off_dev, peers_dev)
     return W, ld, S
 

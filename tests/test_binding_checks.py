@@ -60,6 +60,36 @@ def test_every_matrix_argument_is_checked_against_x_in(bad, match):
     refuses(cx.cx_pushsum_mix, mat(), mat(), torch.ones(W), torch.ones(W), bad(), P, 1, match=match)
 
 
+@pytest.mark.parametrize("columns", [slice(0, P - 1), slice(LD // 2, LD), slice(4, P), slice(0, 0)])
+def test_every_matrix_argument_holds_P_columns(columns):
+    """A view with x_in's row stride and fewer than P columns: the kernels would write beyond it, for the last row beyond
+    the allocation.  Exactly P columns are enough."""
+    so, pe = tables()
+    so2, pe2 = tables(W // G)
+    w = lambda: torch.ones(W)
+    b16 = lambda *a: mat(*a, dtype=torch.bfloat16)
+    calls = [(cx.cx_gossip_mix, [mat, mat], (P, so, pe)), (cx.cx_gossip_mix_noalloc, [mat, mat], (P, so, pe)),
+             (cx.cx_gossip_mix_bf16, [b16, b16], (P, so, pe)), (cx.cx_hier_mix, [mat, mat], (P, G, so2, pe2)),
+             (cx.cx_hier_mix_f16, [b16, b16], (P, G, so2, pe2)),
+             (cx.cx_sgd_fused_mix, [mat] * 5, (0.1, 0.9, 1e-4, P, so, pe)),
+             (cx.cx_sgd_fused_mix_bf16, [b16, b16, mat, mat, b16], (0.1, 0.9, 1e-4, P, so, pe)),
+             (cx.cx_hier_sgd_fused_mix, [mat, mat, lambda: mat(W // G), lambda: mat(W // G), mat], (0.1, 0.9, 1e-4, P, G, so2, pe2)),
+             (cx.cx_hier_sgd_fused_mix_f16, [b16, b16, lambda: mat(W // G), lambda: mat(W // G), b16],
+              (0.1, 0.9, 1e-4, P, G, so2, pe2)),
+             (lambda x, y, z, *r: cx.cx_pushsum_mix(x, y, w(), w(), z, *r), [mat, mat, mat], (P, 1)),
+             (lambda x, y, z, *r: cx.cx_pushsum_mix_bf16(x, y, w(), w(), z, *r), [b16, b16, b16], (P, 1))]
+    for on_device in (False, True):
+        view = lambda make, c: OnDevice(make()[:, c]) if on_device else make()[:, c]
+        tail = lambda rest: [OnDevice(t) if on_device and torch.is_tensor(t) else t for t in rest]
+        for call, makes, rest in calls[:9] if on_device else calls:
+            for slot in range(1, len(makes)):
+                refuses(call, *[view(m, columns if i == slot else slice(0, P)) for i, m in enumerate(makes)], *tail(rest),
+                        match=f"columns, P is {P}")
+    x = OnDevice(mat()[:, :P])
+    assert cx._full_checks(x, 4, (("x_out", x, 1, 4),), P, 1, OnDevice(so), OnDevice(pe), ()) == (W, LD, S)
+    assert cx._ready(x, 4, (("x_out", OnDevice(mat()[:, columns]), 1, 4),), P, 1, OnDevice(so), OnDevice(pe), ()) is None
+
+
 def test_hierarchical_gradient_step_checks_the_leader_momentum_shape():
     so, pe = tables(W // G)
     L = W // G
