@@ -118,17 +118,18 @@ constexpr int waves_with_schedules(int n, int waves)
 // Below kShortTiles tiles (8 wavefronts per CU; three times as many where a lane would take two slices) a lane takes
 // one slice and the deepest ring that stays within kShortRing 16-byte registers; workgroups are halved until there
 // are kShortBlocks of them, one for every second CU (fewer, larger ones lose to idle CUs, more lose the lock-step of
-// the waves: bf16 gradient step on 256 x 300,007 in groups of 8: 117 us with 4 waves, 132 with one).  fp32 optimizer
-// step on 256 x 75,003: 444 -> 123 us with one slice, eight rows; bf16 gossip on 256 x 300,007: 153 -> 108.
+// the waves: bf16 gradient step on 256 x 400,007 in groups of 8, one segment: 102 us with 4 waves, 149 with eight, 138 with
+// two, 161 with one).  fp32 optimizer step on 64 x 300,007, one segment: 131 -> 82 us with one slice, eight rows; bf16
+// gossip on 256 x 800,007: 273 -> 194.  (Calls that part_shape splits do not come here.)
 //
 // The cap on resident workgroups is a cap on wavefronts: where a workgroup has fewer than the operator's, because rows
-// are short or because many rows' schedules fill the LDS, more of them may be resident.  1,024 x 300,007 fp32 in place,
-// workgroups of two waves, two of them against eight per CU: gossip 707 -> 592 us, optimizer step 1,494 -> 1,349,
-// push-sum with the de-biased copy 1,713 -> 1,179.
+// are short or because many rows' schedules fill the LDS, more of them may be resident.  1,024 x 600,003 fp32 in place,
+// workgroups of two waves, two of them against eight per CU: gossip 1,274 -> 1,196 us, optimizer step 2,796 -> 2,793,
+// push-sum with the de-biased copy 3,063 -> 2,274.
 //
 // Operators on plain rows that take one slice instead of two there, with tiles enough, take eight rows in flight beside
-// many rows only: push-sum of 16-bit rows with the copy on 64 x 2,500,007 271 us with eight, 228 with four; bf16 gossip
-// on 32 x 3,200,013 98 us with eight, 85 with four; push-sum of 16-bit rows on 256 x 3,000,001 587 with either.
+// many rows only: push-sum of 16-bit rows with the copy on 64 x 2,000,003 193 us with eight, 155 with four; bf16 gossip
+// on 32 x 3,200,013 97 us with eight, 83 with four; push-sum of 16-bit rows on 256 x 3,000,001 606 and 599.
 constexpr int64_t kShortTiles = 2048, kShortBlocks = 128;
 constexpr int kShortRing = 32;
 template <class Op, class = void>
@@ -410,21 +411,36 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
 // ---------------------------------------------------------------------------------
 // In place with the rows of a tile split over wavefronts (parts_kernel), or parts == 0: mix_kernel.
 //
-// Rows of few tiles want as many wavefronts as there can be: the smallest power of two of parts that gives kPartJobs of
-// them.  Longer ones gain from two parts, since the two rows that a part reads ahead come all at once, with two slices per
-// lane where the registers allow it; there the launch has few rounds of workgroups, and mix_kernel stays where the last
-// one would leave too many CUs idle.  Times in place, us, mix_kernel / parts, every pass on the next of several matrices:
-//   below kPartLong tiles (n >= 4): fp32 gossip on 512 x 3,001 118 / 21; fewer than four rows have nothing to split;
-//   below kPartMid: 8 rows (bf16 gossip on 100 x 250,007 56 / 32), 16 where fp32 rows carry groups or momentum (fp32
-//     mean of groups of 2 on 16 x 350,003 11.7 / 14.2), 32 for groups on the longer half (of 4 on 80 x 250,007 33 / 36);
-//   16-bit rows up to kPartWide16 tiles (bf16 gossip on 70 x 2,100,003 0.93, 3,000,017 0.99, 4,000,037 1.04 of
-//     mix_kernel's time), kPartVeryLong with four or five registers a row and slice (binary16 optimizer step on
-//     33 x 1,500,003 0.89, 8,000,021 1.05), half of that with two or three (groups of 2 of 70 x 1,100,003 0.91, 1,500,003 1.03);
-//   fp32 rows from 16 on: gossip and the optimizer step up to 2 * kPartVeryLong tiles (33 x 1,100,003 0.91 and 0.87,
-//     9,000,011 gossip 1.03), push-sum with the copy up to kPartWide16 (0.91, 2,100,003 without gain), groups in
-//     workgroups of one tile of two slices (of 4 of 33 x 1,100,003 0.90; two and four tiles 1.00 to 1.07, one slice up to 1.12);
-//   up to 8 very long fp32 rows, which mix_kernel's two waves serve badly: gossip where they begin inside lines
-//     (8 x 6,000,011 0.84), push-sum without the copy (5 x 6,000,011 0.78).
+// Lengths are counted in tiles of one slice per lane and in rounds of mix_kernel, kRound tiles: one workgroup of eight
+// waves on every CU, each wavefront with a tile and all rows of it.  Two parts need twice the wavefronts for half the
+// rows each, so that tiles up to the middle of mix_kernel's last round take the split an odd number of half rounds where
+// mix_kernel pays for a whole one, and beyond the middle both take the same and the split has its two extra rows on top.
+// Time of the split over mix_kernel's, in place, several matrices in turn, on 16 to 350 rows: geometric
+// mean (largest), 7,000 shapes in all:
+//   tiles                    512-1,023    1,024-2,047  2,049-3,072  3,073-4,096  4,097-5,120  5,121-6,144
+//   fp32 gossip              0.87 (1.00)  0.96 (1.04)  0.90 (1.01)  1.04 (1.09)  0.93 (1.00)  1.04 (1.12)
+//   fp32 push-sum, copy      0.56 (0.71)  0.79 (0.98)  0.92 (0.99)  1.05 (1.11)  0.91 (0.95)  0.96 (1.05)
+//   bf16 gossip              0.78 (0.95)  0.97 (1.12)  0.92 (1.03)  1.04 (1.18)  0.94 (1.05)  1.00 (1.16)
+//   fp32 optimizer step      0.95 (1.10)  1.01 (1.14)  0.91 (1.02)  1.02 (1.12)  0.92 (0.97)  0.99 (1.04)
+//   fp32 groups, up to four registers a row and slice
+//                            0.96 (1.11)  1.05 (1.30)  0.91 (1.06)  1.04 (1.16)  0.95 (1.05)  0.99 (1.14)
+//   16-bit steps and groups  0.91 (1.18)  0.99 (1.37)  0.90 (1.21)  1.03 (1.24)  0.93 (1.05)  1.03 (1.18)
+// later_round() follows that.  In the first round what counts is how soon mix_kernel's wavefronts have enough loads in
+// flight, and whether all its workgroups walk in lock-step, as they do in one segment (first_round()):
+//   fp32 plain rows    three quarters of the round, with the copy of push-sum all of it; half below 16 rows and in push-sum
+//               without the copy;
+//   16-bit plain rows  all of the round with the copy and below 32 rows (beyond three quarters 0.92), three quarters, half
+//               from 256 rows on (beyond half: fewer rows 0.95, more 1.01, up to 1.21);
+//   fp32 steps, and groups of up to four registers  a quarter of the round from 16 rows on (400-512 tiles: 0.85), half of it
+//               from 32 rows in several segments (0.90; in one 0.98, up to 1.09), the step on plain rows three quarters from
+//               64 rows in several segments;
+//   fp32 groups of more  half of the round in several segments (0.89), a quarter in one (up to there 0.95, to half of the
+//               round 1.04, up to 1.24), less for gradient steps and below eight rows;
+//   16-bit steps and groups  three quarters in several segments (0.88); in one half of it to a quarter (512-640 tiles of
+//               groups 0.89, 768-1,536 0.99, up to 1.23);
+//   fewer than eight rows otherwise, and fewer than 16 of fp32 steps and groups  short rows (kPartLong).
+// Of 5,930 shapes drawn afterwards (60 to 9,000 tiles, 3 to 1,024 rows) 16 took more than 1.03 of mix_kernel's time, up to 1.11
+// (bf16 gossip on 237 x 708,400 in one segment 167 / 150 us); a rule by length and row count alone had 130, up to 1.39.
 // ---------------------------------------------------------------------------------
 struct PartShape {
     int U, D, parts, tiles;
@@ -432,6 +448,11 @@ struct PartShape {
 enum class Push { kNo, kPlain, kWithCopy };
 template <class Op> constexpr Push push_kind(const Op &) { return Push::kNo; }
 constexpr Push push_kind(const PushOp &op) { return op.zout ? Push::kWithCopy : Push::kPlain; }
+template <bool H> constexpr Push push_kind(const Push16Op<H> &op) { return op.zout ? Push::kWithCopy : Push::kPlain; }
+template <class Op, class = void>
+struct HasMomentum : std::false_type {};
+template <class Op>
+struct HasMomentum<Op, std::void_t<decltype(std::declval<const Op &>().vin)>> : std::true_type {};
 
 template <class Op>
 struct PartRing {                       // the two rings that are built: short rows, long rows
@@ -442,7 +463,49 @@ struct PartRing {                       // the two rings that are built: short r
 };
 
 constexpr int64_t kPartJobs = 1024, kCUs = 256;           // wavefronts
-constexpr int64_t kPartLong = 400, kPartMid = 1000, kPartVeryLong = 4096, kPartWide16 = 5000;   // tiles of one slice per lane
+constexpr int64_t kPartLong = 400;                        // tiles of one slice per lane
+constexpr int64_t kRound = kCUs * kMaxWavesPerBlock;
+
+// Most tiles in mix_kernel's first round that are split.
+template <class Op>
+constexpr int64_t first_round(const Op &op, int n, bool one_segment)
+{
+    constexpr int kRaw = Op::kRawPerSlice;
+    constexpr bool kWideRows = Op::kElems == 4, kStep = HasMomentum<Op>::value, kPlainStep = std::is_same_v<Op, FusedOp>;
+    constexpr int64_t kShort = kPartLong - 1;
+    const Push push = push_kind(op);
+    if (kWideRows && kRaw > 1) {
+        if (n < 8) return kStep && kRaw > 6 ? kRound / 16 : kRaw > 4 || (one_segment && !kPlainStep) ? kRound / 8 : kShort;
+        if (n < 16) return kRaw <= 6 || !one_segment ? kShort : kRound / 8;
+        if (one_segment) return kStep && kRaw > 5 ? kRound * 5 / 32 : kRound / 4;
+        if (kRaw > 4) return n >= 32 ? kRound / 2 : kRound * 3 / 8;
+        return kPlainStep && n >= 64 ? kRound * 3 / 4 : n >= 32 ? kRound / 2 : kRound / 4;
+    }
+    if (n < 8) return kShort;
+    if (kRaw == 1) {
+        if (kWideRows) return n < 16 || push == Push::kPlain ? kRound / 2 : push == Push::kWithCopy ? kRound : kRound * 3 / 4;
+        return push == Push::kWithCopy || n < 32 ? kRound : n < 256 ? kRound * 3 / 4 : kRound / 2;
+    }
+    if (!one_segment) return kRound * 3 / 4;
+    return kRaw <= 2 ? kRound / 2 : kRaw <= 4 ? kRound * 3 / 8 : kStep ? kRound / 4 : kRound * 5 / 16;
+}
+
+// In the first half of a later round?  Up to the round from which the walk's own time hides the difference.
+template <class Op>
+constexpr bool later_round(const Op &op, int n, int64_t tiles)
+{
+    constexpr int kRaw = Op::kRawPerSlice;
+    constexpr bool kWideRows = Op::kElems == 4;
+    const Push push = push_kind(op);
+    const int last = !kWideRows                                     ? (kRaw == 1 || kRaw > 5 ? 3 : kRaw > 3 ? 2 : 1)
+                     : std::is_same_v<Op, FusedOp>                  ? 4
+                     : kRaw > 4 || (kRaw == 1 && push == Push::kPlain) ? 1
+                                                                    : 3;
+    if (n < (kWideRows ? 16 : 8)) return false;
+    const int64_t round = kCUs * waves_with_schedules<Op>(n, kMaxWavesPerBlock), before = (tiles - 1) / round;
+    return before >= 1 && before < last && 2 * (tiles - before * round) <= round;
+}
+
 template <class Op>
 constexpr PartShape part_shape(const Op &op, int n, int64_t P, int S)
 {
@@ -452,31 +515,27 @@ constexpr PartShape part_shape(const Op &op, int n, int64_t P, int S)
     constexpr bool kGroups = kWideRows && !kPlainRows && !std::is_same_v<Op, FusedOp>;
     if (!Ring::kBuilt || n < 4 || P < Op::kElems) return kNone;
     const int64_t tiles = (P + kWave * Op::kElems - 1) / (kWave * Op::kElems);
+    // up to 8 very long fp32 rows, which mix_kernel's two waves serve badly: gossip where they begin inside lines
+    // (0.75 to 0.98 between 4 and 8 rows of 4.2 to 21 million columns), push-sum without the copy (0.74 to 0.90)
+    const bool whole_lines = op.ld * (16 / Op::kElems) % 128 == 0;
+    const Push push = push_kind(op);
+    const bool few = kWideRows && kPlainRows && n <= 8 && tiles >= 8 * kRound &&
+                     (push == Push::kNo ? !whole_lines : push == Push::kPlain);
+    if (!few && tiles > first_round(op, n, S == 1) && !later_round(op, n, tiles)) return kNone;
     const bool long_rows = tiles >= kPartLong;
-    if (tiles >= kPartMid) {
-        if (kWideRows) {
-            const Push push = push_kind(op);
-            const bool whole_lines = op.ld * (16 / Op::kElems) % 128 == 0;
-            const bool few = kPlainRows && n <= 8 && tiles >= 4 * kPartVeryLong &&
-                             (push == Push::kNo ? !whole_lines : push == Push::kPlain);
-            const int64_t most = push == Push::kPlain ? 0 : push == Push::kWithCopy || kGroups ? kPartWide16 : 2 * kPartVeryLong;
-            if (!few && (n < 16 || tiles >= most)) return kNone;
-        } else if (n < 8 || tiles >= (kPlainRows || Op::kRawPerSlice > 5 ? kPartWide16 : Op::kRawPerSlice > 3 ? kPartVeryLong : kPartVeryLong / 2)) {
-            return kNone;
-        }
-    } else if (long_rows && n < (!kWideRows || kPlainRows ? 8 : kGroups && tiles >= kPartMid / 2 ? 32 : 16)) {
-        return kNone;
-    }
     PartShape s{long_rows ? Ring::kLongU : 1, long_rows ? Ring::kLongD : Ring::kShortD, 2, 1};
     const int limit = long_rows ? kPartWaves<Op, Ring::kLongU, Ring::kLongD> : kPartWaves<Op, 1, Ring::kShortD>;
     const int64_t jobs = (tiles + s.U - 1) / s.U;
+    // As many parts as give kPartJobs wavefronts; longer rows gain from two parts, since the two rows that a part reads
+    // ahead come all at once.
     while (s.parts * jobs < kPartJobs && s.parts < limit && 2 * s.parts <= n) s.parts *= 2;
     // As many adjacent tiles a workgroup as leave the last round of workgroups, one a CU, nearly as full as the others
-    // (2 parts x 4 tiles, 258 workgroups: fp32 mean of groups of 2 on 24 x 515,003 28.6 us, mix_kernel 20.0).  Beside
+    // (fp32 means of groups of 2 to 4 on 700 to 800 tiles: 0.95 of mix_kernel's time, with 2 parts x 4 tiles 1.40).  Beside
     // many rows one round of the widest is best whatever it leaves idle: fp32 optimizer step on 256 x 300,007, 154
-    // workgroups of 4 tiles 340 us, 593 of one tile 362.
+    // workgroups of 4 tiles 340 us, 593 of one tile 362.  Two slices per lane of groups on longer rows: one tile each (on 2,049
+    // to 3,072 tiles 0.94 with one, 0.95 with two, 1.03 with four).
     int most_full = 0;
-    const int widest = s.parts >= kMaxWavesPerBlock ? 1 : (n < 8 ? 4 : kMaxWavesPerBlock) / s.parts;
+    const int widest = s.parts >= kMaxWavesPerBlock || (kGroups && tiles > kRound) ? 1 : (n < 8 ? 4 : kMaxWavesPerBlock) / s.parts;
     for (int t = widest; t >= 1 && most_full < 90; t /= 2) {
         const int64_t blocks = (jobs + t - 1) / t + S - 1, rounds = (blocks + kCUs - 1) / kCUs;
         const int full = n >= 64 && long_rows && rounds == 1 ? 100 : static_cast<int>(100 * blocks / (rounds * kCUs));
@@ -485,8 +544,10 @@ constexpr PartShape part_shape(const Op &op, int n, int64_t P, int S)
             most_full = full;
         }
     }
-    if (tiles >= kPartMid && (most_full < 88 || (kGroups && (s.tiles > 1 || s.U == 1)))) return kNone;
-    return s;
+    // mix_kernel where few rows leave the split's rounds of workgroups badly filled (the workgroups of the segments' pieces
+    // count: fp32 gradient step without groups on 20 x 119,800 in 32 segments, 257 workgroups, 1.32)
+    const bool idle = long_rows && kWideRows && !kPlainRows && Op::kRawPerSlice <= 4 && n < 64 && most_full < 70;
+    return idle ? kNone : s;
 }
 
 template <class Op>

@@ -22,8 +22,8 @@ constexpr bool is(const WalkShape &s, int U, int D, int waves, int wgs_per_cu)
 {
     return s.U == U && s.D == D && s.waves == waves && s.wgs_per_cu == wgs_per_cu;
 }
-static_assert(is(shape<MeanOp<1>>(1024, 300007, 300032), 1, 8, 2, 8) && is(shape<MeanOp<1>>(1024, 300007, 300008), 1, 8, 2, 8));
-static_assert(is(shape<PushOp>(1024, 11689511, 11689512), 2, 8, 2, 8) && is(shape<FusedOp>(256, 100003, 100004), 1, 8, 2, 8));
+static_assert(is(shape<MeanOp<1>>(1024, 600003, 600032), 1, 8, 2, 8) && is(shape<MeanOp<1>>(1024, 600003, 600008), 1, 8, 2, 8));
+static_assert(is(shape<PushOp>(1024, 11689511, 11689512), 2, 8, 2, 8) && is(shape<FusedOp>(12, 110003, 110004), 1, 8, 2, 8));
 
 // Long rows: two waves where rows begin on 128-byte lines (11,689,536 fp32 columns: a multiple of 32) and there are
 // few of them, eight where they begin inside lines.
@@ -39,8 +39,8 @@ static_assert(is(shape<MeanOp<16>>(4, 11689511, 11689536), 1, 2, 8, 2) && is(sha
 
 // Plain rows: eight rows in flight beside many rows, or where tiles are few.
 static_assert(is(shape<Row16Op<false>>(256, 3000003, 3000008), 1, 8, 8, 2) && is(shape<Row16Op<false>>(64, 3000003, 3000008), 1, 4, 8, 2) &&
-              is(shape<Row16Op<false>>(16, 3000003, 3000008), 1, 4, 8, 2) && is(shape<Row16Op<false>>(16, 100003, 100008), 1, 8, 1, 16) &&
-              is(shape<MeanOp<1>>(16, 100003, 100032), 1, 8, 2, 8));
+              is(shape<Row16Op<false>>(16, 3000003, 3000008), 1, 4, 8, 2) && is(shape<Row16Op<false>>(3, 100003, 100008), 1, 8, 1, 16) &&
+              is(shape<MeanOp<1>>(3, 100003, 100032), 1, 8, 2, 8));
 
 // In place with a tile's rows split over wavefronts: as many parts as make kPartJobs wavefronts and the rows and the
 // registers allow, as many tiles a workgroup as fill the last round of workgroups; mix_kernel elsewhere.
@@ -60,11 +60,54 @@ static_assert(parts_are<MeanOp<1>>(512, 3001, 4, 1, 4, 16, 1) && parts_are<MeanO
               parts_are<FusedOp>(4, 2000, 4, 1, 2, 4, 1) && no_parts<FusedOp>(3, 2000, 4));
 static_assert(parts_are<MeanOp<1>>(16, 256 * 399, 1, 1, 4, 4, 2) && parts_are<MeanOp<1>>(16, 256 * 399 + 1, 1, 2, 2, 8, 1) &&
               no_parts<MeanOp<1>>(7, 256 * 399 + 1, 1) && no_parts<FusedOp>(15, 256 * 399 + 1, 1));
-static_assert(parts_are<FusedOp>(256, 300007, 8, 2, 4, 2, 4) && no_parts<MeanOp<4>>(33, 515003, 7) && no_parts<MeanOp<1>>(33, 800003, 7) &&
-              parts_are<MeanOp<4>>(33, 1100003, 7, 2, 2, 2, 1) && parts_are<MeanOp<1>>(33, 515003, 7, 2, 2, 2, 2));
+static_assert(parts_are<FusedOp>(256, 300007, 8, 2, 4, 2, 4) && no_parts<MeanOp<1>>(33, 800003, 7) &&
+              parts_are<MeanOp<4>>(33, 1100003, 7, 2, 2, 2, 1));
 static_assert(parts_are<MeanOp<1>>(8, 6000011, 7, 2, 2, 2, 4) && no_parts<MeanOp<1>>(8, 6000011, 7, 6000032) && no_parts<MeanOp<1>>(9, 6000011, 7));
 static_assert(parts_are<Row16Op<true, 4>>(16, 400009, 7, 1, 2, 2, 4) && no_parts<Row16Op<true, 4>>(16, 4000009, 7) &&
               parts_are<Row16Op<true, 8>>(16, 2100003, 7, 1, 2, 2, 1) && no_parts<Row16Op<false>>(32, 25557032, 8));
 static_assert(no_parts<MeanOp<16>>(32, 3001, 4) && kPartWaves<MeanOp<1>, 1, 4> == 16 && kPartWaves<FusedOp, 2, 4> == 8);
+
+float a_copy;
+constexpr PushOp with_copy()
+{
+    PushOp op{};
+    op.zout = &a_copy;
+    return op;
+}
+static_assert(parts_are<PushOp>(64, 256 * 2048, 1, 2, 2, 2, 4, 0, with_copy()) && parts_are<PushOp>(9, 256 * 1025, 1, 0, 0, 0, 0, 0, with_copy()));
+
+// The short shapes of mix_kernel above are those of calls that are not split.
+static_assert(no_parts<MeanOp<1>>(1024, 600003, 8) && no_parts<FusedOp>(12, 110003, 8) && no_parts<Row16Op<false>>(3, 100003, 8) &&
+              no_parts<MeanOp<1>>(3, 100003, 8) && no_parts<MeanOp<8>>(4, 900001, 8) && no_parts<FusedOp>(32, 900001, 1) &&
+              no_parts<Row16Op<false>>(64, 3000003, 8) && no_parts<MeanOp<1>>(32, 2000003, 8));
+
+// Shapes that the split slowed by 5 to 32 per cent stay whole.
+static_assert(no_parts<Row16Op<false>>(500, 650003, 8) && no_parts<Row16Op<false>>(500, 1500003, 8) && no_parts<HierFusedOp<8>>(5, 60007, 4) &&
+              no_parts<HierFused16Op<true, 8>>(64, 828274, 1) && no_parts<Row16Op<false, 4>>(10, 884531, 1) &&
+              parts_are<PushOp>(200, 840693, 1, 0, 0, 0, 0, 0, with_copy()) && no_parts<HierFusedOp<8>>(33, 139500, 1) && no_parts<HierFusedOp<1>>(20, 119800, 32));
+
+// Every length of a stretch takes one answer: in the first half of mix_kernel's second and third round the split, one tile a
+// workgroup for groups, in the second halves mix_kernel; many rows, whose schedules leave a workgroup fewer waves, have
+// shorter rounds.
+template <class Op>
+constexpr bool all_lengths(int n, int S, int64_t from, int64_t to, bool split, int tiles_a_workgroup = 0)
+{
+    for (int64_t tiles = from; tiles <= to; tiles += 7) {
+        Op op{};
+        op.ld = tiles * kWave * Op::kElems + 8;
+        const PartShape s = part_shape(op, n, tiles * kWave * Op::kElems, S);
+        if ((s.parts != 0) != split || (split && tiles_a_workgroup && s.tiles != tiles_a_workgroup)) return false;
+    }
+    return true;
+}
+static_assert(all_lengths<MeanOp<4>>(33, 7, 2049, 3072, true, 1) && all_lengths<MeanOp<4>>(33, 7, 3073, 4096, false) &&
+              all_lengths<MeanOp<4>>(33, 7, 4097, 5120, true, 1) && all_lengths<MeanOp<4>>(33, 7, 5121, 20000, false) &&
+              all_lengths<MeanOp<4>>(33, 7, 1025, 2048, false) && all_lengths<MeanOp<4>>(64, 7, 400, 1024, true));
+static_assert(all_lengths<MeanOp<1>>(64, 8, 20, 1536, true) && all_lengths<MeanOp<1>>(64, 8, 1537, 2048, false) &&
+              all_lengths<MeanOp<1>>(64, 8, 2049, 3072, true) && all_lengths<MeanOp<1>>(64, 8, 3073, 4096, false) &&
+              all_lengths<HierFusedOp<8>>(33, 1, 321, 20000, false) && all_lengths<Row16Op<true, 2>>(33, 8, 1537, 20000, false));
+static_assert(all_lengths<MeanOp<1>>(500, 1, 1537, 2304, true) && all_lengths<MeanOp<1>>(500, 1, 2305, 3072, false));
+static_assert(all_lengths<FusedOp>(64, 8, 6145, 7168, true) && all_lengths<FusedOp>(64, 8, 7169, 20000, false) &&
+              all_lengths<FusedOp>(15, 8, 400, 20000, false) && all_lengths<PushOp>(64, 1, 1025, 20000, false));
 
 }  // namespace
