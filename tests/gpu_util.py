@@ -1,7 +1,8 @@
-"""Helpers shared by the GPU parity tests (marshalling only)."""
+"""Helpers shared by the GPU parity tests: marshalling, launch parameters, and one call in place against the oracle."""
 import numpy as np
 import torch
 
+import oracle as O
 from paper_2012_15198_amd import cxmix as cx
 
 DEV = "cuda:0"
@@ -87,3 +88,53 @@ def worst_rel(got, ref64, floor=1e-30):
     ref = np.asarray(ref64, dtype=np.float64)
     m = np.isfinite(ref) & (np.abs(ref) > floor)
     return float((np.abs(got[m] - ref[m]) / np.abs(ref[m])).max()) if m.any() else 0.0
+
+
+def in_place_equals_the_oracle(kind, G, n, P, ld, so, apart=""):
+    """One call of n gossiping rows in place, every buffer that it writes against the oracle, bit for bit.  kind: gossip,
+    hier, fused, hiersgd, pushsum or debias, and the same with 16 for bfloat16 rows; apart: "v" or "x" of the fp32 step in buffers of its own."""
+    W, rng = n * G, np.random.default_rng(P + n)
+    wide = kind.endswith("16")
+    kind, b16 = kind.removesuffix("16"), "_bf16" if wide else ""
+    pe, hop, sgd = O.topology(P, n, len(so) - 1, 0, 1)[0], min(2, n - 1), (0.1, 0.9, 1e-4)
+    sod, ped = dev(so), dev(pe)
+    matrix = lambda rows, sigma: rng.standard_normal((rows, ld), dtype=np.float32) * np.float32(sigma)
+    x = matrix(W, 0.05)
+    if wide:
+        x = O.f32_to_bf16(x)
+    a = dev(x.view(np.int16) if wide else x)
+    if kind == "gossip":
+        getattr(cx, "cx_gossip_mix" + b16)(a, a, P, sod, ped)
+        want = O.gossip_mix_bf16(x, P, so, pe) if wide else O.gossip_mix(x, P, so, pe)
+    elif kind == "hier":
+        getattr(cx, "cx_hier_mix" + b16)(a, a, P, G, sod, ped)
+        want = O.hier_mix16("bf16", x, P, G, so, pe) if wide else once(O.hier_mix_f64(x, P, G, so, pe))
+    elif kind in ("pushsum", "debias"):
+        w = (0.5 + rng.random(W)).astype(np.float32)
+        wd, wo, z = dev(w), dev(w), torch.zeros_like(a) if kind == "debias" else None
+        getattr(cx, "cx_pushsum_mix" + b16)(a, a, wd, wo, z, P, hop)
+        want, ww, wz = O.pushsum_mix16("bf16", x, w, P, hop, True) if wide else O.pushsum_mix_f32(x, w, P, hop, True)
+        assert same_bits(host(wo), ww)
+        if z is not None:
+            got = host(z)[:, :P]
+            assert (got.view(np.uint16) == wz[:, :P]).all() if wide else same_bits(got, wz[:, :P])
+    else:
+        v, g = matrix(n, 0.02), matrix(W, 0.01)
+        if wide:
+            g = O.f32_to_bf16(g)
+        vd, gd = dev(v), dev(g.view(np.int16) if wide else g)
+        vo = torch.zeros_like(vd) if apart == "v" else vd
+        xd, a = a, torch.zeros_like(a) if apart == "x" else a
+        if kind == "fused":
+            getattr(cx, "cx_sgd_fused_mix" + b16)(xd, a, vd, vo, gd, *sgd, P, sod, ped)
+            want, wv = O.sgd_fused_mix16("bf16", x, v, g, *sgd, P, so, pe) if wide else \
+                (once(t) for t in O.sgd_fused_mix_f64(x, v, g, *sgd, P, so, pe))
+        else:
+            getattr(cx, "cx_hier_sgd_fused_mix" + b16)(xd, a, vd, vo, gd, *sgd, P, G, sod, ped)
+            want, wv = O.hier_sgd_fused_mix16("bf16", x, v, g, *sgd, P, G, so, pe) if wide else \
+                (once(t) for t in O.hier_sgd_fused_mix_f64(x, v, g, *sgd, P, G, so, pe))
+        assert same_bits(host(vo)[:, :P], wv[:, :P])
+    if wide:
+        assert (host(a).view(np.uint16)[:, :P] == want[:, :P]).all()
+    else:
+        assert same_bits(host(a)[:, :P], want[:, :P])

@@ -8,7 +8,7 @@ import torch
 import oracle as O
 from paper_2012_15198_amd import cxmix as cx
 from paper_2012_15198_amd import workloads as WL
-from gpu_util import Tuning, dev, host, once, same_bits
+from gpu_util import Tuning, dev, host, in_place_equals_the_oracle, once, same_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -101,30 +101,35 @@ def test_boundary_tiles_keep_to_their_columns(P, in_place):
 
 
 # in place: the edges where workgroups are halved (127 * 1, 2, 4, 8 tiles) and full ones of one slice per lane, for rings
-# that the steady loop turns never, once and many times (n <= 2 D, n just above, n = 37)
+# that the steady loop turns never, once and many times (n <= 2 D, n just above, n = 37).  Most of these calls split their
+# rows over wavefronts by default; the lock-step parameter at its default value asks for mix_kernel and leaves it its shape.
+@pytest.mark.parametrize("lockstep", [-1, 1])
 @pytest.mark.parametrize("W", [3, 5, 17, 37])
 @pytest.mark.parametrize("P", [TILE * 127 + 1, TILE * 254, TILE * 1016 + 3, 2 * TILE * 2047, 2 * TILE * 2047 + 1])
 @pytest.mark.parametrize("kind", ["gossip", "fused", "bf16"])
-def test_in_place_walk_shapes(kind, W, P):
+def test_in_place_walk_shapes(kind, W, P, lockstep):
     ld = (P + 7) // 8 * 8
     so = np.array([0, P // 3 + 1, P // 3 + 1, P - 2, P], dtype=np.int64)
     pe = O.topology(P, W, len(so) - 1, 0, 1)[0]
     x = WL.gen_matrix(W, P, 0.05, seed=P, ld=ld)
-    print(kind, W, P, flush=True)
+    print(kind, W, P, lockstep, flush=True)
     if kind == "bf16":
         xb = O.f32_to_bf16(x)
         a = dev(xb.view(np.int16))
-        cx.cx_gossip_mix_bf16(a, a, P, dev(so), dev(pe))
+        with Tuning(lockstep=lockstep):
+            cx.cx_gossip_mix_bf16(a, a, P, dev(so), dev(pe))
         assert (host(a).view(np.uint16)[:, :P] == O.gossip_mix_bf16(xb, P, so, pe)[:, :P]).all()
         return
     a = dev(x)
     if kind == "gossip":
-        cx.cx_gossip_mix(a, a, P, dev(so), dev(pe))
+        with Tuning(lockstep=lockstep):
+            cx.cx_gossip_mix(a, a, P, dev(so), dev(pe))
         want = O.gossip_mix(x, P, so, pe)
     else:
         v, g = (WL.gen_matrix(W, P, s, seed=P, ld=ld, stream=k) for s, k in ((0.02, 1), (0.01, 2)))
         vd = dev(v)
-        cx.cx_sgd_fused_mix(a, a, vd, vd, dev(g), 0.1, 0.9, 1e-4, P, dev(so), dev(pe))
+        with Tuning(lockstep=lockstep):
+            cx.cx_sgd_fused_mix(a, a, vd, vd, dev(g), 0.1, 0.9, 1e-4, P, dev(so), dev(pe))
         want, wv = (once(t) for t in O.sgd_fused_mix_f64(x, v, g, 0.1, 0.9, 1e-4, P, so, pe))
         assert same_bits(host(vd)[:, :P], wv[:, :P])
     assert same_bits(host(a)[:, :P], want[:, :P])
@@ -196,50 +201,7 @@ LONG_EDGES = [("gossip", 1, 9, (3 << 20) - 1, 32), ("gossip", 1, 9, 512 * 6143, 
 @pytest.mark.parametrize("kind,G,n,short,ld_of", LONG_EDGES)
 @pytest.mark.parametrize("beyond", [0, 1])
 def test_in_place_edge_of_short_rows(kind, G, n, short, ld_of, beyond):
-    W, P = n * G, short + beyond
+    P = short + beyond
     ld = (P + ld_of - 1) // ld_of * ld_of
     print(kind, G, n, P, ld, flush=True)
-    rng = np.random.default_rng(P + n)
-    so = np.array([0, P // 3 + 1, P // 3 + 1, P - 2, P], dtype=np.int64)
-    pe, hop = O.topology(P, n, len(so) - 1, 0, 1)[0], 2
-    sod, ped = dev(so), dev(pe)
-    matrix = lambda rows, sigma: rng.standard_normal((rows, ld), dtype=np.float32) * np.float32(sigma)
-    x, sgd = matrix(W, 0.05), (0.1, 0.9, 1e-4)
-    wide = kind.endswith("16")
-    if wide:
-        x = O.f32_to_bf16(x)
-    a = dev(x.view(np.int16) if wide else x)
-    kind, b16 = kind.removesuffix("16"), "_bf16" if wide else ""
-    if kind == "gossip":
-        getattr(cx, "cx_gossip_mix" + b16)(a, a, P, sod, ped)
-        want = O.gossip_mix_bf16(x, P, so, pe) if wide else O.gossip_mix(x, P, so, pe)
-    elif kind == "hier":
-        getattr(cx, "cx_hier_mix" + b16)(a, a, P, G, sod, ped)
-        want = O.hier_mix16("bf16", x, P, G, so, pe) if wide else once(O.hier_mix_f64(x, P, G, so, pe))
-    elif kind in ("pushsum", "debias"):
-        w = (0.5 + rng.random(W)).astype(np.float32)
-        wd, wo, z = dev(w), dev(w), torch.zeros_like(a) if kind == "debias" else None
-        getattr(cx, "cx_pushsum_mix" + b16)(a, a, wd, wo, z, P, hop)
-        want, ww, wz = O.pushsum_mix16("bf16", x, w, P, hop, True) if wide else O.pushsum_mix_f32(x, w, P, hop, True)
-        assert same_bits(host(wo), ww)
-        if z is not None:
-            got = host(z)[:, :P]
-            assert (got.view(np.uint16) == wz[:, :P]).all() if wide else same_bits(got, wz[:, :P])
-    else:
-        v, g = matrix(n, 0.02), matrix(W, 0.01)
-        if wide:
-            g = O.f32_to_bf16(g)
-        vd, gd = dev(v), dev(g.view(np.int16) if wide else g)
-        if kind == "fused":
-            getattr(cx, "cx_sgd_fused_mix" + b16)(a, a, vd, vd, gd, *sgd, P, sod, ped)
-            want, wv = O.sgd_fused_mix16("bf16", x, v, g, *sgd, P, so, pe) if wide else \
-                (once(t) for t in O.sgd_fused_mix_f64(x, v, g, *sgd, P, so, pe))
-        else:
-            getattr(cx, "cx_hier_sgd_fused_mix" + b16)(a, a, vd, vd, gd, *sgd, P, G, sod, ped)
-            want, wv = O.hier_sgd_fused_mix16("bf16", x, v, g, *sgd, P, G, so, pe) if wide else \
-                (once(t) for t in O.hier_sgd_fused_mix_f64(x, v, g, *sgd, P, G, so, pe))
-        assert same_bits(host(vd)[:, :P], wv[:, :P])
-    if wide:
-        assert (host(a).view(np.uint16)[:, :P] == want[:, :P]).all()
-    else:
-        assert same_bits(host(a)[:, :P], want[:, :P])
+    in_place_equals_the_oracle(kind, G, n, P, ld, np.array([0, P // 3 + 1, P // 3 + 1, P - 2, P], dtype=np.int64))

@@ -58,7 +58,7 @@ def test_no_mixing_kernel_keeps_registers_in_scratch(kernels):
 
 
 def test_no_kernel_of_split_rows_keeps_registers_in_scratch(kernels):
-    """Nor more registers than its largest workgroup leaves a wavefront (kPartWaves in cx_launch.hpp)."""
+    """Nor more registers than its largest workgroup leaves a wavefront (kPartWaves in cx_kernels.hpp)."""
     parts = {name: value for name, value in kernels.items() if name.startswith("parts_kernel<")}
     assert len(parts) > 50 and not {name: scratch for name, (_, scratch) in parts.items() if scratch}
     assert parts["parts_kernel<MeanOp<1>, 1, 4>"][0] <= 128 and parts["parts_kernel<FusedOp, 1, 2>"][0] <= 128
