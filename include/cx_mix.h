@@ -132,7 +132,7 @@ int cx_topology_gen(uint64_t seed, int32_t n, int32_t S, int32_t round0, int32_t
  * host copy before uploading it.
  * cx_check_segments: 0 = seg_off[0] <= seg_off[1] <= ... <= seg_off[S] = P, else CX_ERR_SEGMENTS.
  * cx_check_peers: peers_host is int32 [S][n]; `mode` names the kind of table, which is also what
- * the two kernels accept:
+ * the kernels accept:
  *   CX_TOPO_FAIR, CX_TOPO_DIRECTED_EXP  every peers[s] is a permutation of 0..n-1 without a fixed
  *       point (Section 3.2: every row is chosen exactly once and nobody chooses itself).  This is
  *       what a call that updates its matrix IN PLACE needs: in place, a segment whose table is not
@@ -167,7 +167,9 @@ int cx_gossip_mix(const float *x_in, float *x_out, int64_t ld, int32_t W, int64_
  * address the library asks the runtime for once per device.  The call makes no hipMalloc /
  * hipFree and no allocating library call; it enqueues two kernels on `stream`.
  *   x_out must differ from x_in (CX_ERR_ALIAS otherwise: the in-place kernel has no scratch).
- *   The table needs W words per cluster of 65,536 columns (8 clusters side by side):
+ *   The table holds the rows' order once per cluster of 65,536 columns (8 clusters side by side), or, with one segment
+ *   or many segment edges, once per segment and one word per tile where that fits.  The limit is the first layout's,
+ *   W words per cluster, whichever a call takes:
  *   CX_ERR_SHAPE if ceil(P / 1024) > 64 * (CX_NOALLOC_ORDER_WORDS / W - 8), e.g. P > 133 M columns
  *   at W = 128 or P > 16 M at W = 1024 -- the call never falls back to a slower path silently.
  *   (Launch parameters changed through cx_set_tuning move this limit.)

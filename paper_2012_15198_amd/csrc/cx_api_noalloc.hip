@@ -1,14 +1,15 @@
 // C-ABI entry point cx_gossip_mix_noalloc: cx_gossip_mix for callers that cannot allocate (see
-// include/cx_mix.h).  Its only scratch -- the row-order table that order_kernel writes and
-// gather_kernel reads -- is a file-scope device array of a fixed size; the kernels receive its
+// include/cx_mix.h).  Its only scratch -- the row-order table that order_kernel or segment_order_kernel writes
+// and gather_kernel reads -- is a file-scope device array of a fixed size; the kernels receive its
 // device address as an argument.
 #include "cx_launch.hpp"
 
 namespace {
 
 // One table per GPU, held until the process ends.  Nothing in it has to start at zero: a call
-// rewrites every word it later reads (one word per cluster and row of its own geometry) and
-// reads no other, so the leftovers of an earlier, larger call are never looked at.
+// rewrites every word it later reads (of its own geometry: one per cluster and row, or one per segment and row
+// and, for several segments, one per tile; try_gather chooses) and reads no other, so the leftovers of an earlier,
+// larger call are never looked at.  The largest call is the one whose words per cluster and row fit, in either layout.
 static __device__ __align__(256) unsigned scratch[CX_NOALLOC_ORDER_WORDS];
 
 // In host code `scratch` is only a handle for the runtime: the array's device address comes from

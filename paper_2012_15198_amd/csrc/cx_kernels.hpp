@@ -1,8 +1,8 @@
 // Device half of the gossip-mixing library for gfx950 (MI355X): the mixing kernels behind
 // cx_gossip_mix / cx_hier_mix / cx_pushsum_mix / cx_sgd_fused_mix / cx_hier_sgd_fused_mix and
 // their 16-bit variants.  Internal header; the pieces: cx_tile.hpp (slices, tiles, fp32 row
-// accesses), cx_ops.hpp and cx_ops16.hpp (the row operators), this file (the two kernels and the
-// order kernel), cx_launch.hpp (launch shapes, the row-order table's slots, argument checks;
+// accesses), cx_ops.hpp and cx_ops16.hpp (the row operators), this file (the three mixing kernels and the
+// two that write the row order), cx_launch.hpp (launch shapes, the row-order table's slots, argument checks;
 // the header each cx_api_*.hip includes).  Everything has internal linkage.
 //
 // Mixing is independent per column and every element has to be read once and written once
@@ -552,7 +552,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void gather_kernel(
     // own rows before the partner's are requested, which halves the registers in flight.  Boundary tiles always
     // do, and form the rows' addresses anew for each phase: they are few, but the kernel is given the registers of
     // its hungriest path, and with fewer wavefronts per SIMD every tile runs slower.  Against both rows at once, with
-    // their addresses kept: mean of groups of 2 85 -> 72 registers, gradient step of groups of 3 171 -> 118;
+    // their addresses kept: mean of groups of 2 85 -> 72 registers, gradient step of groups of 3 171 -> 118.
     int row = blockIdx.y;
     typename Op::template Raw<U> mine;
     auto mix_and_store = [&](auto mode_c, int64_t at, const unsigned (&m)[U], int peer) {

@@ -375,7 +375,7 @@ struct HierFusedOp {
 
 // The weights of push-sum, w_out[i] = (w_in[i] + w_in[(i - hop) mod n]) * 0.5f.  The de-biasing of a row divides by its new
 // weight; the first workgroup of the launch also writes them (a launch of its own in front of the mix cost as much as
-// the mix on small matrices: 8 x 20,011 fp32 15.3 / 8.0 us.  Written beside the row's column 0 instead, in store(), the
+// the mix on small matrices: 8 x 20,011 fp32 15.3 / 8.3 us.  Written beside the row's column 0 instead, in store(), the
 // branch cost the in-place walk its rows in flight: 64 x 300,007 fp32 without the copy 37 / 55).
 struct PushWeights {
     const float *in;
@@ -411,8 +411,9 @@ struct PushOp {
     template <int U> using Work = Tile<U>;                 // fp32 values a lane works on
     static constexpr int kRawPerSlice = 1;
     static constexpr GatherShape kGather{2, 4, 512, 0};
-    // Out of place with the copy, five workgroups on a CU instead of six: 128 x 1,500,013 398 -> 389 us, 16 x 25,557,032
-    // 879 -> 848; without it as many as fit (16 x 25,557,032 549 / 555).
+    // Out of place with the copy, five workgroups on a CU instead of as many as fit (six): 1 to 5 % on every shape of seven,
+    // most on many rows (500 x 300,007 347 -> 331 us, 128 x 1,500,013 407 -> 396, 16 x 25,557,032 859 -> 843, 128 x 11,689,513
+    // 3,080 -> 3,049).  Without it no cap of four or more moves a shape by more than 3 %, either way.
     constexpr int gather_wgs_per_cu() const { return zout ? 5 : kGather.wgs_per_cu; }
     static constexpr WalkShape kWalk{2, 8, 8, 2};
     template <int U> struct Raw { Tile<U> x; };

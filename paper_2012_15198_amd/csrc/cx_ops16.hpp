@@ -218,6 +218,8 @@ template <bool IEEE_HALF>
 struct Push16Op : Row16Op<IEEE_HALF, 1> {
     using Base = Row16Op<IEEE_HALF, 1>;
     static constexpr GatherShape kGather{2, 4, 192, 0};    // measured on C4: one slice per lane 52 %, two 76 %
+    // (as many workgroups on a CU as fit, with the copy too: caps of four to eight within 1 % on long rows, 128 x 11,689,513
+    // 1,677 to 1,685 us, and slower on short ones, 500 x 300,007 181 with none, 275 with five)
     static constexpr WalkShape kWalk{2, 4, 8, 2};
     template <int U, int D> static constexpr bool kSpills = U * D >= 16;
     // With the copy, as in PushOp: 64 x 6,000,003 449 us with one slice, 564 with two (as short rows take it);
