@@ -201,8 +201,8 @@ Op with_stage_base(const Op &op, size_t base)
 // groups behind its rows may name a shorter visit for tables of few gossiping rows.  A pair that closes
 // a cycle finds its partner in L2 only if all visits in between are still there: with at most
 // kFewRows rows the longest cycle's visits fit one XCD's 4 MB L2 at the short length (measured, 8 leaders:
-// L2-miss traffic 1.060 -> 1.019 x algorithmic, +0.8 points); with more rows they cannot fit anyway and
-// the long visit's DRAM locality wins (32 leaders: 77.1 % at 768 KB against 76.3 % at 384 KB).
+// L2-miss traffic 1.062 -> 1.016 x algorithmic, +0.8 points); with more rows they cannot fit anyway and
+// the length counts for little (32 leaders: 768 KB against 384 KB 77.0 and 76.3 % on one box, 76.1 and 76.5 % on another).
 constexpr int kFewRows = 8;
 template <class Op, class = void>
 struct VisitKb {
