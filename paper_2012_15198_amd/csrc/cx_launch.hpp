@@ -276,6 +276,7 @@ constexpr int64_t kMinChunks = 104;
 // thread: 512 rows 9.5 us with 256 threads, 7.4 with 512; the call on 512 x 100,003
 // fp32 98.3 / 96.4, on 1,000 x 30,011 68.6 / 62.8.
 constexpr int order_threads(int n) { return n <= 256 ? 256 : n <= 512 ? 512 : 1024; }
+constexpr int64_t kCachedBytes = 64LL << 20;              // a matrix that the last-level cache holds, and its copy
 constexpr int kTileOrder = 16;                            // see by_tile in try_gather
 template <class Op, int U>
 constexpr int gather_waves(int64_t P, int waves)
@@ -301,15 +302,22 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     const int full_waves = waves;
     if (!waves_fixed && xcd_aware) waves = gather_waves<Op, U>(a.P, waves);
     const int64_t chunk_cols = static_cast<int64_t>(kWave) * Op::kElems * U * waves;
-    const int64_t nchunks = (a.P + chunk_cols - 1) / chunk_cols;
-    if (nchunks < 8) xcd_aware = 0;               // fewer chunks than XCDs: rows go round the XCDs instead
-    const int nxcd = xcd_aware ? 8 : 1;
+    const int64_t matrix_bytes = static_cast<int64_t>(a.n) * a.rows_per_gossip_row * a.P * (16 / Op::kElems);
     // Rows in cycle order pay when the partner's fetch has to be kept out of HBM; a matrix that
     // the last-level cache holds whole gains nothing from the extra launch.
-    const int64_t matrix_bytes = static_cast<int64_t>(a.n) * a.rows_per_gossip_row * a.P * (16 / Op::kElems);
     const bool own_table = a.order_provider != nullptr;
     bool ordered = a.n > 1 && a.S <= 4096 &&
-                   (own_table || cx_get_tuning(8) == 1 || (cx_get_tuning(8) != 0 && matrix_bytes > (64LL << 20)));
+                   (own_table || cx_get_tuning(8) == 1 || (cx_get_tuning(8) != 0 && matrix_bytes > kCachedBytes));
+    // Rows that begin inside a line keep to their lines where they are in cycle order too: what the cache holds whole loses by
+    // the one chunk more that a row may need (fp32 gossip on 700 x 3,003 9.1 / 9.4 us, on 8 x 1,000,001 13.0 / 13.5).  A tile
+    // must not reach over both ends of a row, a group's rows begin on different columns of a line, and a table of the
+    // caller's holds what it was sized for.
+    const bool on_lines = ((reinterpret_cast<uintptr_t>(op.xout) | static_cast<uint64_t>(op.ld) * (16 / Op::kElems)) & (kLineBytes - 1)) == 0;
+    const bool lines = Op::kRows == 1 && !on_lines && ordered && !own_table && a.P >= 2 * kWave * Op::kElems * U;
+    const int slack = lines ? kLineSlack<Op> : 0;
+    const int64_t nchunks = (a.P + slack + chunk_cols - 1) / chunk_cols;
+    if (nchunks < 8) xcd_aware = 0;               // fewer chunks than XCDs: rows go round the XCDs instead
+    const int nxcd = xcd_aware ? 8 : 1;
     if (own_table && !ordered) { *status = CX_ERR_SHAPE; return true; }
     std::lock_guard<std::mutex> enqueue_lock(enqueue_mutex());
     unsigned *order = nullptr;
@@ -378,13 +386,13 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     }
     if (by_tile) {
         hipLaunchKernelGGL(segment_order_kernel, dim3(a.S), dim3(order_threads(a.n)), sizeof(int) * kScheduleWords(a.n), a.stream, a.n, a.P, a.S,
-                           a.seg_off, a.peers, a.shift, __builtin_ctz(kWave * Op::kElems * U), order);
+                           a.seg_off, a.peers, a.shift, __builtin_ctz(kWave * Op::kElems * U), slack, order);
         if (hipGetLastError() != hipSuccess) { *status = CX_ERR_HIP; return true; }
     } else if (ordered) {
         const int64_t nclusters = clusters * nxcd;
         hipLaunchKernelGGL(order_kernel, dim3(a.S), dim3(order_threads(a.n)), sizeof(int) * kScheduleWords(a.n), a.stream, a.n,
                            a.P, a.S, a.seg_off, a.peers, a.shift, cl * chunk_cols, static_cast<int>(nclusters),
-                           order);
+                           slack, order);
         if (hipGetLastError() != hipSuccess) { *status = CX_ERR_HIP; return true; }
     }
     int cap = cx_get_tuning(9);
@@ -393,16 +401,21 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     if (U == 1 && staged_shape<Op>(waves) && glds < LdsStaged<Op>::bytes) glds = LdsStaged<Op>::bytes;
     if (glds < static_cast<size_t>(StageBytes<Op>::value) * waves) glds = static_cast<size_t>(StageBytes<Op>::value) * waves;
     const Op staged = with_stage_base(op, 0);
-    const auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, glds, a.stream, staged, a.n, a.P, a.S, a.seg_off, a.peers, a.shift,
+    const auto launch = [&](auto kernel, const auto &rows) {
+        hipLaunchKernelGGL(kernel, grid, block, glds, a.stream, rows, a.n, a.P, a.S, a.seg_off, a.peers, a.shift,
                            a.skip_mix, static_cast<unsigned>(nchunks), static_cast<unsigned>(cl),
                            static_cast<unsigned>(waves), xcd_shift, order,
                            by_tile ? 1 : 0);
     };
     if (a.P < Op::kElems) {
-        if constexpr (U == 1) launch(gather_kernel<Op, U, false, true>);
-    } else if (nt) launch(gather_kernel<Op, U, true>);
-    else launch(gather_kernel<Op, U, false>);
+        if constexpr (U == 1) launch(gather_kernel<Op, U, false, true>, staged);
+    } else if (lines) {
+        if constexpr (Op::kRows == 1) {
+            if (nt) launch(gather_kernel<OnLines<Op>, U, true>, OnLines<Op>{staged});
+            else launch(gather_kernel<OnLines<Op>, U, false>, OnLines<Op>{staged});
+        }
+    } else if (nt) launch(gather_kernel<Op, U, true>, staged);
+    else launch(gather_kernel<Op, U, false>, staged);
     *status = hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
     return true;
     }

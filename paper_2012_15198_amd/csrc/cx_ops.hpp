@@ -56,6 +56,7 @@ constexpr int ring_for(int n) { return n >= 128 ? 8 : 4; }
 // the result.  The kernel is bound by HBM bandwidth; the fp64 rate is not what limits it.
 template <int G>
 struct MeanOp {
+    static constexpr int kRows = G;                       // matrix rows behind a gossiping row
     static constexpr int kElems = 4;                       // fp32 columns per 16-byte slice
     template <int U> using Work = std::conditional_t<G == 1, Tile<U>, WideTile<U>>;
     static constexpr int kRawPerSlice = G;
@@ -255,6 +256,7 @@ struct SgdStep {
 };
 
 struct FusedOp {
+    static constexpr int kRows = 1;                       // matrix rows behind a gossiping row
     static constexpr int kElems = 4;                       // fp32 columns per 16-byte slice
     template <int U> using Work = WideTile<U>;             // the updated row, in fp64
     static constexpr int kRawPerSlice = 3;
@@ -313,6 +315,7 @@ struct FusedOp {
 // FusedOp: the gradients are summed in row order starting from zero and divided by G.
 template <int G>
 struct HierFusedOp {
+    static constexpr int kRows = G;                       // matrix rows behind a gossiping row
     static constexpr int kElems = 4;                       // fp32 columns per 16-byte slice
     template <int U> using Work = WideTile<U>;             // the updated leader row, in fp64
     static constexpr int kRawPerSlice = G + 2;
@@ -407,6 +410,7 @@ struct OncePerLaunch<Op, std::void_t<decltype(std::declval<const Op &>().weights
 
 // Push-sum: plain rows, optional de-biased copy z = x' / w'.
 struct PushOp {
+    static constexpr int kRows = 1;                       // matrix rows behind a gossiping row
     static constexpr int kElems = 4;                       // fp32 columns per 16-byte slice
     template <int U> using Work = Tile<U>;                 // fp32 values a lane works on
     static constexpr int kRawPerSlice = 1;

@@ -121,6 +121,7 @@ __device__ __forceinline__ f4 narrow16_once(const d4 &lo, const d4 &hi)
 // format on the way out.
 template <bool IEEE_HALF, int G = 1>
 struct Row16Op {
+    static constexpr int kRows = G;                       // matrix rows behind a gossiping row
     static constexpr int kElems = 8;                       // 16-bit columns per 16-byte slice
     template <int U> using Work = std::conditional_t<G == 1, Tile<2 * U>, WideTile<2 * U>>;   // 8 values per slice
     static constexpr int kRawPerSlice = G;
@@ -357,6 +358,7 @@ __device__ __forceinline__ void stage_from_own(f4 *stage, Tile<2 * U> &t)
 // cx_sgd_fused_mix_bf16 / _f16: FusedOp with 16-bit x and g rows and fp32 momentum rows.
 template <bool IEEE_HALF>
 struct Fused16Op {
+    static constexpr int kRows = 1;                       // matrix rows behind a gossiping row
     static constexpr int kElems = 8;                       // 16-bit columns per 16-byte slice
     template <int U> using Work = WideTile<2 * U>;         // the updated row, 8 doubles per slice
     static constexpr int kRawPerSlice = 4;                 // x, g: one register each; v: two
@@ -413,6 +415,7 @@ struct Fused16Op {
 // cx_hier_sgd_fused_mix_bf16 / _f16: HierFusedOp with 16-bit x and g rows, fp32 leader momentum.
 template <bool IEEE_HALF, int G>
 struct HierFused16Op {
+    static constexpr int kRows = G;                       // matrix rows behind a gossiping row
     static constexpr int kElems = 8;
     template <int U> using Work = WideTile<2 * U>;
     static constexpr int kRawPerSlice = G + 3;             // G gradient rows, x, and two registers of v
