@@ -409,6 +409,11 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     };
     if (a.P < Op::kElems) {
         if constexpr (U == 1) launch(gather_kernel<Op, U, false, true>, staged);
+    } else if (std::is_same_v<Op, MeanOp<1>> && nt && ordered && (lines || (on_lines && matrix_bytes > kCachedBytes))) {
+        if constexpr (std::is_same_v<Op, MeanOp<1>>) {
+            if (lines) launch(gather_kernel<OnLines<ThroughOp>, U, true>, OnLines<ThroughOp>{{staged}});
+            else launch(gather_kernel<ThroughOp, U, true>, ThroughOp{staged});
+        }
     } else if (lines) {
         if constexpr (Op::kRows == 1) {
             if (nt) launch(gather_kernel<OnLines<Op>, U, true>, OnLines<Op>{staged});

@@ -129,6 +129,27 @@ struct MeanOp {
     }
 };
 
+// Plain gossip out of place whose wavefronts store whole lines, to matrices that the last-level cache does not hold: the lines
+// go to memory in the order in which they are made, not in that in which L2 gives them up, which DRAM serves faster.
+// Non-temporal / written through, us: 32 x 25,557,032 1,088 / 1,067; 4 x 25,557,032 inside lines 154 / 141; 64 x 11,689,512
+// 997 / 983; 1,024 x 1,200,003 1,671 / 1,655; 100 x 200,003 31.1 / 30.7; 512 x 100,003 94.3 / 94.1.  What L2 would have
+// merged must not go out by itself (8 x 1,000,001 inside lines, wavefronts in the column grid, 13.0 / 15.1; in-place walks 1 to
+// 12 % slower), and other operators gain nothing: optimizer step on 64 x 5,000,001 1,144 / 1,165, push-sum on
+// 128 x 1,689,513 291 / 296, bf16 gossip on 32 x 25,557,032 551 / 554, mean of groups of 8 on 64 x 11,689,512 1,057 / 1,056.
+struct ThroughOp : MeanOp<1> {
+    template <int U, TileMode MODE, bool NT>
+    __device__ __forceinline__ void store(int row, int64_t off, const unsigned (&mask)[U], const Tile<U> &t) const
+    {
+        float *p = xout + static_cast<int64_t>(row) * ld + off;
+        if constexpr (MODE == kFull && NT) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) store_through(reinterpret_cast<f4 *>(p + u * 256), t.v[u]);
+        } else {
+            tile_store<U, MODE, NT>(p, mask, t);
+        }
+    }
+};
+
 // The hierarchical mean staged through LDS, kept for measurement next to the sum in registers (launch
 // parameter 10).  A workgroup is G wavefronts and owns G tiles of 256 columns; wavefront j fetches
 // row j of its group and of the partner group (G contiguous 1-KB loads each), the rows meet in

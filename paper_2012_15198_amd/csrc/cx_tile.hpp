@@ -142,6 +142,13 @@ __device__ __forceinline__ void tile_store(float *p, const unsigned (&mask)[U], 
     }
 }
 
+// A whole slice to memory at once (sc1) instead of when its line leaves L2, and the line not kept (nt).
+__device__ __forceinline__ void store_through(f4 *p, const f4 &v)
+{
+    // s_nop: the registers of a store of 16 bytes may be written from the second instruction after it on
+    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+
 }  // namespace
 
 #endif  // CX_TILE_HPP
