@@ -63,11 +63,13 @@ namespace {
 // The two groups that build schedules: one wavefront in its private LDS region, or a workgroup.
 struct WaveSync {
     __device__ __forceinline__ void sync() const { wave_sync(); }
-    __device__ __forceinline__ void add(int *p, int v) const { atomicAdd(p, v); }
+    __device__ __forceinline__ int add(int *p, int v) const { return atomicAdd(p, v); }
+    __device__ __forceinline__ void claim(int *p, int v) const { *p = v; }
 };
 struct BlockSync {
     __device__ __forceinline__ void sync() const { __syncthreads(); }
-    __device__ __forceinline__ void add(int *p, int v) const { atomicAdd(p, v); }
+    __device__ __forceinline__ int add(int *p, int v) const { return atomicAdd(p, v); }
+    __device__ __forceinline__ void claim(int *p, int v) const { *p = v; }
 };
 
 // One lane's walk over all cycles of the schedule.  Rows are fetched in schedule order, each exactly
@@ -215,8 +217,12 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
         const int64_t e = (s == S - 1) ? P : seg_off[s + 1];
         if (g1 <= P && b <= g0 && e >= g1) {
             const int *sched = lds + n;
-            if (wave == 0) build_schedule(lds, n, lane, kWave, peers, s, shift, WaveSync{});
-            __syncthreads();
+            if (n > kWave) {
+                schedule_rows(lds, n, static_cast<int>(threadIdx.x), static_cast<int>(blockDim.x), peers, s, shift, BlockSync{});
+            } else {
+                if (wave == 0) schedule_rows(lds, n, lane, kWave, peers, s, shift, WaveSync{});
+                __syncthreads();
+            }
             unsigned mask[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) mask[u] = (1u << kSliceCols) - 1u;
@@ -260,7 +266,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
     const int64_t place = column_of<Op>(c0, lane, 0, 0);
     // this lane's first column
     const int64_t off = place - (SHORT ? 0 : row_end_slide(P, c0, place, U, kTileCols, kSliceCols));
-    build_schedule(work, n, lane, kWave, peers, s, shift, WaveSync{});
+    schedule_rows(work, n, lane, kWave, peers, s, shift, WaveSync{});
     unsigned mask[U];
     if (e - b == kTileCols) {
 #pragma unroll
@@ -363,7 +369,7 @@ __global__ __launch_bounds__((kWave * kPartWaves<Op, U, D>)) void parts_kernel(
     int64_t e = bound(s + 1);
     if (e > c0 + block_cols) e = c0 + block_cols;
     if (b >= e) return;
-    build_schedule(lds, n, static_cast<int>(threadIdx.x), static_cast<int>(blockDim.x), peers, s, shift, BlockSync{});
+    schedule_rows(lds, n, static_cast<int>(threadIdx.x), static_cast<int>(blockDim.x), peers, s, shift, BlockSync{});
     const SchedulePart part = schedule_part(lds, n, wave / tiles, parts, lane, kWave,
                                             [](bool c) { return __builtin_amdgcn_ballot_w64(c); });
     c0 += static_cast<int64_t>(wave % tiles) * kTileCols;
@@ -417,20 +423,15 @@ constexpr unsigned kOrderOneSegment = 1u << (2 * kOrderRowBits);
 constexpr unsigned kLineBytes = 128;
 __device__ __align__(256) unsigned g_order[kOrderSlots][kOrderEntries];
 
-// The row that gossiping row `row` averages with in segment s (Algorithm 1: receive_from):
-// the fixed shift of the push-sum schedule, or the peer table's entry; an entry outside
-// [0, n) means the row itself.
-__device__ __forceinline__ int partner_of(const int32_t *__restrict__ peers, int shift, int n, int s, int row)
+__device__ __forceinline__ unsigned order_word(const Place &p, int row)
 {
-    int peer = row;
-    if (shift > 0) peer = row >= shift ? row - shift : row - shift + n;
-    else if (peers) peer = peers[static_cast<int64_t>(s) * n + row];
-    if (static_cast<unsigned>(peer) >= static_cast<unsigned>(n)) peer = row;
-    return peer;
+    return static_cast<unsigned>(row) | (static_cast<unsigned>(p.partner) << kOrderRowBits);
 }
 
-// One workgroup per segment: builds the segment's cycle schedule and writes it as the row
-// order of every cluster whose first column lies in that segment.
+// One workgroup per segment: builds the segment's row order and writes it for every cluster whose first
+// column lies in that segment.  With build_schedule and the partners read again / now, us: 32 rows in 8 segments 6.7 / 5.8;
+// segment_order_kernel below, 512 rows in 16 segments 6.4 / 4.8; the call on 512 x 100,003 fp32 93.4 / 91.6, on 512 x 50,003
+// 52.9 / 50.9, on 900 x 50,003 bf16 48.4 / 45.1.
 __global__ __launch_bounds__(1024) void order_kernel(int n, int64_t P, int S,
                                                     const int64_t *__restrict__ seg_off,
                                                     const int32_t *__restrict__ peers, int shift,
@@ -438,28 +439,27 @@ __global__ __launch_bounds__(1024) void order_kernel(int n, int64_t P, int S,
                                                     unsigned *__restrict__ order)
 {
     extern __shared__ int lds[];
-    const int *sched = lds + n;
     const int s = blockIdx.x;
-    build_schedule(lds, n, static_cast<int>(threadIdx.x), static_cast<int>(blockDim.x), peers, s, shift, BlockSync{});
     int64_t sb = (s == 0) ? 0 : seg_off[s];
     int64_t se = (s == S - 1) ? P : seg_off[s + 1];
     sb = sb < 0 ? 0 : (sb > P ? P : sb);
     se = se < 0 ? 0 : (se > P ? P : se);
+    const int row = static_cast<int>(threadIdx.x);         // a thread for every row: order_threads
+    const Place p = place_row(lds, n, row, peers, s, shift, BlockSync{});
+    unsigned *words = reinterpret_cast<unsigned *>(lds);
+    if (row < n) words[p.at] = order_word(p, row);
+    __syncthreads();
     const int64_t c_lo = (sb + cluster_cols - 1) / cluster_cols;
     int64_t c_hi = (se + (s == S - 1 ? slack : 0) + cluster_cols - 1) / cluster_cols;
     if (c_hi > nclusters) c_hi = nclusters;
-    // the table as the schedule was built from it: a table that is not a permutation has become
-    // the identity there, but the gather serves it as written, so partners come from the source
     const unsigned un = static_cast<unsigned>(n);
     const unsigned total = static_cast<unsigned>(c_hi > c_lo ? c_hi - c_lo : 0) * un;   // fits: the table does
     for (unsigned idx = threadIdx.x; idx < total; idx += blockDim.x) {
         const unsigned k = idx % un;
         const int64_t c = c_lo + idx / un;
-        const int row = sched[k] & kRowMask;
         const int64_t first_col = c * cluster_cols - slack > 0 ? c * cluster_cols - slack : 0;
         const int64_t last_col = (c + 1) * cluster_cols < P ? (c + 1) * cluster_cols : P;
-        unsigned e = static_cast<unsigned>(row) |
-                     (static_cast<unsigned>(partner_of(peers, shift, n, s, row)) << kOrderRowBits);
+        unsigned e = words[k];
         if (first_col >= sb && last_col <= se) e |= kOrderOneSegment;
         order[c * n + k] = e;
     }
@@ -478,18 +478,14 @@ __global__ __launch_bounds__(1024) void segment_order_kernel(int n, int64_t P, i
                                                             int slack, unsigned *__restrict__ order)
 {
     extern __shared__ int lds[];
-    const int *sched = lds + n;
     const int s = blockIdx.x;
-    build_schedule(lds, n, static_cast<int>(threadIdx.x), static_cast<int>(blockDim.x), peers, s, shift, BlockSync{});
-    for (int k = threadIdx.x; k < n; k += blockDim.x) {
-        const int row = sched[k] & kRowMask;
-        order[static_cast<unsigned>(s) * n + k] = static_cast<unsigned>(row) |
-            (static_cast<unsigned>(partner_of(peers, shift, n, s, row)) << kOrderRowBits);
-    }
     int64_t sb = (s == 0) ? 0 : seg_off[s];
     int64_t se = (s == S - 1) ? P : seg_off[s + 1];
     sb = sb < 0 ? 0 : (sb > P ? P : sb);
     se = se < 0 ? 0 : (se > P ? P : se);
+    const int row = static_cast<int>(threadIdx.x);
+    const Place p = place_row(lds, n, row, peers, s, shift, BlockSync{});
+    if (row < n) order[static_cast<unsigned>(s) * n + p.at] = order_word(p, row);
     if (S == 1) return;
     unsigned *tiles = order + static_cast<unsigned>(S) * n;
     const int64_t tile_cols = static_cast<int64_t>(1) << tile_shift;

@@ -99,6 +99,92 @@ CX_SCHED_FN void build_schedule(int *work, int n, int tid, int nthreads, const i
 }
 
 // ---------------------------------------------------------------------------------
+// The row that gossiping row `row` averages with in segment s (Algorithm 1: receive_from):
+// the fixed shift of the push-sum schedule, or the peer table's entry; an entry outside
+// [0, n) means the row itself.
+CX_SCHED_FN int partner_of(const int32_t *__restrict__ peers, int shift, int n, int s, int row)
+{
+    int peer = row;
+    if (shift > 0) peer = row >= shift ? row - shift : row - shift + n;
+    else if (peers) peer = peers[static_cast<int64_t>(s) * n + row];
+    if (static_cast<unsigned>(peer) >= static_cast<unsigned>(n)) peer = row;
+    return peer;
+}
+
+// The place of row `i` in the cycle order of segment s, the cycles in any order, for a group with a thread for every row
+// (threads without one come along for the syncs).  `work` holds kScheduleWords(n) ints, of which the first n stay as they are.
+//
+// build_schedule orders the cycles as well and serves fewer threads than rows: with a thread for each row the row's own word
+// stays in a register, one write and one read tell whether the table is a permutation, and an atomic places a cycle where
+// a prefix sum did: 12 syncs instead of 24 at 512 rows.  `group.add` returns what was there, `group.claim(p, v)` is *p = v
+// where several threads may write the same word.
+struct Place {
+    int partner;                           // as the table has it, entries outside [0, n) the row itself
+    int at;                                // a table that is not a permutation: every row a cycle of its own
+    bool last, permutation;                // last of its cycle
+};
+template <class Group>
+CX_SCHED_FN Place place_row(int *work, int n, int i, const int32_t *__restrict__ peers, int s, int shift, Group group)
+{
+    int *claimed = work + n, *a = work + 2 * n, *b = work + 3 * n, *state = work + 4 * n;   // state: not a permutation, rows placed
+    const bool mine = i < n;
+    if (i < 2) state[i] = 0;
+    int to = i, w = 0;
+    bool in_range = true;
+    if (mine) {
+        to = partner_of(peers, shift, n, s, i);
+        in_range = shift > 0 || !peers || peers[static_cast<int64_t>(s) * n + i] == to;
+        group.claim(&claimed[to], i);             // one of a row's claimants stays
+        // successor after `span` steps | smallest row among the next `span` rows of the cycle, i included | distance to it
+        w = to | (i << kRowBits);
+        a[i] = w;
+    }
+    group.sync();
+    if (mine && !(in_range && claimed[to] == i)) group.add(&state[0], 1);
+    group.sync();
+    if (state[0] != 0) return Place{to, i, true, false};   // the group's threads together
+    for (int span = 1; span < n; span <<= 1) {
+        if (mine) {
+            const int ahead = a[w & kRowField];
+            int least = (w >> kRowBits) & kRowField, d = w >> (2 * kRowBits);
+            const int other = (ahead >> kRowBits) & kRowField;
+            if (other < least) { least = other; d = span + (ahead >> (2 * kRowBits)); }
+            w = (ahead & kRowField) | (least << kRowBits) | (d << (2 * kRowBits));
+            b[i] = w;
+        }
+        group.sync();
+        int *t = a; a = b; b = t;
+    }
+    const int least = (w >> kRowBits) & kRowField, d = w >> (2 * kRowBits);
+    if (mine && least == i) {                              // its successor is as far from it as the cycle is long, less one
+        const int length = (a[to] >> (2 * kRowBits)) + 1;
+        b[i] = group.add(&state[1], length) | (length << kRowBits);
+    }
+    group.sync();
+    const int cycle = mine ? b[least] : 0, first = cycle & kRowField, length = cycle >> kRowBits;
+    return Place{to, d == 0 ? first : first + length - d, to == least, true};
+}
+
+// The schedule of segment s in `work`, as build_schedule lays it out: by place_row where the group has a thread for every
+// row.  In place, us, build_schedule / this: fp32 gossip on 512 x 3,001 25.5 / 23.3, 256 x 30,011 21.6 / 20.0, 12 x 400,007
+// 11.5 / 10.6, 300 x 100,003 56.8 / 54.8; bf16 gossip on 355 x 50,356 27.4 / 25.4, on 32 x 25,557,032 596 / 591.
+template <class Group>
+CX_SCHED_FN void schedule_rows(int *work, int n, int tid, int nthreads, const int32_t *__restrict__ peers, int s,
+                                              int shift, Group group)
+{
+    if (n > nthreads) {
+        build_schedule(work, n, tid, nthreads, peers, s, shift, group);
+        return;
+    }
+    const Place p = place_row(work, n, tid, peers, s, shift, group);
+    if (tid < n) {
+        work[tid] = p.permutation ? p.partner : tid;
+        work[n + p.at] = tid | (p.last ? kLastBit : 0);
+    }
+    group.sync();
+}
+
+// ---------------------------------------------------------------------------------
 // A schedule walked in parts, each by a wavefront of its own and all of them at once: part q of Q takes the positions
 // [n*q/Q, n*(q+1)/Q).  In place, a part's walk needs two rows that another part overwrites, and reads them before any
 // part stores:

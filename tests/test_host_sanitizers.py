@@ -4,6 +4,7 @@ code the kernels share with the host, and the oracle.  CPU only; every build goe
   * tests/host/schedule_check.cpp: build_schedule (csrc/cx_schedule.hpp) run by a group of real threads
     against a serial cycle walk -- under ThreadSanitizer, where a missing group.sync() is a data race,
     and under AddressSanitizer + UBSan at the largest row count;
+  * tests/host/place_check.cpp: place_row and schedule_rows (csrc/cx_schedule.hpp) with a thread for every row, the same way;
   * tests/host/parts_check.cpp: schedule_part (csrc/cx_schedule.hpp), the rows of a segment mixed in place by parts;
   * tests/host/host_half_check.cpp: csrc/cx_host.cpp and oracle/cx_oracle.c in one ASan + UBSan program:
     topologies of both compared for every mode, the table checkers, every oracle function on exact-size
@@ -47,6 +48,15 @@ def test_cycle_schedule_under_address_sanitizer_at_the_maximum_row_count(tmp_pat
     run(["g++", "-std=c++17", *SAN, "-I", CSRC, os.path.join(HOST, "schedule_check.cpp"), "-o", str(exe), "-lpthread"])
     assert run([str(exe), "7", "1024"], env=ENV).startswith("ok")
     assert run([str(exe), "1", "1024"], env=ENV).startswith("ok")
+
+
+def test_row_order_with_a_thread_for_every_row(tmp_path):
+    for name, flags, sizes in (("tsan", ["-O1", "-g", "-fsanitize=thread"], (["1", "150", "0"], ["2", "70", "5"])),
+                               ("asan", SAN, (["1", "300", "3"], ["1023", "1024", "0"]))):
+        exe = tmp_path / f"place_{name}"
+        run(["g++", "-std=c++17", *flags, "-I", CSRC, os.path.join(HOST, "place_check.cpp"), "-o", str(exe), "-lpthread"])
+        for args in sizes:
+            assert run([str(exe), *args], env=ENV).startswith("ok")
 
 
 def test_rows_mixed_in_place_by_parts(tmp_path):
