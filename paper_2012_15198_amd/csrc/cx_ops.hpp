@@ -61,11 +61,10 @@ struct MeanOp {
     template <int U> using Work = std::conditional_t<G == 1, Tile<U>, WideTile<U>>;
     static constexpr int kRawPerSlice = G;
     // out-of-place launch: slices per lane, waves per workgroup, KB of one visit to a gossiping row
-    // (all G rows behind it) per XCD -- measured optima on MI355X, on matrices spread over the
-    // physical memory (cx_hbm_alloc)
+    // (all G rows behind it) per XCD -- measured optima on MI355X (see VisitKb)
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 4, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0} : GatherShape{1, 8, 768, 0};
-    static constexpr int kVisitKbFewRows = G >= 8 ? 256 : kGather.visit_kb;      // see VisitKb
+    static constexpr int kVisitKbFewRows = G > 8 ? 256 : G == 8 ? 512 : kGather.visit_kb;      // see VisitKb
     static constexpr WalkShape kWalk =
         G == 1 ? WalkShape{2, 8, 8, 2} : G == 2 ? WalkShape{2, 4, 8, 2} : G <= 5 ? WalkShape{2, 2, 8, 2}
         : G <= 8 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
@@ -220,11 +219,21 @@ Op with_stage_base(const Op &op, size_t base)
 }
 
 // Visit length of the out-of-place kernel: the operator's kGather.visit_kb, except that an operator with
-// groups behind its rows may name a shorter visit for tables of few gossiping rows.  A pair that closes
-// a cycle finds its partner in L2 only if all visits in between are still there: with at most
-// kFewRows rows the longest cycle's visits fit one XCD's 4 MB L2 at the short length (measured, 8 leaders:
-// L2-miss traffic 1.062 -> 1.016 x algorithmic, +0.8 points); with more rows they cannot fit anyway and
-// the length counts for little (32 leaders: 768 KB against 384 KB 77.0 and 76.3 % on one box, 76.1 and 76.5 % on another).
+// groups behind its rows may name a shorter visit for tables of few gossiping rows, whose longest cycle's visits then
+// fit one XCD's 4 MB L2 (groups of 16; of the fp32 mean also groups of 8: with more rows 768 KB, 256 x 25,557,032 in 32
+// groups 9,725 us, with 512 KB 9,743).
+//
+// Operators on groups visit 8 or 16 workgroups' chunks of 8 KB of every matrix row: with a power of two the XCDs' visits of a
+// row together begin and end on multiples of 512 KB.  Time with that over the time with the visit before (256 KB at up to
+// 8 gossiping rows, 768 KB or 384 KB of 16-bit rows beyond, of the whole group) on matrices as torch allocates them, groups of 8,
+// 1,000,003 / 4,000,003 / 11,689,512 columns, 8 gossiping rows, then 1,000,003 / 4,000,003 columns, 32 gossiping rows:
+//   fp32 mean             8 chunks   0.978 / 0.987 / 0.976   (unchanged)
+//   16-bit mean          16 chunks   0.968 / 0.986 / 0.978   0.927 / 0.958
+//   fp32 gradient step   16 chunks   0.935 / 0.971 / 0.954   0.974 / 1.001
+//   16-bit gradient step  8 chunks   0.914 / 1.006 / 0.982   0.879 / 0.999
+// (the largest of 4 to 32 gossiping rows 1.026, 16-bit gradient step on 4 groups x 4,000,003).  Groups of 4 of the 16-bit mean, 16
+// chunks for 8: 0.97 to 0.999; groups of 3 to 7 within 0.966 to 1.02.  On matrices spread over the physical memory the fp32 mean
+// on 64 x 11,689,512 loses 0.6 % to 256 KB visits, which keep a cycle's first row in L2 until it closes.
 constexpr int kFewRows = 8;
 template <class Op, class = void>
 struct VisitKb {
@@ -342,8 +351,9 @@ struct HierFusedOp {
     static constexpr int kRawPerSlice = G + 2;
     // out-of-place launch: slices, waves, group visit KB per XCD
     static constexpr GatherShape kGather =
-        G == 1 ? GatherShape{1, 8, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0} : GatherShape{1, 8, 768, 0};
-    static constexpr int kVisitKbFewRows = G >= 8 ? 256 : kGather.visit_kb;      // see VisitKb
+        G == 1 ? GatherShape{1, 8, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0}
+        : G <= 8 ? GatherShape{1, 8, 128 * G, 0} : GatherShape{1, 8, 768, 0};
+    static constexpr int kVisitKbFewRows = G > 8 ? 256 : kGather.visit_kb;       // see VisitKb
     static constexpr WalkShape kWalk = G <= 4 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G <= 2 ? 2 : 1;
     template <int U, int D> static constexpr bool kSpills = G == 5 && D == 4;
