@@ -574,10 +574,6 @@ bool try_parts(const Op &op, const MixArgs &a)
     if constexpr (!PartRing<Op>::kBuilt) {
         return false;
     } else {
-        // launch parameters of the in-place kernel ask for mix_kernel's shapes
-        for (const int key : {0, 1, 2, 3, 4, 9})
-            if (cx_get_tuning(key) != -1) return false;
-        if (a.skip_mix) return false;
         const PartShape s = part_shape(op, a.n, a.P, a.S);
         if (s.parts == 0) return false;
         const int64_t block_cols = static_cast<int64_t>(kWave) * Op::kElems * s.U * s.tiles;
@@ -596,6 +592,58 @@ bool try_parts(const Op &op, const MixArgs &a)
         else launch(parts_kernel<Op, 1, Ring::kShortD>);
         return true;
     }
+}
+
+// ---------------------------------------------------------------------------------
+// In place, many plain rows of medium length: mix_kernel with as many waves a workgroup as deal the tiles out evenly.  A launch
+// lasts as long as the CU with the most slices: ceil(workgroups / CUs) * waves * slices per lane.  Eight waves, or five where
+// many rows' schedules fill the LDS, leave CUs idle (fp32, 300,007 columns: 1,172 tiles are 147 workgroups of eight waves, of
+// the split's four tiles as well, 235 of five), so waves and slices are chosen for the least of that, and of equals the one with
+// fewer, wider workgroups.  From kEvenLoad slices a CU on, below which a CU has too few wavefronts and the split or mix_kernel's
+// short shapes serve, where the other shape is more than kEvenGain per cent off (at 8 slices for 7 the step on 117 x 398,433
+// took 171 us for 166), and up to kEvenRows16 plain 16-bit rows (831 x 943,628 899 us, 738 before).
+// Before / now, us: fp32 optimizer step on 256 x 300,007 342 / 314, on 263 x 589,905 713 / 573; fp32 gossip on 265 x 278,339
+// 136 / 117, on 611 x 512,664 525 / 474; fp32 push-sum on 171 x 1,202,009 321 / 294; bf16 gossip on 118 x 626,350 75 / 60; bf16
+// optimizer step on 158 x 3,248,642 1,553 / 1,351.  Of 110 shapes drawn afterwards (100 to 1,024 rows, 1,024 to 8,000
+// slices) 35 changed by more than 0.6 %: geometric mean 0.947, four above 1.02 (fp32 step on 266 x 324,362 361 / 375).
+// ---------------------------------------------------------------------------------
+constexpr int kEvenRows = 100, kEvenRows16 = 500, kEvenLoad = 5, kEvenMost = 32, kEvenGain = 15;
+
+// Slices on the CU with the most, workgroups of `tiles` tiles of U slices.
+template <class Op>
+constexpr int64_t cu_load(int64_t P, int U, int tiles)
+{
+    const int64_t cols = static_cast<int64_t>(kWave) * Op::kElems * U * tiles, blocks = (P + cols - 1) / cols;
+    return (blocks + kCUs - 1) / kCUs * tiles * U;
+}
+
+template <class Op>
+constexpr WalkShape even_shape(const Op &op, int n, int64_t P, int S)
+{
+    constexpr WalkShape kNone{0, 0, 0, 0};
+    constexpr bool kStep = HasMomentum<Op>::value, kHalf = Op::kElems == 8;
+    if (Op::kRows != 1 || n < kEvenRows || (kHalf && !kStep && n > kEvenRows16) || push_kind(op) == Push::kWithCopy) return kNone;
+    const int64_t slices = (P + kWave * Op::kElems - 1) / (kWave * Op::kElems);
+    if (slices <= (kEvenLoad - 1) * kCUs || slices > kEvenMost * kCUs) return kNone;
+    WalkShape best = kNone;
+    int64_t least = 0;
+    for (int U = 1; U <= Op::kWalk.U; ++U)
+        for (int waves = 3; waves <= waves_with_schedules<Op>(n, kMaxWavesPerBlock); ++waves) {
+            const int64_t load = cu_load<Op>(P, U, waves);
+            if (best.U && (load > least || (load == least && waves * U <= best.waves * best.U))) continue;
+            least = load;
+            best = WalkShape{U, 0, waves, 2};
+        }
+    if (!best.U) return kNone;
+    // where the split serves, few waves of a narrow tile each do not replace it (bf16 optimizer step on 506 x 587,964 943 us
+    // split, 973 with three waves)
+    const PartShape split = part_shape(op, n, P, S);
+    if (split.parts && (kHalf ? best.waves : best.waves * best.U) < kEvenLoad) return kNone;
+    const WalkShape whole = walk_shape(op, n, P);
+    const int64_t usual = split.parts ? cu_load<Op>(P, split.U, split.tiles) : cu_load<Op>(P, whole.U, whole.waves);
+    if (100 * usual <= (100 + kEvenGain) * least) return kNone;
+    best.D = kStep ? (kHalf ? 2 : 4) : push_kind(op) == Push::kPlain && best.U == 2 ? 2 : kHalf ? 4 : 8;
+    return best;
 }
 
 template <class Op>
@@ -625,8 +673,11 @@ int launch_mix(const Op &op, const MixArgs &a)
             try_gather<Op, 4>(op, u, waves, waves_fixed, nt, cl, xcd_aware, a, &status))
             return status;
     }
-    if (try_parts<Op>(op, a)) return hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
-    Launch l = pick_launch(walk_shape(op, a.n, a.P));
+    bool as_tuned = a.skip_mix != 0;                       // launch parameters of the in-place kernel ask for mix_kernel's shapes
+    for (const int key : {0, 1, 2, 3, 4, 9}) as_tuned = as_tuned || cx_get_tuning(key) != -1;
+    const WalkShape even = as_tuned ? WalkShape{0, 0, 0, 0} : even_shape(op, a.n, a.P, a.S);
+    if (!as_tuned && !even.U && try_parts<Op>(op, a)) return hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
+    Launch l = pick_launch(even.U ? even : walk_shape(op, a.n, a.P));
     if (a.P < kSliceLanes * l.U) l.U = 1;
     if (a.P < Op::kElems) l.D = 2;
     const bool done =

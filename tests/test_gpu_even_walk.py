@@ -1,0 +1,50 @@
+"""In place on many plain rows of medium length, where the waves of a workgroup are chosen to deal the tiles out evenly:
+the bits of the out-of-place kernels at both ends of that rule's lengths and rows, and where neither side takes it."""
+import pytest
+import torch
+
+import oracle as O
+from paper_2012_15198_amd import cxmix as cx
+from paper_2012_15198_amd import workloads as WL
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+SGD = (0.1, 0.9, 1e-4)
+
+
+@pytest.mark.parametrize("kind", ["gossip", "step", "push"])
+@pytest.mark.parametrize("rows", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("n,slices,beyond,S", [(100, 1024, 1, 3), (99, 1024, 1, 3), (120, 1172, -25, 8), (101, 1172, 3, 40), (513, 1030, 9, 5),
+                                               (500, 1100, 0, 1)])
+def test_even_walk_equals_the_out_of_place_kernel(kind, rows, n, slices, beyond, S):
+    P = slices * (256 if rows == "f32" else 512) + beyond
+    ld, dtype = (P + 7) // 8 * 8 + 8, {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[rows]
+    suffix = "" if rows == "f32" else "_" + rows
+    print(kind, rows, n, P, S, flush=True)
+
+    def matrix(t, sigma, stream):
+        out = WL.gen_matrix_device(n, P, sigma, 9, ld=ld, stream=stream, device="cuda:0", out=torch.empty((n, ld), dtype=t, device="cuda:0"))
+        out[:, P:] = 7
+        return out
+
+    x, y = matrix(dtype, 0.05, 0), torch.full((n, ld), 7, dtype=dtype, device="cuda:0")
+    so, pe = dev(WL.equal_seg_off(P, S)), dev(O.topology(S, n, S, 0, 1)[0])
+    if kind == "gossip":
+        call = getattr(cx, "cx_gossip_mix" + suffix)
+        call(x, y, P, so, pe)
+        call(x, x, P, so, pe)
+    elif kind == "step":
+        call, v, g = getattr(cx, "cx_sgd_fused_mix" + suffix), matrix(torch.float32, 0.02, 1), matrix(dtype, 0.01, 2)
+        v2 = torch.full_like(v, 7)
+        call(x, y, v, v2, g, *SGD, P, so, pe)
+        call(x, x, v, v, g, *SGD, P, so, pe)
+        assert torch.equal(v.view(torch.int32)[:, :P], v2.view(torch.int32)[:, :P]) and (v[:, P:] == 7).all()
+    else:
+        call, w = getattr(cx, "cx_pushsum_mix" + suffix), torch.rand(n, device="cuda:0") + 0.5
+        w2, w3 = torch.empty_like(w), torch.empty_like(w)
+        call(x, y, w, w2, None, P, 1 + n // 3)
+        call(x, x, w, w3, None, P, 1 + n // 3)
+        assert torch.equal(w2, w3)
+    bits = torch.int32 if rows == "f32" else torch.int16
+    assert torch.equal(x.view(bits)[:, :P], y.view(bits)[:, :P]) and (x[:, P:] == 7).all()
