@@ -18,6 +18,7 @@
 //     in the L2 of one XCD (block b runs on XCD b mod 8; an XCD walks a cluster of
 //     neighbouring chunks row after row; rows follow the cycles of the peer permutation,
 //     so a block's partner is the next block's own row).
+//   * Rows that begin inside a line of 128 bytes: each row's tiles start on the row's own lines (OnLines).
 //   * Long contiguous row visits per XCD keep the DRAM row buffers busy, which a kernel
 //     whose waves each wander over all rows cannot do as well.
 //   * segment_order_kernel, a few microseconds ahead of it, derives the row order from the
@@ -81,8 +82,12 @@ struct BlockSync {
 // depends on finish() (waits read from the assembly): where finish() consumes the slot by arithmetic and a store
 // (FusedOp with one slice, HierFusedOp, Fused16Op), every step waits for its own row and the others stay in
 // flight; where finish() only copies, widens or sums the slot (gossip, group means, push-sum, 16-bit rows), the
-// compiler gathers that at the head of the turn and waits there for all rows in flight and the last stores: the
-// ring is a batch of D rows a turn, not a pipeline.  (A branch around each load made it wait for all but the last
+// compiler gathers that at the head of the turn, or issues the first turn's loads in another order, whose last row then
+// bounds the wait of every turn: it waits there for all rows in flight and the last stores, and the ring is a batch of D rows
+// a turn, not a pipeline.  The batch is the better of the two: with the order pinned (sched_barrier between the loads and
+// steps, the first turn peeled) every step waits for its own row only, and in place, batch / pipeline, us, bf16 gossip on
+// 32 x 25,557,032 takes 597 / 602, on 512 x 1,000,003 514 / 558, the binary16 mean of groups of 4 on 64 x 11,689,511 594 / 638,
+// fp32 gossip and steps as long either way: DRAM serves reads and writes that come in turns better than mixed ones.  (A branch around each load made it wait for all but the last
 // access of the wavefront at every step: gossip on 256 x 8,303 fp32, in place, 8 segments: 230 -> 86 us together
 // with the boundary pieces below; fused step 256 x 300,007: 806 -> 573 us.)  The schedule's words are read from
 // LDS one step ahead and kept until their row arrives.  The last turns, up to 2 * D steps, decide step by step;
@@ -287,8 +292,7 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerBlock) void mix_kernel(
 // take a part of the rows each (schedule_part); `tiles` adjacent tiles make up the workgroup.  The rows of a part that
 // other parts overwrite are read ahead (PartEnds), and no wavefront stores before all of the workgroup have theirs.
 // In place, us, mix_kernel / this: fp32 gossip on 512 x 3,001 118 / 21, on 256 x 30,011 61 / 20; bf16 gossip on
-// 355 x 50,356 123 / 31; binary16 optimizer step on 256 x 30,011 232 / 50; push-sum with the copy on 826 x 79,896 628 / 249;
-// fp32 optimizer step on 256 x 300,007 364 / 344.
+// 355 x 50,356 123 / 31; binary16 optimizer step on 256 x 30,011 232 / 50; push-sum with the copy on 826 x 79,896 628 / 249.
 // The first `pieces` workgroups serve the pieces that begin at a segment boundary inside a workgroup's columns.
 // ---------------------------------------------------------------------------------
 template <class Op, int U>

@@ -272,9 +272,8 @@ unsigned *order_table_for(hipStream_t stream)
 // An operator staged through LDS keeps its waves: the staging is laid out for one shape, and other workgroups of it
 // take the path in registers.
 constexpr int64_t kMinChunks = 104;
-// A thread for every row, so that each of the schedule's rounds, of which there are about 2 log2 n, is one LDS access a
-// thread: 512 rows 9.5 us with 256 threads, 7.4 with 512; the call on 512 x 100,003
-// fp32 98.3 / 96.4, on 1,000 x 30,011 68.6 / 62.8.
+// A thread for every row, as place_row needs (512 rows with 256 threads and build_schedule 9.5 us, with 512 7.4, with
+// place_row 4.8).
 constexpr int order_threads(int n) { return n <= 256 ? 256 : n <= 512 ? 512 : 1024; }
 constexpr int64_t kCachedBytes = 64LL << 20;              // a matrix that the last-level cache holds, and its copy
 constexpr int kTileOrder = 16;                            // see by_tile in try_gather
@@ -427,7 +426,8 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
 }
 
 // ---------------------------------------------------------------------------------
-// In place with the rows of a tile split over wavefronts (parts_kernel), or parts == 0: mix_kernel.
+// In place with the rows of a tile split over wavefronts (parts_kernel), or parts == 0: mix_kernel.  (What even_shape below
+// takes does not come here.)
 //
 // Lengths are counted in tiles of one slice per lane and in rounds of mix_kernel, kRound tiles: one workgroup of eight
 // waves on every CU, each wavefront with a tile and all rows of it.  Two parts need twice the wavefronts for half the
@@ -549,8 +549,8 @@ constexpr PartShape part_shape(const Op &op, int n, int64_t P, int S)
     while (s.parts * jobs < kPartJobs && s.parts < limit && 2 * s.parts <= n) s.parts *= 2;
     // As many adjacent tiles a workgroup as leave the last round of workgroups, one a CU, nearly as full as the others
     // (fp32 means of groups of 2 to 4 on 700 to 800 tiles: 0.95 of mix_kernel's time, with 2 parts x 4 tiles 1.40).  Beside
-    // many rows one round of the widest is best whatever it leaves idle: fp32 optimizer step on 256 x 300,007, 154
-    // workgroups of 4 tiles 340 us, 593 of one tile 362.  Two slices per lane of groups on longer rows: one tile each (on 2,049
+    // 64 rows and more one round of the widest is best whatever it leaves idle (measured on the fp32 optimizer step on
+    // 256 x 300,007, 154 workgroups of 4 tiles 340 us, 593 of one tile 362; from kEvenRows rows on even_shape serves that better).  Two slices per lane of groups on longer rows: one tile each (on 2,049
     // to 3,072 tiles 0.94 with one, 0.95 with two, 1.03 with four).
     int most_full = 0;
     const int widest = s.parts >= kMaxWavesPerBlock || (kGroups && tiles > kRound) ? 1 : (n < 8 ? 4 : kMaxWavesPerBlock) / s.parts;
