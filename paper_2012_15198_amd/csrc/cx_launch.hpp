@@ -603,17 +603,19 @@ bool try_parts(const Op &op, const MixArgs &a)
 // short shapes serve, where the other shape is more than kEvenGain per cent off (at 8 slices for 7 the step on 117 x 398,433
 // took 171 us for 166), and up to kEvenRows16 plain 16-bit rows (831 x 943,628 899 us, 738 before).
 // Before / now, us: fp32 optimizer step on 256 x 300,007 342 / 314, on 263 x 589,905 713 / 573; fp32 gossip on 265 x 278,339
-// 136 / 117, on 611 x 512,664 525 / 474; fp32 push-sum on 171 x 1,202,009 321 / 294; bf16 gossip on 118 x 626,350 75 / 60; bf16
-// optimizer step on 158 x 3,248,642 1,553 / 1,351.  Of 110 shapes drawn afterwards (100 to 1,024 rows, 1,024 to 8,000
-// slices) 35 changed by more than 0.6 %: geometric mean 0.947, four above 1.02 (fp32 step on 266 x 324,362 361 / 375).
+// 136 / 117, on 611 x 512,664 525 / 474; fp32 push-sum on 171 x 1,202,009 321 / 294, on 34 x 598,370 38 / 30; bf16 gossip on
+// 118 x 626,350 75 / 60; bf16 optimizer step on 158 x 3,248,642 1,553 / 1,351, on 75 x 2,115,692 506 / 413.  Of 280 shapes drawn
+// afterwards (24 to 1,024 rows, 1,024 to 8,000 slices) 69 changed by more than 0.6 %: geometric mean 0.94; more than 24 slices a
+// CU of plain rows lost (bf16 gossip on 30 x 3,322,532 86 / 94) and keep the shapes they had.
 // ---------------------------------------------------------------------------------
-constexpr int kEvenRows = 100, kEvenRows16 = 500, kEvenLoad = 5, kEvenMost = 32, kEvenGain = 15;
+constexpr int kEvenRows = 24, kEvenRows16 = 500, kEvenLoad = 5, kEvenMost = 24, kEvenMostStep = 32, kEvenGain = 15;
 
-// Slices on the CU with the most, workgroups of `tiles` tiles of U slices.
+// Slices on the CU with the most, workgroups of `tiles` tiles of U slices.  The workgroups of the segments' pieces count: fp32
+// optimizer step on 66 x 650,762 in 20 segments, 255 workgroups and four of pieces 196 us, 171 with workgroups of eight waves.
 template <class Op>
-constexpr int64_t cu_load(int64_t P, int U, int tiles)
+constexpr int64_t cu_load(int64_t P, int U, int tiles, int pieces)
 {
-    const int64_t cols = static_cast<int64_t>(kWave) * Op::kElems * U * tiles, blocks = (P + cols - 1) / cols;
+    const int64_t cols = static_cast<int64_t>(kWave) * Op::kElems * U * tiles, blocks = (P + cols - 1) / cols + pieces;
     return (blocks + kCUs - 1) / kCUs * tiles * U;
 }
 
@@ -624,12 +626,12 @@ constexpr WalkShape even_shape(const Op &op, int n, int64_t P, int S)
     constexpr bool kStep = HasMomentum<Op>::value, kHalf = Op::kElems == 8;
     if (Op::kRows != 1 || n < kEvenRows || (kHalf && !kStep && n > kEvenRows16) || push_kind(op) == Push::kWithCopy) return kNone;
     const int64_t slices = (P + kWave * Op::kElems - 1) / (kWave * Op::kElems);
-    if (slices <= (kEvenLoad - 1) * kCUs || slices > kEvenMost * kCUs) return kNone;
+    if (slices <= (kEvenLoad - 1) * kCUs || slices > (kStep ? kEvenMostStep : kEvenMost) * kCUs) return kNone;
     WalkShape best = kNone;
     int64_t least = 0;
     for (int U = 1; U <= Op::kWalk.U; ++U)
         for (int waves = 3; waves <= waves_with_schedules<Op>(n, kMaxWavesPerBlock); ++waves) {
-            const int64_t load = cu_load<Op>(P, U, waves);
+            const int64_t load = cu_load<Op>(P, U, waves, (S - 1 + waves - 1) / waves);
             if (best.U && (load > least || (load == least && waves * U <= best.waves * best.U))) continue;
             least = load;
             best = WalkShape{U, 0, waves, 2};
@@ -640,7 +642,8 @@ constexpr WalkShape even_shape(const Op &op, int n, int64_t P, int S)
     const PartShape split = part_shape(op, n, P, S);
     if (split.parts && (kHalf ? best.waves : best.waves * best.U) < kEvenLoad) return kNone;
     const WalkShape whole = walk_shape(op, n, P);
-    const int64_t usual = split.parts ? cu_load<Op>(P, split.U, split.tiles) : cu_load<Op>(P, whole.U, whole.waves);
+    const int64_t usual = split.parts ? cu_load<Op>(P, split.U, split.tiles, S - 1)
+                                      : cu_load<Op>(P, whole.U, whole.waves, (S - 1 + whole.waves - 1) / whole.waves);
     if (100 * usual <= (100 + kEvenGain) * least) return kNone;
     best.D = kStep ? (kHalf ? 2 : 4) : push_kind(op) == Push::kPlain && best.U == 2 ? 2 : kHalf ? 4 : 8;
     return best;

@@ -15,7 +15,7 @@ SGD = (0.1, 0.9, 1e-4)
 
 @pytest.mark.parametrize("kind", ["gossip", "step", "push"])
 @pytest.mark.parametrize("rows", ["f32", "bf16", "f16"])
-@pytest.mark.parametrize("n,slices,beyond,S", [(100, 1024, 1, 3), (99, 1024, 1, 3), (120, 1172, -25, 8), (101, 1172, 3, 40), (513, 1030, 9, 5),
+@pytest.mark.parametrize("n,slices,beyond,S", [(24, 1024, 1, 3), (23, 1024, 1, 3), (120, 1172, -25, 8), (25, 1279, 77, 30), (26, 6143, 5, 2), (101, 1172, 3, 40), (513, 1030, 9, 5),
                                                (500, 1100, 0, 1)])
 def test_even_walk_equals_the_out_of_place_kernel(kind, rows, n, slices, beyond, S):
     P = slices * (256 if rows == "f32" else 512) + beyond
