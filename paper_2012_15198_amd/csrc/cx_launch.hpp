@@ -569,13 +569,11 @@ constexpr PartShape part_shape(const Op &op, int n, int64_t P, int S)
 }
 
 template <class Op>
-bool try_parts(const Op &op, const MixArgs &a)
+bool launch_parts(const Op &op, const PartShape &s, const MixArgs &a)
 {
     if constexpr (!PartRing<Op>::kBuilt) {
         return false;
     } else {
-        const PartShape s = part_shape(op, a.n, a.P, a.S);
-        if (s.parts == 0) return false;
         const int64_t block_cols = static_cast<int64_t>(kWave) * Op::kElems * s.U * s.tiles;
         const int64_t blocks = (a.P + block_cols - 1) / block_cols + a.S - 1;
         if (blocks > 0x7fffffffLL) return false;
@@ -649,6 +647,20 @@ constexpr WalkShape even_shape(const Op &op, int n, int64_t P, int S)
     return best;
 }
 
+// What serves a call in place: the split (parts.parts > 0), or mix_kernel in `walk`, which `even` says is even_shape's.
+struct InPlaceShape {
+    PartShape parts;
+    WalkShape walk;
+    bool even;
+};
+template <class Op>
+constexpr InPlaceShape in_place_shape(const Op &op, int n, int64_t P, int S)
+{
+    const WalkShape even = even_shape(op, n, P, S);
+    if (even.U) return InPlaceShape{{0, 0, 0, 0}, even, true};
+    return InPlaceShape{part_shape(op, n, P, S), walk_shape(op, n, P), false};
+}
+
 template <class Op>
 int launch_mix(const Op &op, const MixArgs &a)
 {
@@ -678,9 +690,9 @@ int launch_mix(const Op &op, const MixArgs &a)
     }
     bool as_tuned = a.skip_mix != 0;                       // launch parameters of the in-place kernel ask for mix_kernel's shapes
     for (const int key : {0, 1, 2, 3, 4, 9}) as_tuned = as_tuned || cx_get_tuning(key) != -1;
-    const WalkShape even = as_tuned ? WalkShape{0, 0, 0, 0} : even_shape(op, a.n, a.P, a.S);
-    if (!as_tuned && !even.U && try_parts<Op>(op, a)) return hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
-    Launch l = pick_launch(even.U ? even : walk_shape(op, a.n, a.P));
+    const InPlaceShape shape = as_tuned ? InPlaceShape{{0, 0, 0, 0}, walk_shape(op, a.n, a.P), false} : in_place_shape(op, a.n, a.P, a.S);
+    if (shape.parts.parts && launch_parts<Op>(op, shape.parts, a)) return hipGetLastError() == hipSuccess ? CX_OK : CX_ERR_HIP;
+    Launch l = pick_launch(shape.walk);
     if (a.P < kSliceLanes * l.U) l.U = 1;
     if (a.P < Op::kElems) l.D = 2;
     const bool done =

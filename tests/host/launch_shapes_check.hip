@@ -42,31 +42,36 @@ static_assert(is(shape<Row16Op<false>>(256, 3000003, 3000008), 1, 8, 8, 2) && is
               is(shape<Row16Op<false>>(16, 3000003, 3000008), 1, 4, 8, 2) && is(shape<Row16Op<false>>(3, 100003, 100008), 1, 8, 1, 16) &&
               is(shape<MeanOp<1>>(3, 100003, 100032), 1, 8, 2, 8));
 
-// In place with a tile's rows split over wavefronts: as many parts as make kPartJobs wavefronts and the rows and the
-// registers allow, as many tiles a workgroup as fill the last round of workgroups; mix_kernel elsewhere.
+// What serves a call in place: the split, mix_kernel with the tiles dealt out evenly, or mix_kernel in walk_shape above.
+template <class Op>
+constexpr InPlaceShape in_place(int n, int64_t P, int S, int64_t ld = 0, Op op = Op{})
+{
+    op.ld = ld ? ld : P + 4;
+    return in_place_shape(op, n, P, S);
+}
 template <class Op>
 constexpr bool parts_are(int n, int64_t P, int S, int U, int D, int parts, int tiles, int64_t ld = 0, Op op = Op{})
 {
-    op.ld = ld ? ld : P + 4;
-    const PartShape s = part_shape(op, n, P, S);
-    return s.parts == parts && (parts == 0 || (s.U == U && s.D == D && s.tiles == tiles));
+    const PartShape s = in_place(n, P, S, ld, op).parts;
+    return s.parts == parts && s.U == U && s.D == D && s.tiles == tiles;
 }
 template <class Op>
-constexpr bool no_parts(int n, int64_t P, int S, int64_t ld = 0)
+constexpr bool even_is(int n, int64_t P, int S, int U, int D, int waves, int wgs_per_cu, Op op = Op{})
 {
-    return parts_are<Op>(n, P, S, 0, 0, 0, 0, ld);
+    const InPlaceShape s = in_place(n, P, S, 0, op);
+    return s.even && s.parts.parts == 0 && is(s.walk, U, D, waves, wgs_per_cu);
 }
-static_assert(parts_are<MeanOp<1>>(512, 3001, 4, 1, 4, 16, 1) && parts_are<MeanOp<1>>(9, 3001, 4, 1, 4, 8, 1) &&
-              parts_are<FusedOp>(4, 2000, 4, 1, 2, 4, 1) && no_parts<FusedOp>(3, 2000, 4));
-static_assert(parts_are<MeanOp<1>>(16, 256 * 399, 1, 1, 4, 4, 2) && parts_are<MeanOp<1>>(16, 256 * 399 + 1, 1, 2, 2, 8, 1) &&
-              no_parts<MeanOp<1>>(7, 256 * 399 + 1, 1) && no_parts<FusedOp>(15, 256 * 399 + 1, 1));
-static_assert(parts_are<FusedOp>(256, 300007, 8, 2, 4, 2, 4) && no_parts<MeanOp<1>>(33, 800003, 7) &&
-              parts_are<MeanOp<4>>(33, 1100003, 7, 2, 2, 2, 1));
-static_assert(parts_are<MeanOp<1>>(8, 6000011, 7, 2, 2, 2, 4) && no_parts<MeanOp<1>>(8, 6000011, 7, 6000032) && no_parts<MeanOp<1>>(9, 6000011, 7));
-static_assert(parts_are<Row16Op<true, 4>>(16, 400009, 7, 1, 2, 2, 4) && no_parts<Row16Op<true, 4>>(16, 4000009, 7) &&
-              parts_are<Row16Op<true, 8>>(16, 2100003, 7, 1, 2, 2, 1) && no_parts<Row16Op<false>>(32, 25557032, 8));
-static_assert(no_parts<MeanOp<16>>(32, 3001, 4) && kPartWaves<MeanOp<1>, 1, 4> == 16 && kPartWaves<FusedOp, 2, 4> == 8);
-
+template <class Op>
+constexpr bool walks(int n, int64_t P, int S, int64_t ld = 0, Op op = Op{})
+{
+    const InPlaceShape s = in_place(n, P, S, ld, op);
+    return s.parts.parts == 0 && !s.even;
+}
+template <class Op>
+constexpr bool not_split(int n, int64_t P, int S, Op op = Op{})
+{
+    return in_place(n, P, S, 0, op).parts.parts == 0;
+}
 float a_copy;
 constexpr PushOp with_copy()
 {
@@ -74,19 +79,33 @@ constexpr PushOp with_copy()
     op.zout = &a_copy;
     return op;
 }
-static_assert(parts_are<PushOp>(64, 256 * 2048, 1, 2, 2, 2, 4, 0, with_copy()) && parts_are<PushOp>(9, 256 * 1025, 1, 0, 0, 0, 0, 0, with_copy()));
+
+// The split: as many parts as make kPartJobs wavefronts and the rows and the registers allow, as many tiles a workgroup as
+// fill the last round of workgroups.
+static_assert(parts_are<MeanOp<1>>(512, 3001, 4, 1, 4, 16, 1) && parts_are<MeanOp<1>>(9, 3001, 4, 1, 4, 8, 1) &&
+              parts_are<FusedOp>(4, 2000, 4, 1, 2, 4, 1) && walks<FusedOp>(3, 2000, 4));
+static_assert(parts_are<MeanOp<1>>(16, 256 * 399, 1, 1, 4, 4, 2) && parts_are<MeanOp<1>>(16, 256 * 399 + 1, 1, 2, 2, 8, 1) &&
+              walks<MeanOp<1>>(7, 256 * 399 + 1, 1) && walks<FusedOp>(15, 256 * 399 + 1, 1));
+static_assert(parts_are<FusedOp>(64, 256 * 1024, 8, 2, 4, 2, 4) && walks<MeanOp<1>>(33, 800003, 7) &&
+              parts_are<MeanOp<4>>(33, 1100003, 7, 2, 2, 2, 1));
+static_assert(parts_are<MeanOp<1>>(8, 6000011, 7, 2, 2, 2, 4) && walks<MeanOp<1>>(8, 6000011, 7, 6000032) && walks<MeanOp<1>>(9, 6000011, 7));
+static_assert(parts_are<Row16Op<true, 4>>(16, 400009, 7, 1, 2, 2, 4) && walks<Row16Op<true, 4>>(16, 4000009, 7) &&
+              parts_are<Row16Op<true, 8>>(16, 2100003, 7, 1, 2, 2, 1) && walks<Row16Op<false>>(32, 25557032, 8));
+static_assert(walks<MeanOp<16>>(32, 3001, 4) && kPartWaves<MeanOp<1>, 1, 4> == 16 && kPartWaves<FusedOp, 2, 4> == 8);
+
+static_assert(parts_are<PushOp>(64, 256 * 2048, 1, 2, 2, 2, 4, 0, with_copy()) && walks<PushOp>(9, 256 * 1025, 1, 0, with_copy()));
 
 // The short shapes of mix_kernel above are those of calls that are not split.
-static_assert(no_parts<MeanOp<1>>(1024, 600003, 8) && no_parts<FusedOp>(12, 110003, 8) && no_parts<Row16Op<false>>(3, 100003, 8) &&
-              no_parts<MeanOp<1>>(3, 100003, 8) && no_parts<MeanOp<8>>(4, 900001, 8) && no_parts<FusedOp>(32, 900001, 1) &&
-              no_parts<Row16Op<false>>(64, 3000003, 8) && no_parts<MeanOp<1>>(32, 2000003, 8));
+static_assert(walks<MeanOp<1>>(1024, 600003, 8) && walks<FusedOp>(12, 110003, 8) && walks<Row16Op<false>>(3, 100003, 8) &&
+              walks<MeanOp<1>>(3, 100003, 8) && walks<MeanOp<8>>(4, 900001, 8) && walks<FusedOp>(32, 900001, 1) &&
+              walks<Row16Op<false>>(64, 3000003, 8) && walks<MeanOp<1>>(32, 2000003, 8));
 
-// Shapes that the split slowed by 5 to 32 per cent stay whole.
-static_assert(no_parts<Row16Op<false>>(500, 650003, 8) && no_parts<Row16Op<false>>(500, 1500003, 8) && no_parts<HierFusedOp<8>>(5, 60007, 4) &&
-              no_parts<HierFused16Op<true, 8>>(64, 828274, 1) && no_parts<Row16Op<false, 4>>(10, 884531, 1) &&
-              parts_are<PushOp>(200, 840693, 1, 0, 0, 0, 0, 0, with_copy()) && no_parts<HierFusedOp<8>>(33, 139500, 1) && no_parts<HierFusedOp<1>>(20, 119800, 32));
+// Shapes that the split slowed by 5 to 32 per cent are not split.
+static_assert(not_split<Row16Op<false>>(500, 650003, 8) && walks<Row16Op<false>>(500, 1500003, 8) && walks<HierFusedOp<8>>(5, 60007, 4) &&
+              walks<HierFused16Op<true, 8>>(64, 828274, 1) && walks<Row16Op<false, 4>>(10, 884531, 1) &&
+              walks<PushOp>(200, 840693, 1, 0, with_copy()) && walks<HierFusedOp<8>>(33, 139500, 1) && walks<HierFusedOp<1>>(20, 119800, 32));
 
-// Every length of a stretch takes one answer: in the first half of mix_kernel's second and third round the split, one tile a
+// Every length of a stretch takes one answer, those aside that the even walk takes: in the first half of mix_kernel's second and third round the split, one tile a
 // workgroup for groups, in the second halves mix_kernel; many rows, whose schedules leave a workgroup fewer waves, have
 // shorter rounds.
 template <class Op>
@@ -95,7 +114,9 @@ constexpr bool all_lengths(int n, int S, int64_t from, int64_t to, bool split, i
     for (int64_t tiles = from; tiles <= to; tiles += 7) {
         Op op{};
         op.ld = tiles * kWave * Op::kElems + 8;
-        const PartShape s = part_shape(op, n, tiles * kWave * Op::kElems, S);
+        const InPlaceShape shape = in_place_shape(op, n, tiles * kWave * Op::kElems, S);
+        if (shape.even) continue;
+        const PartShape s = shape.parts;
         if ((s.parts != 0) != split || (split && tiles_a_workgroup && s.tiles != tiles_a_workgroup)) return false;
     }
     return true;
@@ -109,5 +130,14 @@ static_assert(all_lengths<MeanOp<1>>(64, 8, 20, 1536, true) && all_lengths<MeanO
 static_assert(all_lengths<MeanOp<1>>(500, 1, 1537, 2304, true) && all_lengths<MeanOp<1>>(500, 1, 2305, 3072, false));
 static_assert(all_lengths<FusedOp>(64, 8, 6145, 7168, true) && all_lengths<FusedOp>(64, 8, 7169, 20000, false) &&
               all_lengths<FusedOp>(15, 8, 400, 20000, false) && all_lengths<PushOp>(64, 1, 1025, 20000, false));
+
+// The even walk: from 24 plain rows on, at 1,025 slices of 256 or 512 columns and more; mix_kernel with the waves that leave
+// the busiest CU the fewest slices.
+static_assert(even_is<FusedOp>(256, 300007, 8, 1, 4, 5, 2) && even_is<MeanOp<1>>(265, 278339, 4, 1, 8, 5, 2) &&
+              even_is<MeanOp<1>>(24, 256 * 1025, 3, 1, 8, 5, 2) && !in_place<MeanOp<1>>(23, 256 * 1025, 3).even &&
+              !in_place<MeanOp<1>>(24, 256 * 1024, 3).even && !in_place<MeanOp<2>>(256, 300007, 8).even &&
+              !in_place<PushOp>(256, 300007, 1, 0, with_copy()).even);
+static_assert(even_is<Row16Op<false>>(500, 512 * 1025, 1, 1, 4, 5, 2) && !in_place<Row16Op<false>>(501, 512 * 1025, 1).even &&
+              even_is<Fused16Op<true>>(24, 512 * 1025, 1, 1, 2, 5, 2));
 
 }  // namespace
