@@ -600,11 +600,17 @@ bool launch_parts(const Op &op, const PartShape &s, const MixArgs &a)
 // fewer, wider workgroups.  From kEvenLoad slices a CU on, below which a CU has too few wavefronts and the split or mix_kernel's
 // short shapes serve, where the other shape is more than kEvenGain per cent off (at 8 slices for 7 the step on 117 x 398,433
 // took 171 us for 166), and up to kEvenRows16 plain 16-bit rows (831 x 943,628 899 us, 738 before).
-// Before / now, us: fp32 optimizer step on 256 x 300,007 342 / 314, on 263 x 589,905 713 / 573; fp32 gossip on 265 x 278,339
+// The cap on resident workgroups is one on wavefronts, as in walk_shape: three waves, two / five workgroups a CU, us: fp32 gossip
+// on 24 x 523,592 in 16 segments 29.1 / 24.0, bf16 gossip on 105 x 1,045,250 in 24 117 / 101, fp32 push-sum on 439 x 543,169
+// 418 / 392; four to six waves and two slices are as long either way.  Steps on 16-bit rows keep two workgroups of four waves and
+// more: three waves took 0.96 to 1.04 of the time of eight, five workgroups of them 0.96 to 1.07 (32 shapes of 6,423 to 6,897 slices).
+// Before / now, us: fp32 optimizer step on 256 x 300,007 342 / 314; fp32 gossip on 265 x 278,339
 // 136 / 117, on 611 x 512,664 525 / 474; fp32 push-sum on 171 x 1,202,009 321 / 294, on 34 x 598,370 38 / 30; bf16 gossip on
-// 118 x 626,350 75 / 60; bf16 optimizer step on 158 x 3,248,642 1,553 / 1,351, on 75 x 2,115,692 506 / 413.  Of 280 shapes drawn
-// afterwards (24 to 1,024 rows, 1,024 to 8,000 slices) 69 changed by more than 0.6 %: geometric mean 0.94; more than 24 slices a
-// CU of plain rows lost (bf16 gossip on 30 x 3,322,532 86 / 94) and keep the shapes they had.
+// 118 x 626,350 75 / 60; bf16 optimizer step on 158 x 3,248,642 1,553 / 1,351, on 75 x 2,115,692 506 / 413.  More than 24 slices a CU
+// of plain rows lost (bf16 gossip on 30 x 3,322,532 86 / 94) and keep the shapes they had.
+// It takes 65 to 94 % of the lengths up to 1,535 slices (of 16-bit steps 24 %) and few of the longer ones, up to 4 %, except of fp32
+// push-sum without the copy (57 % up to 3,071, 29 % up to 6,143) and 16-bit steps (28 % from 3,072 on, 10 % from 6,144 on): elsewhere
+// the other shapes fill the CUs.  Time over theirs on 153 shapes drawn from those it takes: geometric mean 0.89, 0.72 to 1.012.
 // ---------------------------------------------------------------------------------
 constexpr int kEvenRows = 24, kEvenRows16 = 500, kEvenLoad = 5, kEvenMost = 24, kEvenMostStep = 32, kEvenGain = 15;
 
@@ -628,20 +634,25 @@ constexpr WalkShape even_shape(const Op &op, int n, int64_t P, int S)
     WalkShape best = kNone;
     int64_t least = 0;
     for (int U = 1; U <= Op::kWalk.U; ++U)
-        for (int waves = 3; waves <= waves_with_schedules<Op>(n, kMaxWavesPerBlock); ++waves) {
+        for (int waves = kHalf && kStep ? 4 : 3; waves <= waves_with_schedules<Op>(n, kMaxWavesPerBlock); ++waves) {
             const int64_t load = cu_load<Op>(P, U, waves, (S - 1 + waves - 1) / waves);
             if (best.U && (load > least || (load == least && waves * U <= best.waves * best.U))) continue;
             least = load;
-            best = WalkShape{U, 0, waves, 2};
+            best = WalkShape{U, 0, waves, kHalf && kStep ? 2 : 2 * kMaxWavesPerBlock / waves};
         }
     if (!best.U) return kNone;
     // where the split serves, few waves of a narrow tile each do not replace it (bf16 optimizer step on 506 x 587,964 943 us
     // split, 973 with three waves)
     const PartShape split = part_shape(op, n, P, S);
     if (split.parts && (kHalf ? best.waves : best.waves * best.U) < kEvenLoad) return kNone;
+    // The first workgroup of pieces does not count for the walk as it is otherwise: beside a full round of tiles it makes no round
+    // of its own, since few of its wavefronts have a piece.  That walk, 256 workgroups and one / three or four waves, us: bf16 gossip
+    // on 115 x 1,047,248 in two segments 94 / 121, fp32 optimizer step on 119 x 522,620 in 8 243 / 268; of 83 such shapes of gossip
+    // and steps three or four waves took 0.92 to 1.29 of its time, beside more workgroups of pieces 0.74 to 1.0.
     const WalkShape whole = walk_shape(op, n, P);
+    const int pieces = (S - 1 + whole.waves - 1) / whole.waves;
     const int64_t usual = split.parts ? cu_load<Op>(P, split.U, split.tiles, S - 1)
-                                      : cu_load<Op>(P, whole.U, whole.waves, (S - 1 + whole.waves - 1) / whole.waves);
+                                      : cu_load<Op>(P, whole.U, whole.waves, pieces > 1 ? pieces - 1 : 0);
     if (100 * usual <= (100 + kEvenGain) * least) return kNone;
     best.D = kStep ? (kHalf ? 2 : 4) : push_kind(op) == Push::kPlain && best.U == 2 ? 2 : kHalf ? 4 : 8;
     return best;

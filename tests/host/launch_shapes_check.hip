@@ -132,12 +132,18 @@ static_assert(all_lengths<FusedOp>(64, 8, 6145, 7168, true) && all_lengths<Fused
               all_lengths<FusedOp>(15, 8, 400, 20000, false) && all_lengths<PushOp>(64, 1, 1025, 20000, false));
 
 // The even walk: from 24 plain rows on, at 1,025 slices of 256 or 512 columns and more; mix_kernel with the waves that leave
-// the busiest CU the fewest slices.
-static_assert(even_is<FusedOp>(256, 300007, 8, 1, 4, 5, 2) && even_is<MeanOp<1>>(265, 278339, 4, 1, 8, 5, 2) &&
-              even_is<MeanOp<1>>(24, 256 * 1025, 3, 1, 8, 5, 2) && !in_place<MeanOp<1>>(23, 256 * 1025, 3).even &&
+// the busiest CU the fewest slices, and as many wavefronts on a CU whatever the workgroup's size.
+static_assert(even_is<FusedOp>(256, 300007, 8, 1, 4, 5, 3) && even_is<MeanOp<1>>(265, 278339, 4, 1, 8, 5, 3) &&
+              even_is<MeanOp<1>>(24, 256 * 1025, 3, 1, 8, 5, 3) && !in_place<MeanOp<1>>(23, 256 * 1025, 3).even &&
               !in_place<MeanOp<1>>(24, 256 * 1024, 3).even && !in_place<MeanOp<2>>(256, 300007, 8).even &&
               !in_place<PushOp>(256, 300007, 1, 0, with_copy()).even);
-static_assert(even_is<Row16Op<false>>(500, 512 * 1025, 1, 1, 4, 5, 2) && !in_place<Row16Op<false>>(501, 512 * 1025, 1).even &&
+static_assert(even_is<Row16Op<false>>(500, 512 * 1025, 1, 1, 4, 5, 3) && !in_place<Row16Op<false>>(501, 512 * 1025, 1).even &&
               even_is<Fused16Op<true>>(24, 512 * 1025, 1, 1, 2, 5, 2));
+// One workgroup of the segments' pieces beside a full round of tiles does not make a second round; several do.
+static_assert(walks<Row16Op<false>>(115, 1047248, 2) && walks<FusedOp>(119, 522620, 8) && walks<MeanOp<1>>(29, 523264, 8) &&
+              walks<MeanOp<1>>(30, 1047296, 3) && even_is<MeanOp<1>>(163, 522496, 16, 1, 8, 3, 5) &&
+              even_is<FusedOp>(98, 523520, 16, 1, 4, 3, 5) && !even_is<FusedOp>(66, 650762, 20, 2, 4, 5, 3));
+// Steps on 16-bit rows: no workgroups of three waves.
+static_assert(walks<Fused16Op<false>>(61, 3505152, 2));
 
 }  // namespace
