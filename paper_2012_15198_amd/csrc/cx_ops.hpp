@@ -48,6 +48,10 @@ constexpr bool two_waves(int G, int rows, int64_t P, bool whole_lines)
 // many rows only, since the last 2 * D steps of a walk are slower ones.
 constexpr int ring_for(int n) { return n >= 128 ? 8 : 4; }
 
+// Gossiping rows that are few, and columns of rows that are long, for the visit of the out-of-place kernel (VisitKb).
+constexpr int kFewRows = 8;
+constexpr int64_t kLongVisits = 2 << 20;
+
 // Plain gossip (G == 1) and hierarchical mode (a gossiping row = a group of G rows).
 // G == 1 is Algorithm 1's averaging line in fp32, as written.  For G > 1 the group sum (rows in
 // order, from zero), the division by G and the average between leaders run in fp64 registers and
@@ -64,7 +68,7 @@ struct MeanOp {
     // (all G rows behind it) per XCD -- measured optima on MI355X (see VisitKb)
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 4, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0} : GatherShape{1, 8, 768, 0};
-    static constexpr int kVisitKbFewRows = G > 8 ? 256 : G == 8 ? 512 : kGather.visit_kb;      // see VisitKb
+    static constexpr int visit_kb(int n, int64_t) { return G < 8 || n > kFewRows ? 0 : G == 8 ? 512 : 256; }
     static constexpr WalkShape kWalk =
         G == 1 ? WalkShape{2, 8, 8, 2} : G == 2 ? WalkShape{2, 4, 8, 2} : G <= 5 ? WalkShape{2, 2, 8, 2}
         : G <= 8 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
@@ -218,30 +222,33 @@ Op with_stage_base(const Op &op, size_t base)
     return copy;
 }
 
-// Visit length of the out-of-place kernel: the operator's kGather.visit_kb, except that an operator with
-// groups behind its rows may name a shorter visit for tables of few gossiping rows, whose longest cycle's visits then
-// fit one XCD's 4 MB L2 (groups of 16; of the fp32 mean also groups of 8: with more rows 768 KB, 256 x 25,557,032 in 32
-// groups 9,725 us, with 512 KB 9,743).
+// Visit length of the out-of-place kernel: kGather.visit_kb, unless the operator's visit_kb(rows, P) names another one (0: it does not).
 //
-// Operators on groups visit 8 or 16 workgroups' chunks of 8 KB of every matrix row: with a power of two the XCDs' visits of a
-// row together begin and end on multiples of 512 KB.  Time with that over the time with the visit before (256 KB at up to
-// 8 gossiping rows, 768 KB or 384 KB of 16-bit rows beyond, of the whole group) on matrices as torch allocates them, groups of 8,
-// 1,000,003 / 4,000,003 / 11,689,512 columns, 8 gossiping rows, then 1,000,003 / 4,000,003 columns, 32 gossiping rows:
-//   fp32 mean             8 chunks   0.978 / 0.987 / 0.976   (unchanged)
-//   16-bit mean          16 chunks   0.968 / 0.986 / 0.978   0.927 / 0.958
-//   fp32 gradient step   16 chunks   0.935 / 0.971 / 0.954   0.974 / 1.001
-//   16-bit gradient step  8 chunks   0.914 / 1.006 / 0.982   0.879 / 0.999
-// (the largest of 4 to 32 gossiping rows 1.026, 16-bit gradient step on 4 groups x 4,000,003).  Groups of 4 of the 16-bit mean, 16
-// chunks for 8: 0.97 to 0.999; groups of 3 to 7 within 0.966 to 1.02.  On matrices spread over the physical memory the fp32 mean
-// on 64 x 11,689,512 loses 0.6 % to 256 KB visits, which keep a cycle's first row in L2 until it closes.
-constexpr int kFewRows = 8;
+// Operators on groups, in chunks of 8 KB of every matrix row (before the clusters are shortened to fill their last round).  Eight or
+// sixteen chunks, with which the XCDs' visits of a row together begin and end on multiples of 512 KB, gain on matrices as torch
+// allocates them for some operators and group sizes; the others keep what they had.  Time over that with the visit before, 20 to 45
+// shapes of 250,000 to 11,689,512 columns and 2 to 64 gossiping rows each, geometric mean (range), and the visit taken:
+//   fp32 mean             groups of 8, up to 8 rows    8 for 4            0.99 (0.95 to 1.014)   8
+//   16-bit mean           groups of 3, 4, 6           16 for 10, 8, 8     0.98 (0.88 to 1.04)   16
+//                         groups of 5                  8 for 9            1.00 (0.97 to 1.04)    9
+//                         groups of 7, 8              16 for 6            0.96 (0.91 to 1.013)  16
+//                           up to 8 rows                                  1.00 (0.86 to 1.06)    6 (on spread matrices 0.995 to 1.055)
+//   fp32 gradient step    groups of 8                 16 for 12 (few: 4)  0.98 (0.93 to 1.014)  16
+//                         groups of 5, 7              16 for 19, 13       1.00 (0.92 to 1.05)   19, 13
+//   16-bit gradient step  groups of 3                  8 for 10           0.99 (0.94 to 1.013)   8
+//                         groups of 8, long rows       8 for 6            0.98 (0.97 to 1.005)   8
+//                           shorter than kLongVisits                      1.02 (0.94 to 1.083)   6
+//                         groups of 5, 7               8 for 9, 6         1.01 (0.94 to 1.14)    9, 6
+// On matrices spread over the physical memory what is taken gains less or loses: fp32 mean 0.980 to 1.010, 16-bit mean 0.97 to
+// 1.013, fp32 gradient step 0.983 to 1.030, 16-bit gradient step 0.985 to 1.008.
+// With groups of 16, at most kFewRows gossiping rows visit 256 KB: their longest cycle's visits then fit one XCD's 4 MB L2.
 template <class Op, class = void>
 struct VisitKb {
-    static constexpr int of(int) { return Op::kGather.visit_kb; }
+    static constexpr int of(int, int64_t) { return Op::kGather.visit_kb; }
 };
 template <class Op>
-struct VisitKb<Op, std::void_t<decltype(Op::kVisitKbFewRows)>> {
-    static constexpr int of(int n) { return n <= kFewRows ? Op::kVisitKbFewRows : Op::kGather.visit_kb; }
+struct VisitKb<Op, std::void_t<decltype(Op::visit_kb(0, 0))>> {
+    static constexpr int of(int n, int64_t P) { return Op::visit_kb(n, P) ? Op::visit_kb(n, P) : Op::kGather.visit_kb; }
 };
 
 template <class Op, class = void>
@@ -352,8 +359,8 @@ struct HierFusedOp {
     // out-of-place launch: slices, waves, group visit KB per XCD
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 8, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0}
-        : G <= 8 ? GatherShape{1, 8, 128 * G, 0} : GatherShape{1, 8, 768, 0};
-    static constexpr int kVisitKbFewRows = G > 8 ? 256 : kGather.visit_kb;       // see VisitKb
+        : G == 8 ? GatherShape{1, 8, 1024, 0} : GatherShape{1, 8, 768, 0};
+    static constexpr int visit_kb(int n, int64_t) { return G <= 8 || n > kFewRows ? 0 : 256; }      // see VisitKb
     static constexpr WalkShape kWalk = G <= 4 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G <= 2 ? 2 : 1;
     template <int U, int D> static constexpr bool kSpills = G == 5 && D == 4;

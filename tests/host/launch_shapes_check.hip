@@ -10,6 +10,23 @@ static_assert(gather_waves<MeanLdsOp<8>, 1>(150001, MeanLdsOp<8>::kGather.waves)
 static_assert(staged_shape<MeanLdsOp<8>>(MeanLdsOp<8>::kGather.waves) && !staged_shape<MeanLdsOp<8>>(4));
 static_assert(gather_waves<MeanOp<8>, 1>(150001, MeanOp<8>::kGather.waves) == 4 && !staged_shape<MeanOp<8>>(8));
 
+// Visits of the out-of-place kernel, KB: longer ones of operators on groups only where they gain.
+template <class Op>
+constexpr bool visits(int few_short, int few_long, int many_short, int many_long)
+{
+    using Kb = VisitKb<Op>;
+    constexpr int64_t kEdge = 2 << 20;
+    return Kb::of(8, kEdge - 1) == few_short && Kb::of(8, kEdge) == few_long && Kb::of(9, kEdge - 1) == many_short && Kb::of(9, kEdge) == many_long;
+}
+static_assert(visits<Row16Op<false, 8>>(384, 384, 1024, 1024) && visits<Row16Op<true, 7>>(384, 384, 896, 896) && visits<Row16Op<true, 6>>(768, 768, 768, 768) &&
+              visits<Row16Op<false, 5>>(384, 384, 384, 384) && visits<Row16Op<true, 4>>(512, 512, 512, 512) && visits<Row16Op<false, 1>>(96, 96, 96, 96) &&
+              visits<Push16Op<true>>(192, 192, 192, 192));
+static_assert(visits<HierFused16Op<false, 8>>(384, 512, 384, 512) && visits<HierFused16Op<true, 7>>(384, 384, 384, 384) &&
+              visits<HierFused16Op<true, 5>>(384, 384, 384, 384) && visits<HierFused16Op<false, 3>>(192, 192, 192, 192));
+static_assert(visits<HierFusedOp<8>>(1024, 1024, 1024, 1024) && visits<HierFusedOp<7>>(768, 768, 768, 768) && visits<HierFusedOp<5>>(768, 768, 768, 768) &&
+              visits<HierFusedOp<16>>(256, 256, 768, 768) && visits<MeanOp<8>>(512, 512, 768, 768) && visits<MeanOp<16>>(256, 256, 768, 768) &&
+              visits<MeanLdsOp<8>>(512, 512, 768, 768) && visits<MeanOp<1>>(256, 256, 256, 256));
+
 // In place, as many wavefronts per CU whatever the workgroup's size: two workgroups of eight, or eight of two where
 // rows are short or 1,024 rows' schedules leave no room for more.
 template <class Op>
