@@ -18,7 +18,8 @@
 //     in the L2 of one XCD (block b runs on XCD b mod 8; an XCD walks a cluster of
 //     neighbouring chunks row after row; rows follow the cycles of the peer permutation,
 //     so a block's partner is the next block's own row).
-//   * Rows that begin inside a line of 128 bytes: each row's tiles start on the row's own lines (OnLines).
+//   * Rows that begin inside a line of 128 bytes: each row's tiles start on the row's own lines (OnLines), for the operators
+//     that gain by it.
 //   * Long contiguous row visits per XCD keep the DRAM row buffers busy, which a kernel
 //     whose waves each wander over all rows cannot do as well.
 //   * segment_order_kernel, a few microseconds ahead of it, derives the row order from the
@@ -43,8 +44,8 @@
 //
 //  parts_kernel (in place, few tiles) -- the same walk, with the rows of a tile split over the wavefronts of a workgroup.
 //
-//  All: tiles wholly inside one segment take the 16-byte vector path.  In the at most S+1 tiles that a
-//  segment boundary or the ragged row end crosses, every piece between two boundaries loads the slices it
+//  All: tiles wholly inside one segment take the 16-byte vector path.  In the at most S tiles of a row (S+1 with tiles on the row's
+//  own lines) that a segment boundary or an end of the row crosses, every piece between two boundaries loads the slices it
 //  meets and stores under a mask of elements: piece after piece by the tile's wavefront in gather_kernel, one
 //  wavefront for each piece in mix_kernel.  Columns [P, ld) are neither read nor written.  Row operators
 //  (MeanOp / FusedOp / HierFusedOp / PushOp / Row16Op ...) say what loading and storing a "gossiping row" means:
@@ -507,9 +508,9 @@ __global__ __launch_bounds__(1024) void segment_order_kernel(int n, int64_t P, i
 // earlier, so that only the partner's loads, which L2 serves, are shifted against lines; the first tile of a row hangs
 // over its beginning and is a boundary tile.  A tile or cluster counts as inside one segment if it is, wherever its row
 // begins.  In the column grid / on lines, us: fp32 gossip on 512 x 100,003 96.3 / 94.4, on 32 x 25,557,032 1,131 / 1,112;
-// bf16 gossip on 32 x 25,557,032 572 / 563; push-sum of bf16 rows with the copy on 128 x 11,689,513 1,595 / 1,568;
-// optimizer step on 64 x 5,000,001 fp32 1,168 / 1,144, on 128 x 3,000,003 bf16 961 / 939.  (With the shift as an argument
-// instead of a kernel of its own, rows on lines paid 0.5 to 1.5 % for it.)
+// push-sum of bf16 rows with the copy on 128 x 11,689,513 1,595 / 1,568; optimizer step on 64 x 5,000,001 fp32 1,168 / 1,144, on
+// 128 x 3,000,003 bf16 961 / 939; which operators take it: starts_on_lines in cx_launch.hpp.  (With the shift as an argument instead
+// of a kernel of its own, rows on lines paid 0.5 to 1.5 % for it.)
 // ---------------------------------------------------------------------------------
 template <class Op>
 struct OnLines : Op {};

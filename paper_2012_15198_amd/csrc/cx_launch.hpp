@@ -284,6 +284,27 @@ constexpr int gather_waves(int64_t P, int waves)
     while (!LdsStaged<Op>::value && waves > 1 && P <= (kMinChunks - 1) * wave_cols * waves) waves /= 2;
     return waves;
 }
+enum class Push { kNo, kPlain, kWithCopy };
+template <class Op> constexpr Push push_kind(const Op &) { return Push::kNo; }
+constexpr Push push_kind(const PushOp &op) { return op.zout ? Push::kWithCopy : Push::kPlain; }
+template <bool H> constexpr Push push_kind(const Push16Op<H> &op) { return op.zout ? Push::kWithCopy : Push::kPlain; }
+template <class Op, class = void>
+struct HasMomentum : std::false_type {};
+template <class Op>
+struct HasMomentum<Op, std::void_t<decltype(std::declval<const Op &>().vin)>> : std::true_type {};
+
+// Operators whose tiles start on the rows' own lines (OnLines) where rows begin inside lines.  Time on lines over that in the column
+// grid, geometric mean (largest): fp32 gossip, its stores written through on lines, 0.982 (1.029) of 84 shapes, fp32 optimizer step
+// 0.989 (1.015) of 49, 16-bit 0.981 (1.000) of 93, push-sum with the copy 0.987 (1.000) of 19 and 0.981 (0.994) of 23, fp32 without
+// it 0.989 (1.008) of 13.  16-bit rows that are only averaged gain nothing: gossip 1.004 (1.094) of 170, 200 rows and more of
+// 300,000 to 3,000,000 columns 1.02, push-sum without the copy 1.004 (1.096) of 19.
+template <class Op>
+constexpr bool kMayStartOnLines = Op::kRows == 1 && !std::is_same_v<Op, Bf16Op> && !std::is_same_v<Op, Fp16Op>;
+template <class Op>
+constexpr bool starts_on_lines(const Op &op)
+{
+    return kMayStartOnLines<Op> && !(Op::kElems == 8 && push_kind(op) == Push::kPlain);
+}
 template <class Op>
 constexpr bool staged_shape(int waves)
 {
@@ -307,12 +328,12 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     const bool own_table = a.order_provider != nullptr;
     bool ordered = a.n > 1 && a.S <= 4096 &&
                    (own_table || cx_get_tuning(8) == 1 || (cx_get_tuning(8) != 0 && matrix_bytes > kCachedBytes));
-    // Rows that begin inside a line keep to their lines where they are in cycle order too: what the cache holds whole loses by
-    // the one chunk more that a row may need (fp32 gossip on 700 x 3,003 9.1 / 9.4 us, on 8 x 1,000,001 13.0 / 13.5).  A tile
-    // must not reach over both ends of a row, a group's rows begin on different columns of a line, and a table of the
-    // caller's holds what it was sized for.
+    // Rows that begin inside a line keep to their lines where the operator gains by it and they are in cycle order too: what the
+    // cache holds whole loses by the one chunk more that a row may need (fp32 gossip on 700 x 3,003 9.1 / 9.4 us, on
+    // 8 x 1,000,001 13.0 / 13.5).  A tile must not reach over both ends of a row, a group's rows begin on different columns of a
+    // line, and a table of the caller's holds what it was sized for.
     const bool on_lines = ((reinterpret_cast<uintptr_t>(op.xout) | static_cast<uint64_t>(op.ld) * (16 / Op::kElems)) & (kLineBytes - 1)) == 0;
-    const bool lines = Op::kRows == 1 && !on_lines && ordered && !own_table && a.P >= 2 * kWave * Op::kElems * U;
+    const bool lines = starts_on_lines(op) && !on_lines && ordered && !own_table && a.P >= 2 * kWave * Op::kElems * U;
     const int slack = lines ? kLineSlack<Op> : 0;
     const int64_t nchunks = (a.P + slack + chunk_cols - 1) / chunk_cols;
     if (nchunks < 8) xcd_aware = 0;               // fewer chunks than XCDs: rows go round the XCDs instead
@@ -414,7 +435,7 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
             else launch(gather_kernel<ThroughOp, U, true>, ThroughOp{staged});
         }
     } else if (lines) {
-        if constexpr (Op::kRows == 1) {
+        if constexpr (kMayStartOnLines<Op>) {
             if (nt) launch(gather_kernel<OnLines<Op>, U, true>, OnLines<Op>{staged});
             else launch(gather_kernel<OnLines<Op>, U, false>, OnLines<Op>{staged});
         }
@@ -463,15 +484,6 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
 struct PartShape {
     int U, D, parts, tiles;
 };
-enum class Push { kNo, kPlain, kWithCopy };
-template <class Op> constexpr Push push_kind(const Op &) { return Push::kNo; }
-constexpr Push push_kind(const PushOp &op) { return op.zout ? Push::kWithCopy : Push::kPlain; }
-template <bool H> constexpr Push push_kind(const Push16Op<H> &op) { return op.zout ? Push::kWithCopy : Push::kPlain; }
-template <class Op, class = void>
-struct HasMomentum : std::false_type {};
-template <class Op>
-struct HasMomentum<Op, std::void_t<decltype(std::declval<const Op &>().vin)>> : std::true_type {};
-
 template <class Op>
 struct PartRing {                       // the two rings that are built: short rows, long rows
     static constexpr bool kBuilt = !LdsStaged<Op>::value && Op::kRawPerSlice < 16;          // groups of 16 keep mix_kernel

@@ -27,6 +27,26 @@ static_assert(visits<HierFusedOp<8>>(1024, 1024, 1024, 1024) && visits<HierFused
               visits<HierFusedOp<16>>(256, 256, 768, 768) && visits<MeanOp<8>>(512, 512, 768, 768) && visits<MeanOp<16>>(256, 256, 768, 768) &&
               visits<MeanLdsOp<8>>(512, 512, 768, 768) && visits<MeanOp<1>>(256, 256, 256, 256));
 
+// Tiles on the rows' own lines: not plain 16-bit gossip and push-sum, which they slow; no operator on groups.
+float a_copy;
+uint16_t a_copy16;
+constexpr PushOp with_copy()
+{
+    PushOp op{};
+    op.zout = &a_copy;
+    return op;
+}
+constexpr Push16Op<true> with_copy16()
+{
+    Push16Op<true> op{};
+    op.zout = &a_copy16;
+    return op;
+}
+static_assert(starts_on_lines(MeanOp<1>{}) && starts_on_lines(FusedOp{}) && starts_on_lines(Fused16Op<false>{}) && starts_on_lines(PushOp{}) &&
+              starts_on_lines(with_copy()) && starts_on_lines(with_copy16()) && starts_on_lines(HierFusedOp<1>{}));
+static_assert(!starts_on_lines(Row16Op<false>{}) && !starts_on_lines(Row16Op<true>{}) && !starts_on_lines(Push16Op<true>{}) &&
+              !starts_on_lines(MeanOp<2>{}) && !starts_on_lines(HierFused16Op<false, 8>{}));
+
 // In place, as many wavefronts per CU whatever the workgroup's size: two workgroups of eight, or eight of two where
 // rows are short or 1,024 rows' schedules leave no room for more.
 template <class Op>
@@ -88,13 +108,6 @@ template <class Op>
 constexpr bool not_split(int n, int64_t P, int S, Op op = Op{})
 {
     return in_place(n, P, S, 0, op).parts.parts == 0;
-}
-float a_copy;
-constexpr PushOp with_copy()
-{
-    PushOp op{};
-    op.zout = &a_copy;
-    return op;
 }
 
 // The split: as many parts as make kPartJobs wavefronts and the rows and the registers allow, as many tiles a workgroup as
