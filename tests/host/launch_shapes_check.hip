@@ -173,6 +173,32 @@ static_assert(even_is<Row16Op<false>>(500, 512 * 1025, 1, 1, 4, 5, 3) && !in_pla
 static_assert(walks<Row16Op<false>>(115, 1047248, 2) && walks<FusedOp>(119, 522620, 8) && walks<MeanOp<1>>(29, 523264, 8) &&
               walks<MeanOp<1>>(30, 1047296, 3) && even_is<MeanOp<1>>(163, 522496, 16, 1, 8, 3, 5) &&
               even_is<FusedOp>(98, 523520, 16, 1, 4, 3, 5) && !even_is<FusedOp>(66, 650762, 20, 2, 4, 5, 3));
+// Every count of waves and slices that the rule chooses: the calls of test_gpu_even_walk.py that are there for it.
+static_assert(even_is<MeanOp<1>>(24, 522735, 17, 1, 8, 3, 5) && even_is<MeanOp<1>>(512, 323055, 17, 2, 8, 3, 5) && even_is<MeanOp<1>>(400, 455919, 17, 2, 8, 4, 4) &&
+              even_is<MeanOp<1>>(400, 688623, 1, 2, 8, 6, 2));
+static_assert(even_is<Row16Op<false>>(33, 1045487, 17, 1, 4, 3, 5) && even_is<Row16Op<true>>(24, 1033199, 17, 1, 4, 8, 2) &&
+              even_is<Row16Op<false>>(400, 911855, 17, 2, 4, 4, 4));
+static_assert(even_is<FusedOp>(24, 390639, 8, 1, 4, 3, 5) && even_is<FusedOp>(512, 323055, 17, 2, 4, 3, 5) && even_is<FusedOp>(400, 455919, 17, 2, 4, 4, 4));
+static_assert(even_is<Fused16Op<true>>(24, 2612207, 17, 1, 2, 4, 2) && even_is<Fused16Op<false>>(24, 656879, 1, 1, 2, 6, 2) &&
+              even_is<Fused16Op<true>>(24, 524783, 1, 1, 2, 5, 2));
+static_assert(even_is<PushOp>(24, 525039, 1, 1, 8, 3, 5) && even_is<PushOp>(24, 590319, 1, 2, 2, 5, 3) && even_is<PushOp>(24, 655599, 1, 2, 2, 6, 2) &&
+              even_is<PushOp>(400, 458991, 1, 2, 2, 4, 4) && even_is<Push16Op<false>>(64, 656879, 1, 1, 4, 6, 2));
+// That test's calls at both ends of the rule: whole slices, columns beyond them, segments (push-sum has one).
+template <class Op>
+constexpr bool even_at(int n, int slices, int beyond, int S)
+{
+    return in_place<Op>(n, static_cast<int64_t>(slices) * kWave * Op::kElems + beyond, S).even;
+}
+static_assert(even_at<MeanOp<1>>(24, 1024, 1, 3) && even_at<MeanOp<1>>(120, 1172, -25, 8) && even_at<MeanOp<1>>(101, 1172, 3, 40) && even_at<MeanOp<1>>(513, 1030, 9, 5) &&
+              even_at<FusedOp>(24, 1024, 1, 3) && even_at<FusedOp>(120, 1172, -25, 8) && even_at<FusedOp>(25, 1279, 77, 30) && even_at<FusedOp>(513, 1030, 9, 5) &&
+              even_at<PushOp>(24, 1024, 1, 1) && even_at<PushOp>(25, 1279, 77, 1) && even_at<Row16Op<true>>(24, 1024, 1, 3) && even_at<Row16Op<true>>(101, 1172, 3, 40) &&
+              even_at<Push16Op<true>>(24, 1024, 1, 1) && even_at<Push16Op<true>>(25, 1279, 77, 1));
+static_assert(!even_at<MeanOp<1>>(23, 1024, 1, 3) && !even_at<MeanOp<1>>(25, 1279, 77, 30) && !even_at<MeanOp<1>>(26, 6143, 5, 2) &&
+              !even_at<FusedOp>(23, 1024, 1, 3) && !even_at<Row16Op<true>>(513, 1030, 9, 5) && !even_at<Fused16Op<true>>(24, 1024, 1, 3));
+// Its last lengths: 6,144 slices, steps 8,192.
+static_assert(even_at<MeanOp<1>>(480, 6144, 0, 24) && !even_at<MeanOp<1>>(480, 6144, 1, 24) && even_at<PushOp>(400, 6144, 0, 1) && !even_at<PushOp>(400, 6144, 1, 1) &&
+              even_at<FusedOp>(200, 8192, 0, 24) && !even_at<FusedOp>(200, 8192, 1, 24));
+
 // Steps on 16-bit rows: no workgroups of three waves.
 static_assert(walks<Fused16Op<false>>(61, 3505152, 2));
 

@@ -1,5 +1,6 @@
 """In place on many plain rows of medium length, where the waves of a workgroup are chosen to deal the tiles out evenly:
-the bits of the out-of-place kernels at both ends of that rule's lengths and rows, and where neither side takes it."""
+the bits of the out-of-place kernels at both ends of that rule's lengths and rows, where the split or the usual walk serves, and
+at every count of waves and slices that the rule chooses.  Which call takes what is pinned in tests/host/launch_shapes_check.hip."""
 import pytest
 import torch
 
@@ -18,7 +19,22 @@ SGD = (0.1, 0.9, 1e-4)
 @pytest.mark.parametrize("n,slices,beyond,S", [(24, 1024, 1, 3), (23, 1024, 1, 3), (120, 1172, -25, 8), (25, 1279, 77, 30), (26, 6143, 5, 2), (101, 1172, 3, 40), (513, 1030, 9, 5),
                                                (500, 1100, 0, 1)])
 def test_even_walk_equals_the_out_of_place_kernel(kind, rows, n, slices, beyond, S):
-    P = slices * (256 if rows == "f32" else 512) + beyond
+    in_place_equals_out_of_place(kind, rows, n, slices * (256 if rows == "f32" else 512) + beyond, S)
+
+
+# one slice a lane: three, four, six and eight waves a workgroup; two slices: three to six
+@pytest.mark.parametrize("kind,rows,n,P,S", [
+    ("gossip", "f32", 24, 522_735, 17), ("gossip", "f32", 512, 323_055, 17), ("gossip", "f32", 400, 455_919, 17), ("gossip", "f32", 400, 688_623, 1),
+    ("gossip", "bf16", 33, 1_045_487, 17), ("gossip", "f16", 24, 1_033_199, 17), ("gossip", "bf16", 400, 911_855, 17),
+    ("step", "f32", 24, 390_639, 8), ("step", "f32", 512, 323_055, 17), ("step", "f32", 400, 455_919, 17),
+    ("step", "f16", 24, 2_612_207, 17), ("step", "bf16", 24, 656_879, 1), ("step", "f16", 24, 524_783, 1),
+    ("push", "f32", 24, 525_039, 1), ("push", "f32", 24, 590_319, 1), ("push", "f32", 24, 655_599, 1), ("push", "f32", 400, 458_991, 1),
+    ("push", "bf16", 64, 656_879, 1)])
+def test_every_shape_of_the_even_walk(kind, rows, n, P, S):
+    in_place_equals_out_of_place(kind, rows, n, P, S)
+
+
+def in_place_equals_out_of_place(kind, rows, n, P, S):
     ld, dtype = (P + 7) // 8 * 8 + 8, {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[rows]
     suffix = "" if rows == "f32" else "_" + rows
     print(kind, rows, n, P, S, flush=True)

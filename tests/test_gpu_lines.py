@@ -1,7 +1,8 @@
 """Out of place where rows begin inside lines of 128 bytes and every row's tiles start on its own lines: the oracle's bits
 and nothing written beside the rows, at the shortest rows that take that kernel, at rows whose last tile exists for some
-of them only, with segments that end inside the shift, in both layouts of the row order, from matrices that begin inside
-a line themselves."""
+of them only, with segments that end inside the shift and with more of them than a wavefront has lanes, in both layouts of the row
+order, from matrices that begin inside a line themselves.  (16-bit gossip, and 16-bit push-sum without the copy, stay in the column
+grid: the same calls there.)"""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +26,9 @@ def inside_lines(rows, ld, dtype, first, fill):
 
 
 def offsets(P, S):
+    if S > 63:                                                                 # the first ones inside the shift of some rows
+        inner = np.random.default_rng(S).integers(0, P + 1, size=S - 6)
+        return np.array([0, 3, 8, 8, 20, 50, *np.sort(inner[inner >= 50]), *[P] * int((inner < 50).sum()), P], dtype=np.int64)
     edges = [P // 3, P // 3 + 5, P // 2, P // 2, P - 3, P - 1][:S - 1]         # short, empty, and at the row end
     return np.array([0, *edges, P], dtype=np.int64)
 
@@ -33,7 +37,8 @@ def offsets(P, S):
 @pytest.mark.parametrize("slices", [-1, 2, 4])
 @pytest.mark.parametrize("rows", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("n,P,S,pad,first", [(2, 2048, 1, 0, 1), (5, 2049, 3, 1, 0), (9, 4096, 7, 3, 7), (16, 4093, 4, 5, 2),
-                                             (33, 9001, 7, 1, 0), (3, 70_000, 2, 7, 3), (12, 30_720, 5, 1, 4)])
+                                             (33, 9001, 7, 1, 0), (3, 70_000, 2, 7, 3), (12, 30_720, 5, 1, 4),
+                                             (40, 5001, 70, 3, 0), (300, 4097, 65, 1, 5)])
 def test_gossip(rows, n, P, S, pad, first, slices):
     e = 4 if rows == "f32" else 8
     ld, so, pe = (P + e - 1) // e * e + pad * e, offsets(P, S), O.topology(S, n, S, 0, 1)[0]
@@ -58,8 +63,8 @@ def test_gossip(rows, n, P, S, pad, first, slices):
         assert (flat == fill).all()                            # nothing beside the rows
 
 
-@pytest.mark.parametrize("rows", ["f32", "bf16"])
-@pytest.mark.parametrize("n,P,S,pad", [(4, 2049, 3, 1), (17, 5000, 7, 3), (9, 40_001, 5, 1)])
+@pytest.mark.parametrize("rows", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("n,P,S,pad", [(4, 2049, 3, 1), (17, 5000, 7, 3), (9, 40_001, 5, 1), (150, 3001, 70, 1)])
 def test_optimizer_step_and_push_sum(rows, n, P, S, pad):
     e = 4 if rows == "f32" else 8
     ld, so, pe = (P + e - 1) // e * e + pad * e, offsets(P, S), O.topology(S, n, S, 0, 1)[0]
@@ -70,10 +75,11 @@ def test_optimizer_step_and_push_sum(rows, n, P, S, pad):
         step, push, put, raw = cx.cx_sgd_fused_mix, cx.cx_pushsum_mix, dev, host
         want_x, want_v = (once(t) for t in O.sgd_fused_mix_f64(x, v, g, *SGD, P, so, pe))
     else:
-        step, push = cx.cx_sgd_fused_mix_bf16, cx.cx_pushsum_mix_bf16
+        step, push = getattr(cx, "cx_sgd_fused_mix_" + rows), getattr(cx, "cx_pushsum_mix_" + rows)
         put, raw = lambda a: dev(a.view(np.int16)), lambda t: host(t).view(np.uint16)
-        x, g = O.f32_to_bf16(x), O.f32_to_bf16(g)
-        want_x, want_v = O.sgd_fused_mix16("bf16", x, v, g, *SGD, P, so, pe)
+        narrow = O.f32_to_bf16 if rows == "bf16" else O.f32_to_f16
+        x, g = narrow(x), narrow(g)
+        want_x, want_v = O.sgd_fused_mix16(rows, x, v, g, *SGD, P, so, pe)
     xd, vd, gd = put(x), dev(v), put(g)
     y, vo, wo, z = torch.full_like(xd, 7), torch.full_like(vd, 7.0), torch.empty(n, device="cuda:0"), torch.full_like(xd, 7)
     with Tuning(ordered=1):
@@ -82,10 +88,11 @@ def test_optimizer_step_and_push_sum(rows, n, P, S, pad):
     assert same(raw(y)[:, :P], want_x[:, :P]) and same_bits(host(vo)[:, :P], want_v[:, :P])
     assert (y[:, P:] == 7).all() and (vo[:, P:] == 7).all()
     results = []
-    for ordered in (0, 1):                                     # against the natural order, which takes gather_kernel
-        y.fill_(7)
-        with Tuning(ordered=ordered):
-            push(xd, y, dev(w), wo, z, P, n // 2)
-        results.append((raw(y), raw(z), host(wo)))
-    assert all((a.view(np.uint8) == b.view(np.uint8)).all() for a, b in zip(*results))
-    assert (y[:, P:] == 7).all() and (z[:, P:] == 7).all()
+    for ordered in (0, 1):                                     # against the natural order, which takes the column grid
+        for copy in (z, None):
+            y.fill_(7)
+            with Tuning(ordered=ordered):
+                push(xd, y, dev(w), wo, copy, P, n // 2)
+            assert (y[:, P:] == 7).all() and (z[:, P:] == 7).all()
+            results.append((raw(y), raw(z), host(wo)))
+    assert all((a.view(np.uint8) == b.view(np.uint8)).all() for other in results[1:] for a, b in zip(results[0], other))

@@ -46,8 +46,21 @@ def kernels(tmp_path_factory):
     ("HierFusedOp<4>", 3), ("HierFusedOp<7>", 3), ("Row16Op<false, 1>", 8), ("Row16Op<false, 4>", 3), ("Row16Op<false, 8>", 3),
     ("HierFused16Op<false, 4>", 3)])
 def test_boundary_tiles_do_not_cost_the_out_of_place_kernels_wavefronts(kernels, op, waves):
-    registers = kernels[f"gather_kernel<{op}, 1, true, false>"][0]
-    assert 512 // (-(-registers // 8) * 8) >= waves, registers
+    assert wavefronts(kernels, op, 1) >= waves
+
+
+def wavefronts(kernels, op, slices):
+    return 512 // (-(-kernels[f"gather_kernel<{op}, {slices}, true, false>"][0] // 8) * 8)
+
+
+# those that matrices beyond the last-level cache take: stores written through, tiles on the rows' own lines (push-sum has two slices)
+@pytest.mark.parametrize("op,slices,waves", [
+    ("ThroughOp", 1, 8), ("OnLines<ThroughOp>", 1, 8), ("OnLines<FusedOp>", 1, 5), ("OnLines<PushOp>", 2, 5), ("OnLines<Push16Op<false> >", 2, 4),
+    ("OnLines<Push16Op<true> >", 2, 4), ("OnLines<Fused16Op<false> >", 1, 4), ("OnLines<Fused16Op<true> >", 1, 4)])
+def test_rows_on_their_own_lines_keep_their_wavefronts(kernels, op, slices, waves):
+    assert wavefronts(kernels, op, slices) >= waves
+    plain = op.removeprefix("OnLines<").removesuffix(">").strip()
+    assert wavefronts(kernels, op, slices) >= wavefronts(kernels, plain, slices)
 
 
 def test_no_mixing_kernel_keeps_registers_in_scratch(kernels):
