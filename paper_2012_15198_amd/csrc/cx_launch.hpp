@@ -611,18 +611,22 @@ bool launch_parts(const Op &op, const PartShape &s, const MixArgs &a)
 // the split's four tiles as well, 235 of five), so waves and slices are chosen for the least of that, and of equals the one with
 // fewer, wider workgroups.  From kEvenLoad slices a CU on, below which a CU has too few wavefronts and the split or mix_kernel's
 // short shapes serve, where the other shape is more than kEvenGain per cent off (at 8 slices for 7 the step on 117 x 398,433
-// took 171 us for 166), and up to kEvenRows16 plain 16-bit rows (831 x 943,628 899 us, 738 before).
+// took 171 us for 166).  The lines for plain 16-bit rows and for long rows were drawn with two workgroups a CU whatever their size
+// (831 x 943,628 899 us, 738 before; bf16 gossip on 30 x 3,322,532 94, 86 before).  With the present cap the even walk would take 0.91
+// of the time beyond kEvenRows16 (0.79 to 1.06, 53 shapes); beyond kEvenMost its workgroups of three waves 0.95 to 1.09, of five
+// 0.91 to 1.08, two slices 0.91 to 0.96 (77 shapes).
 // The cap on resident workgroups is one on wavefronts, as in walk_shape: three waves, two / five workgroups a CU, us: fp32 gossip
 // on 24 x 523,592 in 16 segments 29.1 / 24.0, bf16 gossip on 105 x 1,045,250 in 24 117 / 101, fp32 push-sum on 439 x 543,169
 // 418 / 392; four to six waves and two slices are as long either way.  Steps on 16-bit rows keep two workgroups of four waves and
 // more: three waves took 0.96 to 1.04 of the time of eight, five workgroups of them 0.96 to 1.07 (32 shapes of 6,423 to 6,897 slices).
-// Before / now, us: fp32 optimizer step on 256 x 300,007 342 / 314; fp32 gossip on 265 x 278,339
-// 136 / 117, on 611 x 512,664 525 / 474; fp32 push-sum on 171 x 1,202,009 321 / 294, on 34 x 598,370 38 / 30; bf16 gossip on
-// 118 x 626,350 75 / 60; bf16 optimizer step on 158 x 3,248,642 1,553 / 1,351, on 75 x 2,115,692 506 / 413.  More than 24 slices a CU
-// of plain rows lost (bf16 gossip on 30 x 3,322,532 86 / 94) and keep the shapes they had.
+// Before / now, us: fp32 optimizer step on 256 x 300,007 342 / 314; fp32 gossip on 265 x 278,339 136 / 117, on 611 x 512,664
+// 525 / 474; fp32 push-sum on 171 x 1,202,009 321 / 294, on 34 x 598,370 38 / 30; bf16 gossip on 118 x 626,350 75 / 60; bf16
+// optimizer step on 158 x 3,248,642 1,553 / 1,351, on 75 x 2,115,692 506 / 413.
 // It takes 65 to 94 % of the lengths up to 1,535 slices (of 16-bit steps 24 %) and few of the longer ones, up to 4 %, except of fp32
 // push-sum without the copy (57 % up to 3,071, 29 % up to 6,143) and 16-bit steps (28 % from 3,072 on, 10 % from 6,144 on): elsewhere
-// the other shapes fill the CUs.  Time over theirs on 153 shapes drawn from those it takes: geometric mean 0.89, 0.72 to 1.012.
+// the other shapes' CUs count as full, the split's two-wave workgroups too, though they are slower than that (fp32 optimizer step on
+// 263 x 589,905 722 split, 616 in workgroups of five waves).  Time over the other shapes' on 153 shapes drawn from those it takes:
+// geometric mean 0.89, 0.72 to 1.012.
 // ---------------------------------------------------------------------------------
 constexpr int kEvenRows = 24, kEvenRows16 = 500, kEvenLoad = 5, kEvenMost = 24, kEvenMostStep = 32, kEvenGain = 15;
 
@@ -653,8 +657,8 @@ constexpr WalkShape even_shape(const Op &op, int n, int64_t P, int S)
             best = WalkShape{U, 0, waves, kHalf && kStep ? 2 : 2 * kMaxWavesPerBlock / waves};
         }
     if (!best.U) return kNone;
-    // where the split serves, few waves of a narrow tile each do not replace it (bf16 optimizer step on 506 x 587,964 943 us
-    // split, 973 with three waves)
+    // where the split serves, few waves of a narrow tile each do not replace it (fp32 gossip and optimizer step, three waves 1.02 of
+    // the split's time, 0.93 to 1.07, four 0.99; plain 16-bit rows would gain, 0.91, 0.85 to 0.95: 26 shapes)
     const PartShape split = part_shape(op, n, P, S);
     if (split.parts && (kHalf ? best.waves : best.waves * best.U) < kEvenLoad) return kNone;
     // The first workgroup of pieces does not count for the walk as it is otherwise: beside a full round of tiles it makes no round
