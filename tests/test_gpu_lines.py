@@ -63,8 +63,8 @@ def test_gossip(rows, n, P, S, pad, first, slices):
         assert (flat == fill).all()                            # nothing beside the rows
 
 
-@pytest.mark.parametrize("rows", ["f32", "bf16", "f16"])
-@pytest.mark.parametrize("n,P,S,pad", [(4, 2049, 3, 1), (17, 5000, 7, 3), (9, 40_001, 5, 1), (150, 3001, 70, 1)])
+@pytest.mark.parametrize("rows", ["f32", "bf16"])
+@pytest.mark.parametrize("n,P,S,pad", [(4, 2049, 3, 1), (17, 5000, 7, 3), (9, 40_001, 5, 1)])
 def test_optimizer_step_and_push_sum(rows, n, P, S, pad):
     e = 4 if rows == "f32" else 8
     ld, so, pe = (P + e - 1) // e * e + pad * e, offsets(P, S), O.topology(S, n, S, 0, 1)[0]
@@ -75,11 +75,10 @@ def test_optimizer_step_and_push_sum(rows, n, P, S, pad):
         step, push, put, raw = cx.cx_sgd_fused_mix, cx.cx_pushsum_mix, dev, host
         want_x, want_v = (once(t) for t in O.sgd_fused_mix_f64(x, v, g, *SGD, P, so, pe))
     else:
-        step, push = getattr(cx, "cx_sgd_fused_mix_" + rows), getattr(cx, "cx_pushsum_mix_" + rows)
+        step, push = cx.cx_sgd_fused_mix_bf16, cx.cx_pushsum_mix_bf16
         put, raw = lambda a: dev(a.view(np.int16)), lambda t: host(t).view(np.uint16)
-        narrow = O.f32_to_bf16 if rows == "bf16" else O.f32_to_f16
-        x, g = narrow(x), narrow(g)
-        want_x, want_v = O.sgd_fused_mix16(rows, x, v, g, *SGD, P, so, pe)
+        x, g = O.f32_to_bf16(x), O.f32_to_bf16(g)
+        want_x, want_v = O.sgd_fused_mix16("bf16", x, v, g, *SGD, P, so, pe)
     xd, vd, gd = put(x), dev(v), put(g)
     y, vo, wo, z = torch.full_like(xd, 7), torch.full_like(vd, 7.0), torch.empty(n, device="cuda:0"), torch.full_like(xd, 7)
     with Tuning(ordered=1):
@@ -88,11 +87,31 @@ def test_optimizer_step_and_push_sum(rows, n, P, S, pad):
     assert same(raw(y)[:, :P], want_x[:, :P]) and same_bits(host(vo)[:, :P], want_v[:, :P])
     assert (y[:, P:] == 7).all() and (vo[:, P:] == 7).all()
     results = []
-    for ordered in (0, 1):                                     # against the natural order, which takes the column grid
-        for copy in (z, None):
-            y.fill_(7)
-            with Tuning(ordered=ordered):
-                push(xd, y, dev(w), wo, copy, P, n // 2)
-            assert (y[:, P:] == 7).all() and (z[:, P:] == 7).all()
-            results.append((raw(y), raw(z), host(wo)))
-    assert all((a.view(np.uint8) == b.view(np.uint8)).all() for other in results[1:] for a, b in zip(results[0], other))
+    for ordered in (0, 1):                                     # against the natural order, which takes gather_kernel
+        y.fill_(7)
+        with Tuning(ordered=ordered):
+            push(xd, y, dev(w), wo, z, P, n // 2)
+        results.append((raw(y), raw(z), host(wo)))
+    assert all((a.view(np.uint8) == b.view(np.uint8)).all() for a, b in zip(*results))
+    assert (y[:, P:] == 7).all() and (z[:, P:] == 7).all()
+
+
+@pytest.mark.parametrize("rows", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("n,P,S,pad", [(4, 2049, 3, 1), (17, 5000, 7, 3), (9, 40_001, 5, 1), (150, 3001, 70, 1)])
+def test_step_and_push_sum_have_the_bits_of_the_column_grid(rows, n, P, S, pad):
+    e, dtype = (4, torch.float32) if rows == "f32" else (8, torch.bfloat16 if rows == "bf16" else torch.float16)
+    ld, so, pe = (P + e - 1) // e * e + pad * e, dev(offsets(P, S)), dev(O.topology(S, n, S, 0, 1)[0])
+    x, v, g = (dev(WL.gen_matrix(n, P, s, seed=P + n, ld=ld, stream=k)) for k, s in enumerate((0.05, 0.02, 0.01)))
+    x, g, w = x.to(dtype), g.to(dtype), dev(np.random.default_rng(n).uniform(0.5, 1.5, n).astype(np.float32))
+    suffix, results = "" if rows == "f32" else "_" + rows, []
+    print(rows, n, P, S, pad, flush=True)
+    for ordered in (0, 1):                                     # the natural order takes the column grid
+        a, b, c, z = (torch.full_like(x, 7) for _ in range(4))
+        vo, wb, wc = torch.full_like(v, 7), torch.empty_like(w), torch.empty_like(w)
+        with Tuning(ordered=ordered):
+            getattr(cx, "cx_sgd_fused_mix" + suffix)(x, a, v, vo, g, *SGD, P, so, pe)
+            getattr(cx, "cx_pushsum_mix" + suffix)(x, b, w, wb, z, P, n // 2)
+            getattr(cx, "cx_pushsum_mix" + suffix)(x, c, w, wc, None, P, n // 2)
+        results.append([host(t.view(torch.uint8)) for t in (a, vo, b, wb, z, c, wc)])
+        assert all((t[:, P:] == 7).all() for t in (a, vo, b, z, c))
+    assert all((p == q).all() for p, q in zip(*results))
