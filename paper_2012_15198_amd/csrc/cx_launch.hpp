@@ -352,7 +352,7 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
         // locality, longer ones push the previous visit out of L2);
         // natural row order: the whole cluster (all rows) should fit one XCD's 4 MB L2
         const int64_t row_bytes = chunk_cols * (16 / Op::kElems) * a.rows_per_gossip_row;
-        cl = ordered ? (static_cast<int64_t>(VisitKb<Op>::of(a.n, a.P)) << 10) / row_bytes : (4 << 20) / (row_bytes * a.n);
+        cl = ordered ? (static_cast<int64_t>(VisitKb<Op>::of(a.n, a.P, a.S)) << 10) / row_bytes : (4 << 20) / (row_bytes * a.n);
         if (cl < 1) cl = 1;
     }
     if (ordered) {                                // the order table must fit its slot

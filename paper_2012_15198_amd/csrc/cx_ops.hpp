@@ -48,9 +48,10 @@ constexpr bool two_waves(int G, int rows, int64_t P, bool whole_lines)
 // many rows only, since the last 2 * D steps of a walk are slower ones.
 constexpr int ring_for(int n) { return n >= 128 ? 8 : 4; }
 
-// Gossiping rows that are few, and columns of rows that are long, for the visit of the out-of-place kernel (VisitKb).
+// For the visit of the out-of-place kernel (VisitKb): gossiping rows that are few, and whether a longer visit seldom meets the edge of
+// a segment (they are `cols` columns and more) or does not suffer by it (rows that may be ordered by the tile, see try_gather).
 constexpr int kFewRows = 8;
-constexpr int64_t kLongVisits = 2 << 20;
+constexpr bool inside_segments(int n, int64_t P, int S, int64_t cols) { return n >= kFewRows || S == 1 || P >= cols * S; }
 
 // Plain gossip (G == 1) and hierarchical mode (a gossiping row = a group of G rows).
 // G == 1 is Algorithm 1's averaging line in fp32, as written.  For G > 1 the group sum (rows in
@@ -68,7 +69,10 @@ struct MeanOp {
     // (all G rows behind it) per XCD -- measured optima on MI355X (see VisitKb)
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 4, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0} : GatherShape{1, 8, 768, 0};
-    static constexpr int visit_kb(int n, int64_t) { return G < 8 || n > kFewRows ? 0 : G == 8 ? 512 : 256; }
+    static constexpr int visit_kb(int n, int64_t P, int S)
+    {
+        return G < 8 || n > kFewRows ? 0 : G == 8 && inside_segments(n, P, S, 65536) ? 512 : 256;
+    }
     static constexpr WalkShape kWalk =
         G == 1 ? WalkShape{2, 8, 8, 2} : G == 2 ? WalkShape{2, 4, 8, 2} : G <= 5 ? WalkShape{2, 2, 8, 2}
         : G <= 8 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
@@ -222,33 +226,34 @@ Op with_stage_base(const Op &op, size_t base)
     return copy;
 }
 
-// Visit length of the out-of-place kernel: kGather.visit_kb, unless the operator's visit_kb(rows, P) names another one (0: it does not).
+// Visit length of the out-of-place kernel: kGather.visit_kb, unless the operator's visit_kb(rows, P, S) names another one (0: it does not).
 //
 // Operators on groups, in chunks of 8 KB of every matrix row (before the clusters are shortened to fill their last round).  Eight or
 // sixteen chunks, with which the XCDs' visits of a row together begin and end on multiples of 512 KB, gain on matrices as torch
-// allocates them for some operators and group sizes; the others keep what they had.  Time over that with the visit before, 20 to 45
-// shapes of 250,000 to 11,689,512 columns and 2 to 64 gossiping rows each, geometric mean (range), and the visit taken:
-//   fp32 mean             groups of 8, up to 8 rows    8 for 4            0.99 (0.95 to 1.014)   8
-//   16-bit mean           groups of 3, 4, 6           16 for 10, 8, 8     0.98 (0.88 to 1.04)   16
-//                         groups of 5                  8 for 9            1.00 (0.97 to 1.04)    9
-//                         groups of 7, 8              16 for 6            0.96 (0.91 to 1.013)  16
-//                           up to 8 rows                                  1.00 (0.86 to 1.06)    6 (on spread matrices 0.995 to 1.055)
-//   fp32 gradient step    groups of 8                 16 for 12 (few: 4)  0.98 (0.93 to 1.014)  16
-//                         groups of 5, 7              16 for 19, 13       1.00 (0.92 to 1.05)   19, 13
-//   16-bit gradient step  groups of 3                  8 for 10           0.99 (0.94 to 1.013)   8
-//                         groups of 8, long rows       8 for 6            0.98 (0.97 to 1.005)   8
-//                           shorter than kLongVisits                      1.02 (0.94 to 1.083)   6
-//                         groups of 5, 7               8 for 9, 6         1.01 (0.94 to 1.14)    9, 6
+// allocates them for some operators and group sizes.  Time over that with the visit otherwise taken, shapes of 250,000 to
+// 25,000,000 columns, 2 to 40 gossiping rows and 1 to 32 segments, several matrices in turn, geometric mean (range):
+//   fp32 mean             groups of 8, up to 8 rows    8 for 4              90 shapes   0.995 (0.97 to 1.025)
+//   16-bit mean           groups of 4, 6              16 for 8             160          0.97 (0.86 to 1.03)
+//                         groups of 7, 8, beyond 8    16 for 6              70          0.97 (0.88 to 1.02)
+//   fp32 gradient step    groups of 8                 16 for 12 (few: 4)   120          0.98 (0.92 to 1.02)
+// Not where fewer rows than kFewRows, which are ordered by the cluster, are cut into segments shorter than four visits, of 16-bit rows
+// ten: every cluster with an edge takes the general path, and longer clusters have more of them.  Longer / shorter visit, us: fp32
+// gradient step on 24 x 852,780 in 29 segments 47.0 / 41.9, 16-bit mean of groups of 4 on 20 x 2,549,454 in 20 46.7 / 44.1, of groups
+// of 6 on 30 x 5,699,719 in 11 142.9 / 134.3, fp32 mean on 56 x 407,136 in 24 43.4 / 42.2.
+// Not taken, since they gained nothing or lost: 16-bit mean of groups of 3, 16 for 10 chunks (46 shapes) 0.994, up to 1.12, of 5, 8 for 9, 1.00,
+// of 7 and 8 with up to 8 rows 1.00, up to 1.06; fp32 gradient step of groups of 5 and 7, 16 for 19 and 13, 1.00, up to 1.05; 16-bit
+// gradient step of groups of 3, 8 for 10 (40) 0.993, up to 1.066, of 5 and 7 1.01, up to 1.14, of 8, 8 for 6 (70, two million columns
+// and more) 1.000, up to 1.068.
 // On matrices spread over the physical memory what is taken gains less or loses: fp32 mean 0.980 to 1.010, 16-bit mean 0.97 to
-// 1.013, fp32 gradient step 0.983 to 1.030, 16-bit gradient step 0.985 to 1.008.
+// 1.013, fp32 gradient step 0.983 to 1.030.
 // With groups of 16, at most kFewRows gossiping rows visit 256 KB: their longest cycle's visits then fit one XCD's 4 MB L2.
 template <class Op, class = void>
 struct VisitKb {
-    static constexpr int of(int, int64_t) { return Op::kGather.visit_kb; }
+    static constexpr int of(int, int64_t, int) { return Op::kGather.visit_kb; }
 };
 template <class Op>
-struct VisitKb<Op, std::void_t<decltype(Op::visit_kb(0, 0))>> {
-    static constexpr int of(int n, int64_t P) { return Op::visit_kb(n, P) ? Op::visit_kb(n, P) : Op::kGather.visit_kb; }
+struct VisitKb<Op, std::void_t<decltype(Op::visit_kb(0, 0, 1))>> {
+    static constexpr int of(int n, int64_t P, int S) { return Op::visit_kb(n, P, S) ? Op::visit_kb(n, P, S) : Op::kGather.visit_kb; }
 };
 
 template <class Op, class = void>
@@ -359,8 +364,11 @@ struct HierFusedOp {
     // out-of-place launch: slices, waves, group visit KB per XCD
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 8, 256, 0} : G <= 4 ? GatherShape{1, 8, 512, 0}
-        : G == 8 ? GatherShape{1, 8, 1024, 0} : GatherShape{1, 8, 768, 0};
-    static constexpr int visit_kb(int n, int64_t) { return G <= 8 || n > kFewRows ? 0 : 256; }      // see VisitKb
+        : GatherShape{1, 8, 768, 0};
+    static constexpr int visit_kb(int n, int64_t P, int S)                          // see VisitKb
+    {
+        return G == 8 && inside_segments(n, P, S, 131072) ? 1024 : G >= 8 && n <= kFewRows ? 256 : 0;
+    }
     static constexpr WalkShape kWalk = G <= 4 ? WalkShape{1, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G <= 2 ? 2 : 1;
     template <int U, int D> static constexpr bool kSpills = G == 5 && D == 4;

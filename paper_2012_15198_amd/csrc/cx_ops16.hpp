@@ -126,8 +126,11 @@ struct Row16Op {
     template <int U> using Work = std::conditional_t<G == 1, Tile<2 * U>, WideTile<2 * U>>;   // 8 values per slice
     static constexpr int kRawPerSlice = G;
     static constexpr GatherShape kGather =
-        G == 1 ? GatherShape{1, 8, 96, 0} : GatherShape{1, 8, G == 5 ? 384 : 128 * G, 0};          // see VisitKb
-    static constexpr int visit_kb(int n, int64_t) { return G >= 7 && n <= kFewRows ? 384 : 0; }
+        G == 1 ? GatherShape{1, 8, 96, 0} : G <= 4 ? GatherShape{1, 8, 256, 0} : GatherShape{1, 8, 384, 0};
+    static constexpr int visit_kb(int n, int64_t P, int S)                          // see VisitKb
+    {
+        return (G == 4 || G == 6 || (G >= 7 && n > kFewRows)) && inside_segments(n, P, S, 655360) ? 128 * G : 0;
+    }
     static constexpr WalkShape kWalk = G == 1 ? WalkShape{2, 4, 8, 2} : WalkShape{1, 2, 8, 2};
     static constexpr int kMaxU = G == 1 ? 4 : 1;           // grouped: one slice per lane fills the registers
     template <int U, int D> static constexpr bool kSpills = U == 4 && D == 4;
@@ -421,8 +424,7 @@ struct HierFused16Op {
     template <int U> using Work = WideTile<2 * U>;
     static constexpr int kRawPerSlice = G + 3;             // G gradient rows, x, and two registers of v
     static constexpr GatherShape kGather =
-        G == 1 || G == 3 ? GatherShape{1, 8, 192, 0} : G <= 4 ? GatherShape{1, 8, 256, 0} : GatherShape{1, 8, 384, 0};
-    static constexpr int visit_kb(int, int64_t P) { return G == 8 && P >= kLongVisits ? 512 : 0; }  // see VisitKb
+        G == 1 ? GatherShape{1, 8, 192, 0} : G <= 4 ? GatherShape{1, 8, 256, 0} : GatherShape{1, 8, 384, 0};
     static constexpr WalkShape kWalk{1, 2, 8, 2};
     static constexpr int kMaxU = 1;
     static constexpr int kStageBytes = kStageBytesPerWave;

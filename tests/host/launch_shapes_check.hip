@@ -110,22 +110,23 @@ static_assert(all_lengths<MeanOp<1>>(500, 1, 1537, 2304, true) && all_lengths<Me
 static_assert(all_lengths<FusedOp>(64, 8, 6145, 7168, true) && all_lengths<FusedOp>(64, 8, 7169, 20000, false) &&
               all_lengths<FusedOp>(15, 8, 400, 20000, false) && all_lengths<PushOp>(64, 1, 1025, 20000, false));
 
-// Visits of the out-of-place kernel, KB: longer ones of operators on groups only where they gain.
+// Visits of the out-of-place kernel, KB: longer ones of operators on groups only where they gain.  Seven rows in segments shorter
+// than `cols` and of that length, seven rows in one segment, eight and nine rows in many.
 template <class Op>
-constexpr bool visits(int few_short, int few_long, int many_short, int many_long)
+constexpr bool visits(int cut, int whole, int eight, int nine, int64_t cols = 655360)
 {
     using Kb = VisitKb<Op>;
-    constexpr int64_t kEdge = 2 << 20;
-    return Kb::of(8, kEdge - 1) == few_short && Kb::of(8, kEdge) == few_long && Kb::of(9, kEdge - 1) == many_short && Kb::of(9, kEdge) == many_long;
+    return Kb::of(7, cols * 5 - 1, 5) == cut && Kb::of(7, cols * 5, 5) == whole && Kb::of(7, 1000, 1) == whole &&
+           Kb::of(8, cols, 5) == eight && Kb::of(9, cols, 5) == nine;
 }
-static_assert(visits<Row16Op<false, 8>>(384, 384, 1024, 1024) && visits<Row16Op<true, 7>>(384, 384, 896, 896) && visits<Row16Op<true, 6>>(768, 768, 768, 768) &&
-              visits<Row16Op<false, 5>>(384, 384, 384, 384) && visits<Row16Op<true, 4>>(512, 512, 512, 512) && visits<Row16Op<false, 1>>(96, 96, 96, 96) &&
-              visits<Push16Op<true>>(192, 192, 192, 192));
-static_assert(visits<HierFused16Op<false, 8>>(384, 512, 384, 512) && visits<HierFused16Op<true, 7>>(384, 384, 384, 384) &&
-              visits<HierFused16Op<true, 5>>(384, 384, 384, 384) && visits<HierFused16Op<false, 3>>(192, 192, 192, 192));
-static_assert(visits<HierFusedOp<8>>(1024, 1024, 1024, 1024) && visits<HierFusedOp<7>>(768, 768, 768, 768) && visits<HierFusedOp<5>>(768, 768, 768, 768) &&
-              visits<HierFusedOp<16>>(256, 256, 768, 768) && visits<MeanOp<8>>(512, 512, 768, 768) && visits<MeanOp<16>>(256, 256, 768, 768) &&
-              visits<MeanLdsOp<8>>(512, 512, 768, 768) && visits<MeanOp<1>>(256, 256, 256, 256));
+static_assert(visits<Row16Op<false, 8>>(384, 384, 384, 1024) && visits<Row16Op<true, 7>>(384, 384, 384, 896) && visits<Row16Op<true, 6>>(384, 768, 768, 768) &&
+              visits<Row16Op<false, 5>>(384, 384, 384, 384) && visits<Row16Op<true, 4>>(256, 512, 512, 512) && visits<Row16Op<true, 3>>(256, 256, 256, 256) &&
+              visits<Row16Op<false, 1>>(96, 96, 96, 96) && visits<Push16Op<true>>(192, 192, 192, 192));
+static_assert(visits<HierFused16Op<false, 8>>(384, 384, 384, 384) && visits<HierFused16Op<true, 7>>(384, 384, 384, 384) &&
+              visits<HierFused16Op<true, 5>>(384, 384, 384, 384) && visits<HierFused16Op<false, 3>>(256, 256, 256, 256));
+static_assert(visits<HierFusedOp<8>>(256, 1024, 1024, 1024, 131072) && visits<HierFusedOp<7>>(768, 768, 768, 768) && visits<HierFusedOp<5>>(768, 768, 768, 768) &&
+              visits<HierFusedOp<16>>(256, 256, 256, 768) && visits<MeanOp<8>>(256, 512, 512, 768, 65536) && visits<MeanOp<16>>(256, 256, 256, 768) &&
+              visits<MeanLdsOp<8>>(256, 512, 512, 768, 65536) && visits<MeanOp<1>>(256, 256, 256, 256));
 
 // Tiles on the rows' own lines: not plain 16-bit gossip and push-sum, which they slow; no operator on groups.
 uint16_t a_copy16;
