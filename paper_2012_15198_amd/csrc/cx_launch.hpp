@@ -392,7 +392,7 @@ bool try_gather(const Op &op, int want_u, int waves, bool waves_fixed, int nt, i
     // segment; one segment needs no words of tiles.  On long rows a tile's word is read from memory for few rows, ahead
     // of all loads (4 x 23,403,072 fp32 in 3 segments: by the cluster 137 us, by the tile 151), and clusters with an edge
     // are few.  The mean staged through LDS needs one row for a whole workgroup, which the order by the cluster gives.
-    const bool edges = !LdsStaged<Op>::value && a.n >= 8 && static_cast<int64_t>(a.S - 1) * kTileOrder >= clusters * nxcd;
+    const bool edges = !LdsStaged<Op>::value && a.n >= kFewRows && static_cast<int64_t>(a.S - 1) * kTileOrder >= clusters * nxcd;
     const bool by_tile = ordered && (a.S == 1 || edges) &&
                          static_cast<int64_t>(a.S) * a.n + (a.S > 1 ? (nchunks + 1) * waves : 0) <= order_entries;
     const dim3 grid(static_cast<unsigned>(cl * nxcd), static_cast<unsigned>(a.n),
