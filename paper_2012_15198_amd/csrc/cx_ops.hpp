@@ -48,9 +48,10 @@ constexpr bool two_waves(int G, int rows, int64_t P, bool whole_lines)
 // many rows only, since the last 2 * D steps of a walk are slower ones.
 constexpr int ring_for(int n) { return n >= 128 ? 8 : 4; }
 
-// For the visit of the out-of-place kernel (VisitKb): gossiping rows that are few, and whether a longer visit seldom meets the edge of
+// For the visit of the out-of-place kernel (VisitKb): gossiping rows that are few, columns of long rows, and whether a longer visit seldom meets the edge of
 // a segment (they are `cols` columns and more) or does not suffer by it (rows that may be ordered by the tile, see try_gather).
 constexpr int kFewRows = 8;
+constexpr int64_t kLongRows = 3000000;
 constexpr bool inside_segments(int n, int64_t P, int S, int64_t cols) { return n >= kFewRows || S == 1 || P >= cols * S; }
 
 // Plain gossip (G == 1) and hierarchical mode (a gossiping row = a group of G rows).
@@ -236,14 +237,15 @@ Op with_stage_base(const Op &op, size_t base)
 //   16-bit mean           groups of 4, 6              16 for 8             160          0.97 (0.86 to 1.03)
 //                         groups of 7, 8, beyond 8    16 for 6              70          0.97 (0.88 to 1.02)
 //   fp32 gradient step    groups of 8                 16 for 12 (few: 4)   120          0.98 (0.93 to 1.02)
+//   16-bit gradient step  groups of 8, see below       8 for 6             100          0.994 (0.97 to 1.04)
 // Not where fewer rows than kFewRows, which are ordered by the cluster, are cut into segments shorter than four visits, of 16-bit rows
 // ten: every cluster with an edge takes the general path, and longer clusters have more of them.  Longer / shorter visit, us: fp32
 // gradient step on 24 x 852,780 in 29 segments 47.0 / 41.9, 16-bit mean of groups of 4 on 20 x 2,549,454 in 20 46.7 / 44.1, of groups
 // of 6 on 30 x 5,699,719 in 11 142.9 / 134.3, fp32 mean on 56 x 407,136 in 24 43.4 / 42.2.
 // Not taken, since they gained nothing or lost: 16-bit mean of groups of 3, 16 for 10 chunks (40 shapes) 0.994, up to 1.12, of 5, 8 for 9, 1.00,
 // of 7 and 8 with up to 8 rows 1.00, up to 1.06; fp32 gradient step of groups of 5 and 7, 16 for 19 and 13, 1.00, up to 1.05; 16-bit
-// gradient step of groups of 3, 8 for 10 (40) 0.993, up to 1.066, of 5 and 7 1.01, up to 1.14, of 8, 8 for 6 (70, two million columns
-// and more) 1.000, up to 1.068.
+// gradient step of groups of 3, 8 for 10 (40) 0.993, up to 1.066, of 5 and 7 1.01, up to 1.14, of 8, 8 for 6, with fewer than kFewRows
+// rows 1.00, up to 1.068, on rows below kLongRows up to 1.04, in segments below ten visits of 16 chunks up to 1.066 (70 shapes).
 // On matrices spread over the physical memory what is taken gains less or loses: fp32 mean 0.980 to 1.010, 16-bit mean 0.97 to
 // 1.013, fp32 gradient step 0.983 to 1.030.
 // With groups of 16, at most kFewRows gossiping rows visit 256 KB: their longest cycle's visits then fit one XCD's 4 MB L2.

@@ -425,6 +425,10 @@ struct HierFused16Op {
     static constexpr int kRawPerSlice = G + 3;             // G gradient rows, x, and two registers of v
     static constexpr GatherShape kGather =
         G == 1 ? GatherShape{1, 8, 192, 0} : G <= 4 ? GatherShape{1, 8, 256, 0} : GatherShape{1, 8, 384, 0};
+    static constexpr int visit_kb(int n, int64_t P, int S)                          // see VisitKb
+    {
+        return G == 8 && n >= kFewRows && P >= kLongRows && (S == 1 || P >= static_cast<int64_t>(655360) * S) ? 512 : 0;
+    }
     static constexpr WalkShape kWalk{1, 2, 8, 2};
     static constexpr int kMaxU = 1;
     static constexpr int kStageBytes = kStageBytesPerWave;

@@ -122,7 +122,11 @@ constexpr bool visits(int cut, int whole, int eight, int nine, int64_t cols = 65
 static_assert(visits<Row16Op<false, 8>>(384, 384, 384, 1024) && visits<Row16Op<true, 7>>(384, 384, 384, 896) && visits<Row16Op<true, 6>>(384, 768, 768, 768) &&
               visits<Row16Op<false, 5>>(384, 384, 384, 384) && visits<Row16Op<true, 4>>(256, 512, 512, 512) && visits<Row16Op<true, 3>>(256, 256, 256, 256) &&
               visits<Row16Op<false, 1>>(96, 96, 96, 96) && visits<Push16Op<true>>(192, 192, 192, 192));
-static_assert(visits<HierFused16Op<false, 8>>(384, 384, 384, 384) && visits<HierFused16Op<true, 7>>(384, 384, 384, 384) &&
+static_assert(visits<HierFused16Op<false, 8>>(384, 384, 384, 384, 655359) && visits<HierFused16Op<true, 8>>(384, 384, 384, 384, 599999) &&
+              VisitKb<HierFused16Op<false, 8>>::of(8, 5 * 655360, 5) == 512 && VisitKb<HierFused16Op<true, 8>>::of(8, 5 * 655360 - 1, 5) == 384 &&
+              VisitKb<HierFused16Op<true, 8>>::of(40, 3000000, 1) == 512 && VisitKb<HierFused16Op<true, 8>>::of(40, 2999999, 1) == 384 &&
+              VisitKb<HierFused16Op<true, 8>>::of(7, 9000000, 1) == 384 &&
+              visits<HierFused16Op<true, 7>>(384, 384, 384, 384) &&
               visits<HierFused16Op<true, 5>>(384, 384, 384, 384) && visits<HierFused16Op<false, 3>>(256, 256, 256, 256));
 static_assert(visits<HierFusedOp<8>>(256, 1024, 1024, 1024, 131072) && visits<HierFusedOp<7>>(768, 768, 768, 768) && visits<HierFusedOp<5>>(768, 768, 768, 768) &&
               visits<HierFusedOp<16>>(256, 256, 256, 768) && visits<MeanOp<8>>(256, 512, 512, 768, 65536) && visits<MeanOp<16>>(256, 256, 256, 768) &&
